@@ -306,7 +306,7 @@ int genga_energy(const genga_bodies *b, const genga_params *p, double *out, void
     if (!ws || !out) return GENGA_E_INVAL;
     const KickCfg c = choose_kick_cfg(b->n, p);
     const Layout L = make_layout(b->n, c);
-    hipError_t e = launch_energy(b, p, out, c, L, (char *)ws, (hipStream_t)stream);
+    hipError_t e = launch_energy(b, p, nullptr, out, c, L, (char *)ws, (hipStream_t)stream);
     return e == hipSuccess ? GENGA_OK : hip_fail(e);
 }
 
@@ -322,9 +322,8 @@ int genga_energy_k(const genga_bodies *b, const genga_params *p, genga_pairs *pa
     const KickCfg c = choose_kick_cfg(b->n, p);
     const Layout L = make_layout(b->n, c);
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = launch_energy(b, p, out, c, L, (char *)ws, s);
+    hipError_t e = launch_energy(b, p, pairs, out, c, L, (char *)ws, s);
     if (e != hipSuccess) return hip_fail(e);
-    if ((r = do_kick(b, p, 0.0, nullptr, nullptr, nullptr, pairs, false, ws, stream))) return r;
     e = launch_energy_k_pairs(b, p, pairs, out, L, (char *)ws, s);
     return e == hipSuccess ? GENGA_OK : hip_fail(e);
 }

@@ -4,8 +4,10 @@
 //   U_* = -G m_star sum_i m_i / |x_i|                (Kepler part of H_A)
 //   U   = -G sum_{i<j} m_i m_j / r_ij                (H_B without changeover)
 //   C   = |sum_i m_i v_i|^2 / (2 m_star)             (H_C)
-// U is evaluated as -G/2 sum_i m_i phi_i, phi_i = sum_{j != i} m_j / r_ij,
-// with the rows x column-slices tiling of the kick (columns staged in LDS).
+// U is evaluated as -G sum_i m_i phi_i, phi_i = sum_{j > i} m_j / r_ij, by the
+// one-sided kick's tiles in potential mode (KM_PHI), which evaluate each
+// unordered pair once and, where the encounter list is wanted too (E_K), test
+// it in the same pass.
 // Every sum after the pair loop runs in a fixed order, so the result does not
 // depend on scheduling.
 #include <math.h>
@@ -16,57 +18,6 @@
 namespace genga {
 
 namespace {
-
-constexpr int EB = 256;   // rows per block of the pair-potential kernel
-
-struct EnergyDev {
-    const double *x, *y, *z, *m;
-    int64_t n, npad, slice_len;
-    double *phi;          // [slices][npad]
-    int32_t *status;
-};
-
-// phi partial of row i over the columns of slice blockIdx.y.
-__global__ __launch_bounds__(EB) void k_energy_phi(EnergyDev a)
-{
-    __shared__ double4 sm[EB];
-    const int tid = threadIdx.x;
-    const int64_t i = (int64_t)blockIdx.x * EB + tid;
-    const int64_t j0 = (int64_t)blockIdx.y * a.slice_len;
-    const int64_t j1 = min(a.n, j0 + a.slice_len);
-    double xi, yi, zi;
-    if (i < a.n) {
-        xi = a.x[i]; yi = a.y[i]; zi = a.z[i];
-    } else {
-        xi = yi = zi = __builtin_nan("");   // r2 is NaN: no term, no status
-    }
-    double phi = 0.0;
-    bool coincident = false;
-    for (int64_t t0 = j0; t0 < j1; t0 += EB) {
-        __syncthreads();
-        const int64_t jg = t0 + tid;
-        if (jg < j1) sm[tid] = make_double4(a.x[jg], a.y[jg], a.z[jg], a.m[jg]);
-        __syncthreads();
-        const int tn = (int)min((int64_t)EB, j1 - t0);
-        for (int jj = 0; jj < tn; ++jj) {
-            const double4 b = sm[jj];
-            const double dx = b.x - xi, dy = b.y - yi, dz = b.z - zi;
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            // 1/r from v_rsq_f64 with one Newton correction: y (1 + e/2),
-            // e = 1 - r2 y^2; the remainder 3/8 e^2 is below 5e-15.
-            const double y = __builtin_amdgcn_rsq(r2);
-            const double e = __builtin_fma(-r2, y * y, 1.0);
-            const double rinv = __builtin_fma(y * e, 0.5, y);
-            if (r2 > 0.0) {
-                phi = __builtin_fma(b.w, rinv, phi);
-            } else if (r2 == 0.0 && t0 + jj != i) {
-                coincident = true;
-            }
-        }
-    }
-    if (coincident) atomicOr(a.status, ST_NONFINITE);
-    if (i < a.n) a.phi[(size_t)blockIdx.y * a.npad + i] = phi;
-}
 
 // Per-block sums of the six per-body terms (T, U_*, U, P) in a fixed tree.
 __global__ __launch_bounds__(RB) void k_energy_rows(const double *x, const double *y,
@@ -87,7 +38,7 @@ __global__ __launch_bounds__(RB) void k_energy_rows(const double *x, const doubl
         const double r = __builtin_sqrt(x[i] * x[i] + y[i] * y[i] + z[i] * z[i]);
         v[0] = 0.5 * mi * v2;
         v[1] = -G * m_star * mi / r;
-        v[2] = -0.5 * G * mi * p;
+        v[2] = -G * mi * p;
         v[3] = mi * vx[i];
         v[4] = mi * vy[i];
         v[5] = mi * vz[i];
@@ -249,28 +200,40 @@ hipError_t launch_energy_k_pairs(const genga_bodies *b, const genga_params *p, g
     return hipGetLastError();
 }
 
-hipError_t launch_energy(const genga_bodies *b, const genga_params *p, double *out,
-                         const KickCfg &c, const Layout &L, char *ws, hipStream_t s)
+// Bound by the binary64 vector units: one v_rsq_f64 and 10 other instructions
+// per unordered pair (65,536 bodies: 2.1e9 pairs).  Summing phi_i over j > i
+// instead of all j, and testing for the encounter list in the same pass instead
+// of a second one over every ordered pair, took genga_energy_k there from 3.25
+// to 1.18 ms.
+hipError_t launch_energy(const genga_bodies *b, const genga_params *p, genga_pairs *pairs,
+                         double *out, const KickCfg &c, const Layout &L, char *ws, hipStream_t s)
 {
-    EnergyDev a;
-    a.x = b->x; a.y = b->y; a.z = b->z; a.m = b->m;
-    a.n = b->n;
-    a.npad = L.npad;
-    a.slice_len = c.slice_len;
-    a.phi = (double *)(ws + L.part);
-    a.status = (int32_t *)(ws + L.status);
-    const int slices = (int)((b->n + c.slice_len - 1) / c.slice_len);
+    // the one-sided kick's tiles, whatever the kick's own form (with the
+    // caller's rows per thread; by default one: two share each column's LDS
+    // reads but leave 12 instead of 24 tiles per compute unit at 65,536
+    // bodies, and the last ones run alone: 1.32 ms)
+    KickCfg e = c;
+    e.use_sym = false;
+    KickLaunch k{};
+    k.x = b->x; k.y = b->y; k.z = b->z; k.m = b->m; k.rc = b->rc;
+    k.n = b->n;
+    k.precision = GENGA_FP64;
+    k.phi = true;
+    k.pairs = pairs;
+    if (pairs) {
+        k.ev0 = p->prof_events[0];
+        k.ev1 = p->prof_events[1];
+    }
+    hipError_t err = launch_kick(k, e, L, ws, s);
+    if (err != hipSuccess) return err;
     // phi takes slices * npad doubles of the partial-sum region (sized for
     // 5 * c.slices * npad); the block sums follow it.
-    double *bpart = a.phi + (size_t)slices * L.npad;
-    const unsigned gx = (unsigned)((b->n + EB - 1) / EB);
-    hipLaunchKernelGGL(k_energy_phi, dim3(gx, (unsigned)slices), dim3(EB), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    double *phi = (double *)(ws + L.part);
+    double *bpart = phi + (size_t)e.slices * L.npad;
     hipLaunchKernelGGL(k_energy_rows, dim3((unsigned)L.nb), dim3(RB), 0, s, b->x, b->y, b->z,
-                       b->vx, b->vy, b->vz, b->m, a.phi, b->n, L.npad, slices, p->G, p->m_star,
+                       b->vx, b->vy, b->vz, b->m, phi, b->n, L.npad, e.slices, p->G, p->m_star,
                        bpart);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((err = hipGetLastError()) != hipSuccess) return err;
     hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(RB), 0, s, bpart, L.nb, p->m_star, out);
     return hipGetLastError();
 }

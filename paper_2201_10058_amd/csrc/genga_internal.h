@@ -188,6 +188,8 @@ struct KickLaunch {
     double hfac;               // batch: v += hfac * dt_s * a
     int precision;
     bool forces;               // false: encounter list only
+    bool phi = false;          // energy: sums of m_j / r_ij over j > i, [slices][npad] in L.part,
+                               // with the encounter list if pairs (forces false)
     genga_pairs *pairs;        // optional
     void *ev0, *ev1;           // optional timing events around the main kernel
     const TileDesc *tiles;     // batch: device tile list (else null)
@@ -222,8 +224,9 @@ hipError_t launch_hc_drift(genga_bodies *b, double m_star, double h, double mu, 
 hipError_t launch_gr(genga_bodies *b, const genga_params *p, double h, const Layout &L, char *ws,
                      hipStream_t s);
 hipError_t launch_clear_status(char *ws, hipStream_t s);
-hipError_t launch_energy(const genga_bodies *b, const genga_params *p, double *out,
-                         const KickCfg &c, const Layout &L, char *ws, hipStream_t s);
+// pairs (nullable): also the encounter list of the positions and radii.
+hipError_t launch_energy(const genga_bodies *b, const genga_params *p, genga_pairs *pairs,
+                         double *out, const KickCfg &c, const Layout &L, char *ws, hipStream_t s);
 // out[5] = out[0] + the changeover-potential correction over the listed pairs.
 hipError_t launch_energy_k_pairs(const genga_bodies *b, const genga_params *p, genga_pairs *pairs,
                                  double *out, const Layout &L, char *ws, hipStream_t s);

@@ -122,7 +122,12 @@ enum KickMode : int {
     KM_F64 = 0,    // binary64 pair arithmetic
     KM_MIXED = 1,  // binary32 pair arithmetic on binary64 differences
     KM_PAIRS = 2,  // encounter list only (no forces)
+    KM_PHI = 3,    // potential sums (energy), with or without the encounter list
 };
+// KM_PAIRS and KM_PHI need each unordered pair once: row i takes only the
+// columns j > i (tiles and staged chunks wholly below the diagonal are
+// skipped), half the pairs of a force.
+constexpr bool upper_only(int mode) { return mode == KM_PAIRS || mode == KM_PHI; }
 
 // Per-lane state of the kick: IPT rows per lane.
 template <int IPT>
@@ -308,6 +313,50 @@ __device__ __forceinline__ void interact(const KickDev &a, Rows<IPT> &R, const d
     }
 }
 
+// Potential of the lane's rows from column j (KM_PHI): R.ax[q] += m_j / r_ij for
+// j > i.  b = (x_j, y_j, z_j, m_j / 2); with y = v_rsq_f64(r^2) (relative error
+// below 2^-24) and one Newton step m_j / r = (m_j / 2) y (3 - r^2 y^2), its
+// remainder 3/8 e^2 below 5e-15.  DIAG: the chunk reaches down to the rows, so
+// the columns j <= i are masked out.  A coincident pair leaves a NaN in the
+// sum, which the end of the tile resolves (phi_exact).  gate2 as in interact.
+template <int IPT, bool DIAG>
+__device__ __forceinline__ void phi_term(const KickDev &a, Rows<IPT> &R, const double4 b,
+                                         const double gate2, const int64_t jg, const double c3,
+                                         const int64_t wave_g, int *wcnt, const double *rc2j64)
+{
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+        const double dx = b.x - R.xi[q];
+        const double dy = b.y - R.yi[q];
+        const double dz = b.z - R.zi[q];
+        const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+        const bool after = !DIAG || jg > R.ii[q];
+        const bool cand = r2 <= gate2 && after;
+        const double yv = __builtin_amdgcn_rsq(r2);
+        double t = yv * __builtin_fma(-r2, yv * yv, c3);
+        if (DIAG && !after) t = 0.0;
+        if (cand)
+            slow_pair<IPT, false>(a, R, q, jg, r2, *rc2j64, 0.0, 0.0, 0.0, wave_g, wcnt);
+        R.ax[q] = __builtin_fma(b.w, t, R.ax[q]);
+    }
+}
+
+// The potential of row i over the columns [j0, j1) after i, term by term: a
+// coincident pair is reported and gives no term, a NaN separation gives none.
+__device__ double phi_exact(const KickDev &a, int64_t i, int64_t j0, int64_t j1)
+{
+    double phi = 0.0;
+    for (int64_t j = j0 > i ? j0 : i + 1; j < j1; ++j) {
+        const double dx = a.x[j] - a.x[i], dy = a.y[j] - a.y[i], dz = a.z[j] - a.z[i];
+        const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+        const double y = __builtin_amdgcn_rsq(r2);
+        const double e = __builtin_fma(-r2, y * y, 1.0);
+        if (r2 > 0.0) phi = __builtin_fma(a.m[j], __builtin_fma(y * e, 0.5, y), phi);
+        else if (r2 == 0.0) atomicOr(a.status, ST_NONFINITE);
+    }
+    return phi;
+}
+
 // Mixed mode: add the binary32 partial sums into the binary64 accumulators.
 template <int IPT, int MODE>
 __device__ __forceinline__ void fold(Rows<IPT> &R)
@@ -360,7 +409,9 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
     const double *t_rc2 = sm.rc2 + vzero;
     const double *t_m = sm.m + vzero;
     const double *t_irc = sm.irc + vzero;
-
+    const double c3 = 3.0 + (double)vzero;
+    // the energy alone has no critical radii: nothing is inside a negative gate
+    const bool with_rc = MODE != KM_PHI || a.emit;
 
     Rows<IPT> R;
 #pragma unroll
@@ -371,9 +422,9 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
             R.xi[q] = a.x[R.ii[q]];
             R.yi[q] = a.y[R.ii[q]];
             R.zi[q] = a.z[R.ii[q]];
-            const double r = a.rc[R.ii[q]];
+            const double r = with_rc ? a.rc[R.ii[q]] : 0.0;
             R.rc2i[q] = r * r;
-            R.iri[q] = 1.0 / r;
+            R.iri[q] = MODE == KM_F64 || MODE == KM_MIXED ? 1.0 / r : 0.0;
         } else {
             // rows past the end: NaN positions never enter the slow path
             R.xi[q] = R.yi[q] = R.zi[q] = __builtin_nan("");
@@ -398,14 +449,17 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
     int *wcnt = &sm.wcnt[w];
     if (lane == 0) __hip_atomic_store(wcnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 
-    for (int64_t t0 = j0; t0 < j1; t0 += NT) {
+    // (uniform over the block)
+    int64_t first = j0;
+    if (upper_only(MODE) && td.row0 > j0) first = j0 + (td.row0 - j0) / NT * NT;
+    for (int64_t t0 = first; t0 < j1; t0 += NT) {
         __syncthreads();
         {
             const int q = tid;
             const int64_t jg = t0 + q;
             double g = 0.0;
             if (jg < j1) {
-                const double rcj = a.rc[jg];
+                const double rcj = with_rc ? a.rc[jg] : 0.0;
                 if (!(rcj >= 0.0 && rcj < INFINITY)) atomicOr(a.status, ST_RCRIT);
                 // test-particle mode 1: a test particle acts on no body (it is
                 // still tested for encounters with the massive rows)
@@ -416,11 +470,12 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
                     sm.m[q] = mj;
                 } else {
                     sm.xyzm[q] = make_double4(a.x[jg], a.y[jg], a.z[jg],
-                                              MODE == KM_F64 ? 1.5 * mj : mj);
-                    sm.m[q] = mj;
+                                              MODE == KM_F64 ? 1.5 * mj
+                                                             : (MODE == KM_PHI ? 0.5 * mj : mj));
+                    if (MODE == KM_F64) sm.m[q] = mj;
                 }
                 sm.rc2[q] = rcj * rcj;
-                if (MODE != KM_PAIRS) sm.irc[q] = 1.0 / rcj;
+                if (MODE == KM_F64 || MODE == KM_MIXED) sm.irc[q] = 1.0 / rcj;
                 g = rcj * rcj;
             }
             if (MODE != KM_MIXED) {
@@ -434,10 +489,29 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
             g2 = rg;
 #pragma unroll
             for (int v = 0; v < NT / 64; ++v) g2 = __builtin_fmax(g2, sm.cmax[v]);
-            g2 = wave_uniform(g2);
+            g2 = with_rc ? wave_uniform(g2) : -1.0;
         }
         const int tn = (int)min((int64_t)NT, j1 - t0);
         int jj = 0;
+        if constexpr (MODE == KM_PHI) {
+            // (wave-uniform: the chunk lies after every row of the wave)
+            if (t0 >= rowbase + 64 * IPT) {
+                for (; jj + 4 <= tn; jj += 4) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        phi_term<IPT, false>(a, R, t_xyzm[jj + u], g2, t0 + jj + u, c3, wave_g,
+                                             wcnt, t_rc2 + jj + u);
+                }
+                for (; jj < tn; ++jj)
+                    phi_term<IPT, false>(a, R, t_xyzm[jj], g2, t0 + jj, c3, wave_g, wcnt,
+                                         t_rc2 + jj);
+            } else if (t0 + tn > rowbase) {
+                for (; jj < tn; ++jj)
+                    phi_term<IPT, true>(a, R, t_xyzm[jj], g2, t0 + jj, c3, wave_g, wcnt,
+                                        t_rc2 + jj);
+            }
+            continue;
+        }
         for (; jj + 4 <= tn; jj += 4) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
@@ -451,7 +525,7 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
         fold<IPT, MODE>(R);
     }
 
-    constexpr int PS = MODE == KM_MIXED ? 4 : 3;
+    constexpr int PS = MODE == KM_MIXED ? 4 : (MODE == KM_PHI ? 1 : 3);
     // (a tile's rows are all massive or all test particles)
     const PartRows pr = part_rows(a.tp, a.nm, a.mpad, a.s_m, a.npad, PS, td.row0);
     const PartRows cr = part_rows(a.tp, a.nm, a.mpad, a.s_m, a.npad, 1, td.row0);
@@ -460,9 +534,12 @@ __device__ __forceinline__ void process_tile(const KickDev &a, KickSmem<NT> &sm,
         if (R.ii[q] >= 0) {
             if (MODE != KM_PAIRS) {
                 double *p = a.part + pr.base + (size_t)s * PS * pr.stride + R.ii[q];
+                if (MODE == KM_PHI && R.ax[q] != R.ax[q]) R.ax[q] = phi_exact(a, R.ii[q], j0, j1);
                 p[0] = R.ax[q];
-                p[pr.stride] = R.ay[q];
-                p[2 * pr.stride] = R.az[q];
+                if (MODE != KM_PHI) {
+                    p[pr.stride] = R.ay[q];
+                    p[2 * pr.stride] = R.az[q];
+                }
                 if (MODE == KM_MIXED) p[3 * pr.stride] = R.mag[q];
             }
             if (a.emit) a.cnt[cr.base + (size_t)s * cr.stride + R.ii[q]] = R.kc[q];
@@ -1378,10 +1455,13 @@ Layout make_layout(int64_t n, const KickCfg &c, int64_t S)
 template <int NT, int IPT, int MODE>
 static void launch_k(const KickDev &d, const KickCfg &c, hipStream_t s)
 {
-    if (d.tiles)
-        hipLaunchKernelGGL((k_kick_persistent<NT, IPT, MODE>), dim3(c.grid), dim3(NT), 0, s, d);
-    else
-        hipLaunchKernelGGL((k_kick<NT, IPT, MODE>), dim3(c.gx, c.gy), dim3(NT), 0, s, d);
+    if constexpr (!upper_only(MODE)) {   // (batches have neither)
+        if (d.tiles) {
+            hipLaunchKernelGGL((k_kick_persistent<NT, IPT, MODE>), dim3(c.grid), dim3(NT), 0, s, d);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_kick<NT, IPT, MODE>), dim3(c.gx, c.gy), dim3(NT), 0, s, d);
 }
 
 template <int NT, int IPT, int MODE>
@@ -1410,6 +1490,7 @@ static void launch_mode(const KickDev &d, const KickCfg &c, int mode, hipStream_
 {
     if (mode == KM_MIXED) launch_k<NT, IPT, KM_MIXED>(d, c, s);
     else if (mode == KM_PAIRS) launch_k<NT, IPT, KM_PAIRS>(d, c, s);
+    else if (mode == KM_PHI) launch_k<NT, IPT, KM_PHI>(d, c, s);
     else launch_k<NT, IPT, KM_F64>(d, c, s);
 }
 
@@ -1449,7 +1530,9 @@ hipError_t launch_kick(const KickLaunch &k, const KickCfg &c, const Layout &L, c
     // no pair inside rho_ij can be missed.
     d.widen = MIXED_NEAR * MIXED_NEAR * (1.0 + 0x1p-14);
 
-    const int mode = !k.forces ? KM_PAIRS : (k.precision == GENGA_MIXED ? KM_MIXED : KM_F64);
+    const int mode = k.phi ? KM_PHI
+                           : (!k.forces ? KM_PAIRS
+                                        : (k.precision == GENGA_MIXED ? KM_MIXED : KM_F64));
     const bool refine = mode == KM_MIXED;
     const bool symb = c.use_symb && mode == KM_F64 && k.tiles;
     const bool sym = (c.use_sym && (mode == KM_F64 || mode == KM_MIXED) && !k.tiles && c.tp == 0) || symb;

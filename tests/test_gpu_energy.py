@@ -153,3 +153,47 @@ def test_fixed_rc_map_conserves_e_k_on_gpu(dev):
     assert N.read_status(ws) == N.OK
     _say("fixed-rc close pass: max |dE|/E", de, "max |dE_K|/E_K", dk)
     assert dk < 0.01 * de
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 255, 256, 257, 511, 513, 1100])
+@pytest.mark.parametrize("ipt, slices", [(0, 0), (2, 0), (1, 1), (2, 3)])
+def test_energy_k_tile_edges(dev, n, ipt, slices):
+    # the potential pass takes each unordered pair once: sizes around its row
+    # blocks (256 and 512), staged chunks (256) and column slices, with the
+    # encounter list of the same pass.  At most n^2 / 2 terms of relative
+    # error below 1e-15 in sums of one sign: 1e-13, as above.
+    d = W.random_cloud(n, seed=400 + n, rc_scale=0.3)
+    st = N.State.from_numpy(d)
+    cfg = N.Config(G=G, ipt=ipt, slices=slices)
+    ws = N.Workspace(n, cfg)
+    pl = N.PairList(n * n)
+    out = N.energy_k(st, cfg, ws, pl).cpu().numpy()
+    assert N.read_status(ws) == N.OK
+    oi, oj, cnt = oracle.pairs(d["x"], d["y"], d["z"], d["rc"], cap=n * n)
+    pi, pj, c = pl.result()
+    assert c == cnt and np.array_equal(pi, oi[:cnt]) and np.array_equal(pj, oj[:cnt])
+    if n > 1:
+        still = {**d, **{k: np.zeros(n) for k in ("vx", "vy", "vz")}}
+        ref = oracle.energy(still, G, 1e-300)
+        assert abs(out[3] - ref) <= 1e-13 * abs(ref)
+        assert abs(out[0] - oracle.energy(d, G, 1.0)) <= 1e-13 * abs(out[0])
+    # without the list (no critical radii read): the same energies
+    e = N.energy(st, cfg, ws).cpu().numpy()
+    assert np.array_equal(e, out[:5])
+
+
+def test_energy_coincident_pair_leaves_the_other_terms(dev):
+    # a coincident pair is reported and gives no term of its own
+    d = dict(W.random_cloud(300, seed=33))
+    for k in ("x", "y", "z"):
+        d[k] = d[k].copy()
+        d[k][200] = d[k][17]
+    for k in ("vx", "vy", "vz"):
+        d[k] = np.zeros(300)
+    e, code = _energy(d, m_star=1e-300)
+    assert code == N.E_NONFINITE
+    U = 0.0
+    for i in range(300):
+        r = np.sqrt(sum((d[k][i + 1:] - d[k][i]) ** 2 for k in ("x", "y", "z")))
+        U -= G * d["m"][i] * np.sum((d["m"][i + 1:][r > 0] / r[r > 0]))
+    assert abs(e[3] - U) <= 1e-13 * abs(U)
