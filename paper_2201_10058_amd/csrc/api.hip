@@ -92,14 +92,9 @@ static int status_to_code(int32_t st)
     return GENGA_OK;
 }
 
-// fuse_hc: also apply the Sun kick x += h P / m_star after the velocities,
-// with P from the momentum partials in L.hc2 (genga_step's second half).
-static int do_kick(const genga_bodies *b, const genga_params *p, double h, double *ax, double *ay,
-                   double *az, genga_pairs *pairs, bool forces, void *ws, void *stream,
-                   int ev_slot = 0, bool fuse_hc = false)
+static KickLaunch kick_launch(const genga_bodies *b, const genga_params *p, double h, double *ax,
+                              double *ay, double *az, genga_pairs *pairs, bool forces, int ev_slot)
 {
-    const KickCfg c = choose_kick_cfg(b->n, p);
-    const Layout L = make_layout(b->n, c);
     KickLaunch k;
     k.x = b->x; k.y = b->y; k.z = b->z; k.m = b->m; k.rc = b->rc;
     k.vx = b->vx; k.vy = b->vy; k.vz = b->vz;
@@ -118,6 +113,18 @@ static int do_kick(const genga_bodies *b, const genga_params *p, double h, doubl
     k.sys_slices = nullptr;
     k.sys_dt = nullptr;
     k.sys_off = nullptr;
+    return k;
+}
+
+// fuse_hc: also apply the Sun kick x += h P / m_star after the velocities,
+// with P from the momentum partials in L.hc2 (genga_step's second half).
+static int do_kick(const genga_bodies *b, const genga_params *p, double h, double *ax, double *ay,
+                   double *az, genga_pairs *pairs, bool forces, void *ws, void *stream,
+                   int ev_slot = 0, bool fuse_hc = false)
+{
+    const KickCfg c = choose_kick_cfg(b->n, p);
+    const Layout L = make_layout(b->n, c);
+    KickLaunch k = kick_launch(b, p, h, ax, ay, az, pairs, forces, ev_slot);
     if (fuse_hc) {
         k.px = b->x; k.py = b->y; k.pz = b->z;
         k.hc_part = (const double *)((char *)ws + L.hc2);
@@ -405,12 +412,19 @@ int genga_step(genga_bodies *b, const genga_params *p, genga_pairs *pairs, void 
     if (gr && (levels || p->tp_mode != 0)) return GENGA_E_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     const double h = 0.5 * p->dt;
-    const Layout L = make_layout(b->n, choose_kick_cfg(b->n, p));
+    const KickCfg c = choose_kick_cfg(b->n, p);
+    const Layout L = make_layout(b->n, c);
     const LevelLayout V = make_level_layout(b->n, p, L.total);
     genga_pairs e0;
     if (levels) e0 = level0_pairs(V, (char *)ws);
-    hipError_t e = launch_rcrit(b, p, (char *)ws, s);
-    if (e != hipSuccess) return hip_fail(e);
+    hipError_t e;
+    if (!levels && !gr && c.use_rows) {
+        KickLaunch k = kick_launch(b, p, h, nullptr, nullptr, nullptr, pairs, true, 0);
+        if ((e = launch_step_rows(k, b, p, L, (char *)ws, s)) != hipSuccess) return hip_fail(e);
+        if (p->flags & GENGA_FLAG_NOSYNC) return GENGA_OK;
+        return genga_read_status(ws, stream);
+    }
+    if ((e = launch_rcrit(b, p, (char *)ws, s)) != hipSuccess) return hip_fail(e);
     if ((r = do_kick(b, p, h, nullptr, nullptr, nullptr, levels ? &e0 : pairs, true, ws, stream)))
         return r;
     if (!levels && !gr) {

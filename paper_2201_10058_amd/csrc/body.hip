@@ -1,6 +1,7 @@
 // O(N) operators of the base step: critical radii (eq. rcrit), HC (eq. Hc)
 // and the Keplerian drift FG (Kepler part of eq. Ha), GENGA II Sect. 2 and
 // Appendix A.  One thread per body; reductions run in a fixed order.
+#include "device_common.h"
 #include "genga_internal.h"
 #include "kepler.h"
 
@@ -19,12 +20,7 @@ __global__ __launch_bounds__(RB) void k_rcrit(const double *x, const double *y, 
 {
     const int64_t i = (int64_t)blockIdx.x * RB + threadIdx.x;
     if (i >= n) return;
-    const double r = __builtin_sqrt(x[i] * x[i] + y[i] * y[i] + z[i] * z[i]);
-    const double v = __builtin_sqrt(vx[i] * vx[i] + vy[i] * vy[i] + vz[i] * vz[i]);
-    const double rh = r * cbrt(m[i] / (3.0 * m_star));
-    const double a = n1 * rh;
-    const double b = n2 * fabs(dt) * v;
-    const double out = a > b ? a : b;
+    const double out = rcrit_of(x[i], y[i], z[i], vx[i], vy[i], vz[i], m[i], m_star, dt, n1, n2);
     if (!(out >= 0.0 && out < INFINITY)) atomicOr(status, ST_RCRIT);
     rc[i] = out;
 }
@@ -229,13 +225,12 @@ hipError_t launch_rcrit(const genga_bodies *b, const genga_params *p, char *ws, 
 hipError_t launch_hc(genga_bodies *b, double m_star, double h, const Layout &L, char *ws,
                      hipStream_t s, int64_t nsum)
 {
-    double *hc = (double *)(ws + L.hc);
-    hipLaunchKernelGGL(k_momentum_partial, dim3((unsigned)L.nb), dim3(RB), 0, s, b->vx, b->vy,
-                       b->vz, b->m, nsum, hc);
-    hipError_t e = hipGetLastError();
+    // (row groups have no test-particle modes: nsum is n)
+    if (L.hc_rows) return launch_hc_rows(b, m_star, h, L, ws, s);
+    hipError_t e = launch_momentum(b, L, ws, s, nsum);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_hc_apply, dim3((unsigned)L.nb), dim3(RB), 0, s, b->x, b->y, b->z, b->n,
-                       hc, L.nb, h, m_star);
+                       (const double *)(ws + L.hc), L.nb, h, m_star);
     return hipGetLastError();
 }
 

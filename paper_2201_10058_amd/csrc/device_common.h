@@ -76,12 +76,32 @@ __device__ __forceinline__ double ordered_sum(const double *p, size_t stride, in
     return acc;
 }
 
+// Critical radius of one body, eq. (rcrit): max(n1 R_H, n2 |dt| |v|),
+// R_H = |x| (m / 3 m_star)^(1/3).
+__device__ __forceinline__ double rcrit_of(double x, double y, double z, double vx, double vy,
+                                           double vz, double m, double m_star, double dt,
+                                           double n1, double n2)
+{
+    const double r = __builtin_sqrt(x * x + y * y + z * z);
+    const double v = __builtin_sqrt(vx * vx + vy * vy + vz * vz);
+    const double a = n1 * (r * cbrt(m / (3.0 * m_star)));
+    const double b = n2 * fabs(dt) * v;
+    return a > b ? a : b;
+}
+
 // max of two non-negative doubles in one v_max_f64 (the generic fmax adds
 // NaN-quieting canonicalisations; the critical radii are validated instead).
 __device__ __forceinline__ double vmax_f64(double a, double b)
 {
     double r;
     asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+__device__ __forceinline__ double vmin_f64(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
 

@@ -110,6 +110,13 @@ hipError_t launch_scatter_sym(const SymShape &h, const SymBatch *b, const double
                               const int32_t *rowloc, const int64_t *boff, genga_pairs *pairs,
                               hipStream_t s);
 
+// Row-group kick of small systems (csrc/rows.h): rows per team of 256 threads
+// and the most bodies it takes (the bitmap's words per row).
+constexpr int ROWS_G = 4;
+constexpr int64_t ROWS_MAX = 8192;
+// the kick and the base step of up to this many bodies run in one workgroup
+constexpr int ONE_MAX = 128;
+
 // Launch shape of the kick.
 struct KickCfg {
     int nt = KB;              // threads per block (64 or 256)
@@ -142,6 +149,8 @@ struct KickCfg {
     bool use_symb = false;
     int64_t symb_S = 0, symb_T = 0, symb_cols = 0;
     int symb_W = 0;           // columns per slice of every system (512, 256 or 128)
+    // binary64 forces of one small all-massive system: the row-group kick
+    bool use_rows = false;
 };
 
 // Byte offsets of the workspace regions.
@@ -155,6 +164,7 @@ struct Layout {
     size_t wcount = 0;     // int32  [nwaves]           staged pairs per wave
     size_t hc = 0;         // double [nb][3]            momentum partials
     size_t hc2 = 0;        // double [nb][3]            momentum partials (second buffer)
+    bool hc_rows = false;  // the momentum as the balanced tree of a small system (use_rows)
     size_t rlist = 0;      // int32  [npad]             mixed: rows to evaluate in binary64
     size_t gru = 0;        // double [3][npad]          post-Newtonian: new heliocentric velocities
     size_t grp = 0;        // double [nb][4]            post-Newtonian: partial sums of m u', m
@@ -208,6 +218,14 @@ struct KickLaunch {
 };
 hipError_t launch_kick(const KickLaunch &k, const KickCfg &c, const Layout &L, char *ws,
                        hipStream_t s);
+
+// Row-group form (KickCfg::use_rows): the kick; HC; the base step (k:
+// the kick's arguments with h = dt / 2 and the list; changed here).
+hipError_t launch_kick_rows(const KickLaunch &k, const Layout &L, char *ws, hipStream_t s);
+hipError_t launch_hc_rows(genga_bodies *b, double m_star, double h, const Layout &L, char *ws,
+                          hipStream_t s);
+hipError_t launch_step_rows(KickLaunch &k, genga_bodies *b, const genga_params *p, const Layout &L,
+                            char *ws, hipStream_t s);
 
 hipError_t launch_rcrit(const genga_bodies *b, const genga_params *p, char *ws, hipStream_t s);
 // x_i += h P / m_star for every body, P summed over bodies [0, nsum).

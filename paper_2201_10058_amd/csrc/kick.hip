@@ -1376,6 +1376,10 @@ KickCfg choose_kick_cfg(int64_t n, const genga_params *p)
             c.sym = h;
         }
     }
+    // below the symmetric form's sizes: the row-group kick, unless the caller
+    // sets the tile shape of the one-sided one
+    c.use_rows = plain && !c.use_sym && n <= ROWS_MAX && c.ipt == 1 && (!p || p->slices == 0) &&
+                 (!p || p->precision == GENGA_FP64);
     return c;
 }
 
@@ -1422,6 +1426,7 @@ Layout make_layout(int64_t n, const KickCfg &c, int64_t S)
     off = align256(off + sizeof(double) * 3 * (size_t)L.nb);
     L.hc2 = off;
     off = align256(off + sizeof(double) * 3 * (size_t)L.nb);
+    L.hc_rows = c.use_rows;
     L.rlist = off;
     off = align256(off + sizeof(int32_t) * (size_t)L.npad);
     L.gru = off;
@@ -1497,6 +1502,7 @@ static void launch_mode(const KickDev &d, const KickCfg &c, int mode, hipStream_
 hipError_t launch_kick(const KickLaunch &k, const KickCfg &c, const Layout &L, char *ws,
                        hipStream_t s)
 {
+    if (c.use_rows && k.forces && !k.tiles) return launch_kick_rows(k, L, ws, s);
     KickDev d;
     d.x = k.x; d.y = k.y; d.z = k.z; d.m = k.m; d.rc = k.rc;
     d.n = k.n;

@@ -1,0 +1,256 @@
+// Kick of a small system by row groups: device code of csrc/rows.hip.
+//
+// A team of 256 threads (4 waves) owns ROWS_G = 4 rows and takes every column:
+// thread t the columns t, t + 256, ..., each against the 4 rows, whose data
+// sit in scalar registers (8 rows needed more of them than there are).  A lane
+// loads 5 values per column (the next column's while it works on this one's)
+// and evaluates 4 independent pairs, so no column is staged.
+// Pairs inside the critical radius are only marked in an LDS bitmap
+// (row x column) and leave no term in the loop; afterwards the words of a row
+// are shared out over a wave's lanes, which evaluate the marked pairs side by
+// side.  The bitmap, masked to j > i, is also the encounter list of the rows
+// in canonical order.  The self pair (r^2 = 0) reaches the marking branch like a
+// close pair and is dropped there: once per row, in one wave.
+// Every sum runs in a fixed order that does not depend on the launch.
+#pragma once
+
+#include "device_common.h"
+#include "genga_internal.h"
+
+namespace genga {
+
+// 1/sqrt(v) from v_rsq_f64 with a second-order correction (relative error a
+// few 2^-53).
+__device__ __forceinline__ double rsq_full(double v)
+{
+    const double y = __builtin_amdgcn_rsq(v);
+    const double e = __builtin_fma(-v, y * y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+// Columns of a system (global memory or LDS).
+struct RowsCols {
+    const double *x, *y, *z, *m, *rc;
+};
+
+// LDS of one team.
+struct RowsTeam {
+    uint64_t bits[ROWS_G][ROWS_MAX / 64];
+    double part[4][3 * ROWS_G];
+    double slow[ROWS_G][3];
+    int32_t cnt[ROWS_G];
+};
+
+// a and b summed over the two halves of the wave: lanes 0-31 hold a's sums
+// (l + (l + 32)), lanes 32-63 b's.
+__device__ __forceinline__ double halve32(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// The same over neighbouring rows of 16 lanes: even rows hold a's sums, odd
+// rows b's.
+__device__ __forceinline__ double halve16(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over the 16 lanes of a row, in every lane of it up to rounding order
+// (callers take lane 0's).
+__device__ __forceinline__ double row16_sum(double v)
+{
+    v += dpp_f64<0x128>(v);   // row_ror:8
+    v += dpp_f64<0x124>(v);   // row_ror:4
+    v += dpp_f64<0x122>(v);   // row_ror:2
+    v += dpp_f64<0x121>(v);   // row_ror:1
+    return v;
+}
+
+static_assert(ROWS_G == 4, "12 sums: two halvings leave 3 per row of 16 lanes, one row group per wave");
+
+// One column against the rows.
+__device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROWS_G],
+                                            const double (&yi)[ROWS_G], const double (&zi)[ROWS_G],
+                                            const double (&rc2i)[ROWS_G], double rg, int n, int r0,
+                                            int j, double xj, double yj, double zj, double mj,
+                                            double rcj, double c53, int word, int lane,
+                                            int32_t *status, double (&acc)[3 * ROWS_G])
+{
+    double dx[ROWS_G], dy[ROWS_G], dz[ROWS_G], r2[ROWS_G], sc[ROWS_G];
+    const double m15 = 1.5 * mj, rc2j = rcj * rcj;
+    double near = INFINITY;
+#pragma unroll
+    for (int q = 0; q < ROWS_G; ++q) {
+        dx[q] = xj - xi[q];
+        dy[q] = yj - yi[q];
+        dz[q] = zj - zi[q];
+        r2[q] = __builtin_fma(dz[q], dz[q], __builtin_fma(dy[q], dy[q], dx[q] * dx[q]));
+        near = vmin_f64(near, r2[q]);
+        // m r^-3 = (3/2 m) y^3 (5/3 - r^2 y^2) to first order, as in the other kicks
+        const double y = __builtin_amdgcn_rsq(r2[q]);
+        const double y2 = y * y;
+        sc[q] = (m15 * (y2 * y)) * __builtin_fma(-r2[q], y2, c53);
+    }
+    // rare: some lane has a row inside the larger of the rows' and its own radius
+    if (__any(near <= vmax_f64(rg, rc2j))) {
+#pragma unroll
+        for (int q = 0; q < ROWS_G; ++q) {
+            const double rho2 = rc2i[q] > rc2j ? rc2i[q] : rc2j;
+            const bool same = r2[q] == 0.0;
+            // (a column past the end repeats the last body without its mass)
+            const bool inside = r2[q] < rho2 && !same && j < n;
+            if (same && j < n && j != r0 + q) atomicOr(status, ST_NONFINITE);
+            if (inside || same) sc[q] = 0.0;
+            const uint64_t mask = __ballot(inside);
+            if (mask && lane == 0) sm.bits[q][word] = mask;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < ROWS_G; ++q) {
+        acc[3 * q + 0] = __builtin_fma(dx[q], sc[q], acc[3 * q + 0]);
+        acc[3 * q + 1] = __builtin_fma(dy[q], sc[q], acc[3 * q + 1]);
+        acc[3 * q + 2] = __builtin_fma(dz[q], sc[q], acc[3 * q + 2]);
+    }
+}
+
+// A lane's column values; past the end, the last body's.
+struct RowsColumn {
+    double x, y, z, m, rc;
+};
+
+__device__ __forceinline__ RowsColumn rows_load(const RowsCols &c, int n, int j)
+{
+    // (32-bit byte offsets from scalar bases)
+    const uint32_t o = (uint32_t)(j < n ? j : n - 1) * 8u;
+    auto at = [o](const double *p) { return *(const double *)((const char *)p + o); };
+    return {at(c.x), at(c.y), at(c.z), at(c.m), at(c.rc)};
+}
+
+// Accelerations / G of the rows [r0, r0 + ROWS_G) from the columns [0, n), and
+// their encounter pairs j > i as sm.cnt and sm.bits; the lanes t < ROWS_G of
+// the team's first wave return row r0 + t's sums in a3.  tid: thread of the
+// team; every thread of the block passes here (block barriers).  Rows from n
+// on are computed at a far place and are to be ignored.
+__device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int tid, RowsTeam &sm,
+                                          int32_t *status, double c53k, double a3[3])
+{
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nw = (n + 63) >> 6;
+    RowsColumn A = rows_load(c, n, tid), B;
+    for (int q = 0; q < ROWS_G; ++q)
+        for (int k = tid; k < nw; k += 256) sm.bits[q][k] = 0;
+    // (an opaque zero keeps the constant in vector registers)
+    const double c53 = c53k + (double)(int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
+    double xi[ROWS_G], yi[ROWS_G], zi[ROWS_G], rc2i[ROWS_G], rg = 0.0;
+#pragma unroll
+    for (int q = 0; q < ROWS_G; ++q) {
+        const int i = r0 + q < n ? r0 + q : n - 1;
+        const bool real = r0 + q < n;
+        const double r = wave_uniform(c.rc[i]);
+        xi[q] = wave_uniform(real ? c.x[i] : 1e18);
+        yi[q] = wave_uniform(real ? c.y[i] : 1e18);
+        zi[q] = wave_uniform(real ? c.z[i] : 1e18);
+        rc2i[q] = wave_uniform(real ? r * r : 0.0);
+        rg = rc2i[q] > rg ? rc2i[q] : rg;
+    }
+    rg = wave_uniform(rg);
+    double acc[3 * ROWS_G] = {};
+    __syncthreads();
+
+    auto column = [&](int j0, RowsColumn v) {
+        const int j = j0 + tid;
+        if (j >= n) v.m = 0.0;
+        // (the rows of team 0 meet every column)
+        if (r0 == 0 && !(v.rc >= 0.0 && v.rc < INFINITY)) atomicOr(status, ST_RCRIT);
+        rows_column(sm, xi, yi, zi, rc2i, rg, n, r0, j, v.x, v.y, v.z, v.m, v.rc, c53,
+                    (j0 >> 6) + w, lane, status, acc);
+    };
+    for (int j0 = 0; j0 < n; j0 += 512) {
+        B = rows_load(c, n, j0 + 256 + tid);
+        column(j0, A);
+        if (j0 + 256 >= n) break;
+        A = rows_load(c, n, j0 + 512 + tid);
+        column(j0 + 256, B);
+    }
+    // 12 sums over the wave: two halvings, then the 16 lanes of a row; row h
+    // of the wave ends with the sums of row group member h
+    double v[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = halve32(acc[k], acc[k + 6]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double s = row16_sum(halve16(v[k], v[k + 3]));
+        if ((lane & 15) == 0) sm.part[w][(lane >> 4) * 3 + k] = s;
+    }
+    __syncthreads();
+    // marked pairs: wave w takes row w, a lane the words l, l + 64
+    {
+        const int q = w, i = r0 + w < n ? r0 + w : n - 1;
+        double sx = 0.0, sy = 0.0, sz = 0.0;
+        int cnt = 0;
+        bool seen = false;
+        for (int k = lane; k < nw; k += 64) {
+            uint64_t b = sm.bits[q][k];
+            if (!b) continue;
+            seen = true;
+            const int first = i + 1 - k * 64;   // bit of column i + 1
+            const uint64_t after = first <= 0 ? b : (first > 63 ? 0 : b & (~0ull << first));
+            sm.bits[q][k] = after;
+            cnt += __popcll(after);
+            const double ri = c.rc[i], Xi = c.x[i], Yi = c.y[i], Zi = c.z[i];
+            while (b) {
+                const int j = k * 64 + __ffsll((unsigned long long)b) - 1;
+                b &= b - 1;
+                const double dx = c.x[j] - Xi, dy = c.y[j] - Yi, dz = c.z[j] - Zi;
+                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                const double yc = rsq_full(r2);
+                const double irho = rsq_full(rho2_of(ri, c.rc[j]));
+                const double K =
+                    changeover_of_y(__builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0));
+                const double wk = (c.m[j] * K) * (yc * yc * yc);
+                sx = __builtin_fma(dx, wk, sx);
+                sy = __builtin_fma(dy, wk, sy);
+                sz = __builtin_fma(dz, wk, sz);
+            }
+        }
+        if (__any(seen)) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                sx += __shfl_xor(sx, off);
+                sy += __shfl_xor(sy, off);
+                sz += __shfl_xor(sz, off);
+                cnt += __shfl_xor(cnt, off);
+            }
+        }
+        if (lane == 0) {
+            sm.slow[q][0] = sx;
+            sm.slow[q][1] = sy;
+            sm.slow[q][2] = sz;
+            sm.cnt[q] = cnt;
+        }
+    }
+    __syncthreads();
+    if (tid < ROWS_G) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double t = ((sm.part[0][3 * tid + k] + sm.part[1][3 * tid + k]) +
+                              sm.part[2][3 * tid + k]) + sm.part[3][3 * tid + k];
+            a3[k] = t + sm.slow[tid][k];
+        }
+    }
+}
+
+}  // namespace genga
