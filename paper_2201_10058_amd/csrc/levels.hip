@@ -613,7 +613,7 @@ __global__ __launch_bounds__(LT) void k_group_rank(const int32_t *lab, const int
 // Direct solver: one thread per member; groups of up to 8 bodies take 8 lanes
 // of a wave each, larger ones a workgroup of 512 threads (Table 1 splits them
 // into more classes up to 512 bodies; here they are rare, and 512 threads
-// hold the extrapolation tableau in registers at 2 waves per SIMD with 68 KB
+// hold the extrapolation tableau in registers at 2 waves per SIMD with 125 KB
 // of LDS).  The
 // group's flow (Kepler force of the star plus the remainder R of the mutual
 // forces) is integrated over H by Bulirsch-Stoer steps: the modified
@@ -704,6 +704,40 @@ __device__ __forceinline__ double wave_max_all(double v)
     return v;
 }
 
+// Smallest and largest of a coordinate over the lanes that take part, as
+// bounds in binary32 (rounded outwards) by DPP moves within the wave: a
+// butterfly of binary64 shuffles costs ten times as much, and a box that is
+// 2^-23 too large only keeps a tile whose terms are zeros.  NaN is ignored (a
+// member at NaN fails the step by its own error).
+__device__ __forceinline__ float wave_min_dpp(float v)
+{
+#define BS_DPP_MIN(ctrl, rows)                                                                     \
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(                                       \
+                     __float_as_int(v), __float_as_int(v), ctrl, rows, 0xf, false)))
+    BS_DPP_MIN(0x111, 0xf);   // row_shr:1, 2, 4, 8
+    BS_DPP_MIN(0x112, 0xf);
+    BS_DPP_MIN(0x114, 0xf);
+    BS_DPP_MIN(0x118, 0xf);
+    BS_DPP_MIN(0x142, 0xa);   // row_bcast:15, 31
+    BS_DPP_MIN(0x143, 0xc);
+#undef BS_DPP_MIN
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+__device__ __forceinline__ void wave_bounds(double x, bool in, double &lo, double &hi)
+{
+    const float f = (float)x, e = fabsf(f) * 0x1p-23f + 1e-37f;
+    lo = (double)wave_min_dpp(in ? f - e : INFINITY);
+    hi = -(double)wave_min_dpp(in ? -f - e : INFINITY);
+}
+
+__device__ __forceinline__ void wave_sync_lds()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Squared gap between the box (lo, hi) and the box B = (lo, hi) of another
 // tile: a lower bound of the squared distance of any two of their members.
 __device__ __forceinline__ double box_gap2(const double lo[3], const double hi[3], const double *B)
@@ -718,11 +752,16 @@ __device__ __forceinline__ double box_gap2(const double lo[3], const double hi[3
     return d2;
 }
 
+// Pairs in reach that a wave keeps before it evaluates them.
+constexpr int BS_ENT = 256;
+
 template <int BT>
 struct BsSmem {
     double px[BT], py[BT], pz[BT], m[BT];
     double pv[3][BT], R[BT];
-    double rcd[BT];                     // deepest-level rc
+    alignas(16) int32_t cell[BT];       // bs_cell of the positions
+    uint32_t ent[BT / 64][BS_ENT];      // each wave's pairs in reach: member lane, partner
+    double fo[BT / 64][3][BS_ENT];      // and their terms
     double box[BT / 64][8];             // each wave's box of its members' positions
     double trho[BT / 64];               // each wave's largest deepest-level rc
     int32_t idx[BT];
@@ -731,40 +770,146 @@ struct BsSmem {
     long long ired[BT / 64];
 };
 
-// Partner sum of member t at its position (o) from the positions in LDS,
-// over share `sub` of S: the partners q = sub, sub + S, ... of every partner
-// wave that is not skipped.  The partners come by waves of 64: a wave whose
-// box stays beyond the larger deepest-level critical radius of the two waves
-// from the own wave's box holds no partner with R > 0 and is skipped (its
-// terms are exact zeros), as is each single partner beyond that radius.
-template <int BT>
-__device__ __forceinline__ void bs_accel(const BsDev &a, const BsSmem<BT> &sm, int t, int g,
-                                         int S, int sub, const double o[3], double acc[3])
+// The partners in reach of 64 members are found first and evaluated after.
+// Evaluated where they are found, a partner that any lane needs costs the
+// whole wave a remainder (a chain of several hundred cycles): 15 us for an
+// evaluation of 230 members with about 4 partners each.  Found as the bits of
+// each lane and written down as (member, partner) entries, they are shared
+// out over the lanes, one remainder per lane and pass, and each member then
+// adds its terms in ascending order.
+//
+// The workgroup's search uses the group's x-y plane as a grid of 16,000 cells
+// along its longer side, a pair of 16-bit coordinates per member: one
+// difference, one 16-bit dot product and one compare per partner, four
+// partners to an LDS read.  Rounding moves a coordinate by at most half a
+// cell, and clamping to the frame only brings members closer, so a pair
+// inside the larger deepest-level radius is within that radius plus 2 cells;
+// beyond the radius R = 0 exactly, so the pairs found in vain add exact zeros.
+typedef short bs_s16x2 __attribute__((ext_vector_type(2)));
+
+struct BsFrame {
+    double x0, y0, scale;
+};
+
+__device__ __forceinline__ int32_t bs_cell(const BsFrame &f, double x, double y)
 {
-    const double *BI = sm.box[t >> 6];
+    const double cx = __builtin_fmin(__builtin_fmax((x - f.x0) * f.scale, 0.0), 16000.0);
+    const double cy = __builtin_fmin(__builtin_fmax((y - f.y0) * f.scale, 0.0), 16000.0);
+    return (int)(cx + 0.5) | ((int)(cy + 0.5) << 16);
+}
+
+__device__ __forceinline__ bool bs_cell_near(int32_t a, int32_t b, int reach2)
+{
+    const bs_s16x2 d = __builtin_bit_cast(bs_s16x2, a) - __builtin_bit_cast(bs_s16x2, b);
+    return __builtin_amdgcn_sdot2(d, d, 0, false) <= reach2;
+}
+
+// Exclusive sum over the lanes of a wave and the total (small counts).
+__device__ __forceinline__ int wave_excl_sum(int v, int &total)
+{
+    int s = v;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xf, 0xf, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xf, 0xf, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xf, 0xf, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
+    s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xc, 0xf, false);
+    total = __builtin_amdgcn_readlane(s, 63);
+    return s - v;
+}
+
+// A wave's entries.  Each round a lane adds up to 4; where they went is kept
+// in `where` (base and count, 16 bits a round, up to 4 rounds).
+struct BsEntries {
+    int total = 0, rounds = 0;
+    uint64_t where = 0;
+};
+
+// Partner sum of the wave's members (lane's member t, at position o) from the
+// positions in LDS, over share `sub` of S: every partner wave's S-th part that
+// `sub` names.  A partner wave whose box stays beyond the larger deepest-level
+// critical radius of the two waves from the own wave's box holds no partner
+// with R > 0 and is skipped.  All lanes of the wave pass here.
+template <int BT>
+__device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const BsFrame &fr, int t,
+                                         int g, int S, int sub, double rcd, double acc[3])
+{
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int t0 = t - lane;
+    const double *BI = sm.box[t0 >> 6];
     const double lo[3] = {BI[0], BI[1], BI[2]}, hi[3] = {BI[3], BI[4], BI[5]};
     const int nw = (g + 63) >> 6;
-    const double rhoI = sm.trho[t >> 6];
+    const double rhoI = sm.trho[t0 >> 6];
+    const int32_t me = sm.cell[t < g ? t : 0];
+    uint32_t *ent = sm.ent[w];
+    double(*fo)[BS_ENT] = sm.fo[w];
+    BsEntries E;
+    auto flush = [&]() {
+        wave_sync_lds();
+        for (int p = lane; p < E.total; p += 64) {
+            const uint32_t e = ent[p];
+            const int i = t0 + (int)(e >> 16), q = (int)(e & 0xffffu);
+            const double dx = sm.px[q] - sm.px[i], dy = sm.py[q] - sm.py[i],
+                         dz = sm.pz[q] - sm.pz[i];
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            const double ir = rsq2(r2);
+            const double R = bs_remainder(r2 * ir, &sm.irc[0][i], BT, &sm.irc[0][q], BT, a.nlev);
+            const double s = a.G * sm.m[q] * R * (ir * ir * ir);
+            fo[0][p] = s * dx;
+            fo[1][p] = s * dy;
+            fo[2][p] = s * dz;
+        }
+        wave_sync_lds();
+        for (int r = 0; r < E.rounds; ++r) {
+            const int at = (int)(E.where >> (16 * r)) & 0xffff;
+            const int p0 = at >> 3, c = at & 7;
+            for (int k = 0; k < c; ++k) {
+                acc[0] += fo[0][p0 + k];
+                acc[1] += fo[1][p0 + k];
+                acc[2] += fo[2][p0 + k];
+            }
+        }
+        wave_sync_lds();
+        E = BsEntries();
+    };
+    const int per = 64 / S, u0 = sub * per;
     for (int J = 0; J < nw; ++J) {
         const double rr = rhoI > sm.trho[J] ? rhoI : sm.trho[J];
         if (box_gap2(lo, hi, sm.box[J]) > rr * rr * (1.0 + 0x1p-18)) continue;
-        const int q1 = g < J * 64 + 64 ? g : J * 64 + 64;
-        for (int q = J * 64 + sub; q < q1; q += S) {
-            if (q == t) continue;
-            const double dx = sm.px[q] - o[0], dy = sm.py[q] - o[1], dz = sm.pz[q] - o[2];
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            // beyond the larger deepest-level radius R = 0 exactly: the term
-            // is an exact zero and skipping it leaves the sum unchanged
-            const double rq = sm.rcd[t] > sm.rcd[q] ? sm.rcd[t] : sm.rcd[q];
-            if (r2 > rq * rq * (1.0 + 0x1p-18)) continue;
-            const double ir = rsq2(r2);
-            const double R = bs_remainder(r2 * ir, &sm.irc[0][t], BT, &sm.irc[0][q], BT, a.nlev);
-            const double s = a.G * sm.m[q] * R * (ir * ir * ir);
-            acc[0] += s * dx;
-            acc[1] += s * dy;
-            acc[2] += s * dz;
+        const double re = (rcd > sm.trho[J] ? rcd : sm.trho[J]) * fr.scale + 2.0;
+        const int reach2 = (int)__builtin_fmin(re * re + 1.0, 1e9);
+        const int4 *cells = (const int4 *)&sm.cell[J * 64 + u0];
+        uint64_t mask = 0;
+        for (int u = 0; u < per; u += 4) {
+            const int4 c = cells[u >> 2];
+            const uint32_t b = (bs_cell_near(me, c.x, reach2) ? 1u : 0u) |
+                               (bs_cell_near(me, c.y, reach2) ? 2u : 0u) |
+                               (bs_cell_near(me, c.z, reach2) ? 4u : 0u) |
+                               (bs_cell_near(me, c.w, reach2) ? 8u : 0u);
+            mask |= (uint64_t)b << (u0 + u);
+        }
+        if (g - J * 64 < 64) mask &= (1ull << (g - J * 64)) - 1;
+        if (J * 64 == t0) mask &= ~(1ull << lane);
+        if (t >= g) mask = 0;
+        while (__any(mask != 0)) {
+            const int pc = __popcll(mask), c = pc < 4 ? pc : 4;
+            int sum;
+            const int off = wave_excl_sum(c, sum);
+            if (E.rounds == 4 || E.total + sum > BS_ENT) flush();
+            const int base = E.total + off;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (k < c) {
+                    ent[base + k] = (uint32_t)(lane << 16) | (uint32_t)(J * 64 + __builtin_ctzll(mask));
+                    mask &= mask - 1;
+                }
+            }
+            E.where |= (uint64_t)(base << 3 | c) << (16 * E.rounds);
+            E.total += sum;
+            ++E.rounds;
         }
     }
+    if (E.total) flush();
 }
 
 // Publish positions (and each wave's box), then every member's derivative
@@ -772,8 +917,9 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, const BsSmem<BT> &sm, i
 // order (the waves of a share hold copies of the same members; only share 0
 // writes).  The shares' sums pass through pv, which no evaluation uses.
 template <int BT>
-__device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, int t, int g, int S,
-                                         int sub, const double z[6], double f[6])
+__device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, const BsFrame &fr, int t,
+                                         int g, int S, int sub, double rcd, const double z[6],
+                                         double f[6])
 {
     __syncthreads();   // the previous evaluation has finished reading
     const bool mem = t < g, own = mem && sub == 0;
@@ -781,11 +927,12 @@ __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, int t, 
         sm.px[t] = z[0];
         sm.py[t] = z[1];
         sm.pz[t] = z[2];
+        sm.cell[t] = bs_cell(fr, z[0], z[1]);
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const double lo = wave_min_all(mem ? z[c] : INFINITY);
-        const double hi = wave_max_all(mem ? z[c] : -INFINITY);
+        double lo, hi;
+        wave_bounds(z[c], mem, lo, hi);
         if ((threadIdx.x & 63) == 0 && own) {
             sm.box[t >> 6][c] = lo;
             sm.box[t >> 6][3 + c] = hi;
@@ -796,7 +943,7 @@ __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, int t, 
     f[1] = z[4];
     f[2] = z[5];
     double p[3] = {0.0, 0.0, 0.0};
-    if (mem) bs_accel<BT>(a, sm, t, g, S, sub, z, p);
+    if (t - (int)(threadIdx.x & 63) < g) bs_accel<BT>(a, sm, fr, t, g, S, sub, rcd, p);
     double k[3] = {0.0, 0.0, 0.0};
     if (mem) {
         const double r2s = z[0] * z[0] + z[1] * z[1] + z[2] * z[2];
@@ -851,9 +998,11 @@ struct BlockPol {
     BsSmem<BT> &sm;
     int t, g;
     int S, sub;   // waves per member (the group's shares), this wave's share
+    double rcd;   // own deepest-level rc
+    BsFrame fr;   // the group's plane (bs_cell)
     __device__ void deriv(const BsDev &a, const double z[6], double f[6])
     {
-        bs_deriv<BT>(a, sm, t, g, S, sub, z, f);
+        bs_deriv<BT>(a, sm, fr, t, g, S, sub, rcd, z, f);
     }
     __device__ double gmax(double v) { return bs_block_max<BT>(sm, v); }
     __device__ bool member() const { return t < g; }
@@ -1099,10 +1248,24 @@ __device__ long long bs_overlap(const BsDev &a, Pol &P, const double z[6])
     return P.gmin(key);
 }
 
+// (positions and radii only, the share's own partners)
 template <int BT>
 __device__ long long BlockPol<BT>::overlap(const BsDev &a, const double z[6])
 {
-    return bs_overlap(a, *this, z);
+    publish(z);
+    long long key = NO_PAIR;
+    if (t < g) {
+        const double ru = sm.R[t];
+        for (int q = t + 1 + sub; q < g; q += S) {
+            const double rs = ru + sm.R[q];
+            const double dx = sm.px[q] - z[0], dy = sm.py[q] - z[1], dz = sm.pz[q] - z[2];
+            if (rs > 0.0 && dx * dx + dy * dy + dz * dz < rs * rs) {
+                key = (long long)t * KEY_BASE + q;
+                break;
+            }
+        }
+    }
+    return gmin(key);
 }
 
 template <int GS>
@@ -1303,7 +1466,7 @@ __global__ __launch_bounds__(BT) void k_bs(BsDev a, int lo)
         int S = 1;
         while (nw * S * 2 <= BT / 64) S *= 2;
         const int t = (w / S) * 64 + lane, sub = w % S;
-        BlockPol<BT> P{sm, t, g, S, sub};
+        BlockPol<BT> P{sm, t, g, S, sub, 0.0, {}};
         const int32_t b = t < g ? a.gmem[a.gstart[root] + t] : 0;
         double y[6] = {0, 0, 0, 0, 0, 0};
         double rcd = 0.0;
@@ -1312,17 +1475,31 @@ __global__ __launch_bounds__(BT) void k_bs(BsDev a, int lo)
             for (int c = 0; c < 6; ++c) y[c] = a.shadow[(size_t)c * a.n + b];
             rcd = a.rc[a.nlev - 1][b];
         }
+        P.rcd = rcd;
         if (P.owner()) {
             sm.m[t] = a.m[b];
             sm.R[t] = a.radius ? a.radius[b] : 0.0;
             sm.idx[t] = b;
             for (int l = 0; l < a.nlev; ++l)
                 sm.irc[l][t] = rcp2(a.rc[l][b]);
-            sm.rcd[t] = rcd;
         }
         {
             const double tr = wave_max_all(rcd);
             if (lane == 0 && P.owner()) sm.trho[t >> 6] = tr;
+        }
+        {
+            // the group's frame: its x-y extent and what its members travel
+            const bool in = t < g;
+            const double far = bs_block_max(sm, in ? __builtin_fmax(fabs(y[3]), fabs(y[4])) : 0.0) *
+                               fabs(a.H);
+            const double x0 = -bs_block_max(sm, in ? -y[0] : -INFINITY) - far;
+            const double x1 = bs_block_max(sm, in ? y[0] : -INFINITY) + far;
+            const double y0 = -bs_block_max(sm, in ? -y[1] : -INFINITY) - far;
+            const double y1 = bs_block_max(sm, in ? y[1] : -INFINITY) + far;
+            const double side = x1 - x0 > y1 - y0 ? x1 - x0 : y1 - y0;
+            P.fr.x0 = x0;
+            P.fr.y0 = y0;
+            P.fr.scale = side > 0.0 && side < 1e300 ? 16000.0 / side : 0.0;
         }
         bool failed;
         [[clang::always_inline]] failed = bs_run(a, P, y);
@@ -1357,6 +1534,25 @@ __global__ __launch_bounds__(BT) void k_bs(BsDev a, int lo)
 // ascending tile and slot order.
 // ---------------------------------------------------------------------------
 constexpr int GT = 256;             // threads per workgroup of the grid solver
+
+// The grid solver's search runs in binary32, one 16-byte LDS read per partner: a position
+// rounded to binary32 and the square of the radius widened by twice what two
+// such neighbours can be off (2^-24 of each coordinate, 2^-23 of their
+// difference), so that it misses no pair inside the radius.
+__device__ __forceinline__ float4 bs_near(double x, double y, double z, double rcd)
+{
+    const double e = rcd + 0x1p-20 * (fabs(x) + fabs(y) + fabs(z) + rcd);
+    return make_float4((float)x, (float)y, (float)z, (float)(e * e) * (1.0f + 0x1p-20f));
+}
+
+__device__ __forceinline__ bool bs_in_reach(const float4 &a, const float4 &b)
+{
+    const float dx = b.x - a.x, dy = b.y - a.y, dz = b.z - a.z;
+    const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+    return !(r2 > (a.w > b.w ? a.w : b.w));   // (a NaN is evaluated)
+}
+
+
 constexpr int GCELL = 64;           // ordering cells per axis
 // a barrier that has waited this long (wall clock, 100 MHz ticks: 2 s) gives up
 constexpr uint64_t GWAIT_TICKS = 200000000ull;
@@ -1379,7 +1575,8 @@ struct GridDev {
 };
 
 struct GridSmem {
-    double sx[4][64], sy[4][64], sz[4][64], sm[4][64], src[4][64];
+    double sx[4][64], sy[4][64], sz[4][64], sm[4][64];
+    float4 snear[4][64];                 // bs_near of the partners
     double sirc[4][GENGA_MAX_LEVELS][64];
     double oirc[GENGA_MAX_LEVELS][GT];   // own 1 / rc per level
     double part[4][3][64];               // partial sums of the split waves
@@ -1415,13 +1612,6 @@ __device__ __forceinline__ unsigned hilbert_cell(unsigned x, unsigned y)
         }
     }
     return d;
-}
-
-__device__ __forceinline__ void wave_sync_lds()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 struct GridPol {
@@ -1485,10 +1675,7 @@ struct GridPol {
     {
         const bool mem = member();
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            lo[c] = wave_min_all(mem ? z[c] : INFINITY);
-            hi[c] = wave_max_all(mem ? z[c] : -INFINITY);
-        }
+        for (int c = 0; c < 3; ++c) wave_bounds(z[c], mem, lo[c], hi[c]);
     }
 
     __device__ void publish_n(const double z[6], int nc, double lo[3], double hi[3])
@@ -1557,6 +1744,7 @@ struct GridPol {
         GridSmem &S = g_gsm;
         if (!dead && t0 < ng) {
             const double Gc = a.G, rcme = rcd;
+            const float4 nme = bs_near(x0, y0, z0, rcme);
             const size_t cap = (size_t)G.cap;
             const int nt = (ng + 63) >> 6;
             const double *trho = G.trho, *mm = G.mm, *mrc = G.mrc, *mirc = G.mirc;
@@ -1597,24 +1785,28 @@ struct GridPol {
                     if (seen++ % S_ != mine) continue;
                     const int jq = J * 64 + lane;
                     if (jq < ng) {
-                        S.sx[w][lane] = P[jq];
-                        S.sy[w][lane] = P[cap + jq];
-                        S.sz[w][lane] = P[2 * cap + jq];
+                        const double xq = P[jq], yq = P[cap + jq], zq = P[2 * cap + jq];
+                        S.sx[w][lane] = xq;
+                        S.sy[w][lane] = yq;
+                        S.sz[w][lane] = zq;
+                        S.snear[w][lane] = bs_near(xq, yq, zq, mrc[jq]);
                         S.sm[w][lane] = mm[jq];
-                        S.src[w][lane] = mrc[jq];
                         for (int l = 0; l < nl; ++l) S.sirc[w][l][lane] = mirc[(size_t)l * cap + jq];
                     }
                     wave_sync_lds();
                     const int qn = ng - J * 64 < 64 ? ng - J * 64 : 64;
-                    const int qself = me - J * 64;
-                    for (int q = 0; q < qn; ++q) {
-                        if (q == qself) continue;
+                    uint64_t reach = 0;
+#pragma unroll 4
+                    for (int q = 0; q < qn; ++q)
+                        if (bs_in_reach(nme, S.snear[w][q])) reach |= 1ull << q;
+                    if (J == me >> 6) reach &= ~(1ull << lane);
+                    if (!mem) reach = 0;
+                    while (reach) {
+                        const int q = __builtin_ctzll(reach);
+                        reach &= reach - 1;
                         const double dx = S.sx[w][q] - x0, dy = S.sy[w][q] - y0,
                                      dz = S.sz[w][q] - z0;
                         const double r2 = dx * dx + dy * dy + dz * dz;
-                        const double rq = rcme > S.src[w][q] ? rcme : S.src[w][q];
-                        // beyond the larger deepest-level radius R = 0 exactly
-                        if (r2 > rq * rq * (1.0 + 0x1p-18)) continue;
                         const double ir = rsq2(r2);
                         const double Rw = bs_remainder(r2 * ir, &S.oirc[0][threadIdx.x], GT,
                                                        &S.sirc[w][0][q], 64, nl);

@@ -297,3 +297,25 @@ def test_grid_solver_two_groups_in_one_launch(dev):
     ep, ev = _rel(out, ref, ("x", "y", "z")), _rel(out, ref, ("vx", "vy", "vz"))
     _say(f"two rings of 600: position {ep:.2e} velocity {ev:.2e}")
     assert ep < 1e-11 and ev < 1e-11
+
+
+@pytest.mark.parametrize("n, k", [(12, 5), (64, 31), (150, 74), (300, 60), (600, 40)])
+def test_direct_groups_of_many_partners(dev, n, k):
+    # rings whose bodies meet k neighbours on each side: a wave's pairs in
+    # reach fill its entry buffer (256) several times over, up to every member
+    # (12, 64 and 150 bodies) and over several partner waves; 600 bodies: the
+    # grid solver.  Tolerance as for the other rings.
+    ring = W.make_bs_ring(n, neighbours=k)
+    st = N.State.from_numpy(ring)
+    cfg = N.Config(G=ring["G"], m_star=1.0, dt=ring["dt"], n1=ring["n1"], n2=0.0, slevels=1,
+                   substeps=1, level_capacity=max(1 << 14, n * n), direct=1)
+    ws = N.Workspace(n, cfg)
+    ref = oracle.state_copy(ring)
+    for _ in range(2):
+        assert N.step(st, cfg, ws) == N.OK
+        r = oracle.step_direct(ref, ring["G"], 1.0, ring["dt"], ring["n1"], 0.0, 1, 1, rk_steps=200)
+        assert r[6] == 0 and N.group_stats(n, cfg, ws) == r[5] == (1, n)
+    out = st.numpy()
+    ep, ev = _rel(out, ref, ("x", "y", "z")), _rel(out, ref, ("vx", "vy", "vz"))
+    _say(f"ring {n}, {2 * k} partners: position {ep:.2e} velocity {ev:.2e}")
+    assert ep < 1e-11 and ev < 1e-11
