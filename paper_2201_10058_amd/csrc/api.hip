@@ -418,9 +418,11 @@ int genga_step(genga_bodies *b, const genga_params *p, genga_pairs *pairs, void 
     genga_pairs e0;
     if (levels) e0 = level0_pairs(V, (char *)ws);
     hipError_t e;
-    if (!levels && !gr && c.use_rows) {
+    if (!levels && !gr && (c.use_rows || c.use_tp)) {
         KickLaunch k = kick_launch(b, p, h, nullptr, nullptr, nullptr, pairs, true, 0);
-        if ((e = launch_step_rows(k, b, p, L, (char *)ws, s)) != hipSuccess) return hip_fail(e);
+        e = c.use_tp ? launch_step_tp(k, b, p, c, L, (char *)ws, s)
+                     : launch_step_rows(k, b, p, L, (char *)ws, s);
+        if (e != hipSuccess) return hip_fail(e);
         if (p->flags & GENGA_FLAG_NOSYNC) return GENGA_OK;
         return genga_read_status(ws, stream);
     }

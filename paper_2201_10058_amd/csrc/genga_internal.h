@@ -117,6 +117,10 @@ constexpr int64_t ROWS_MAX = 8192;
 // the kick and the base step of up to this many bodies run in one workgroup
 constexpr int ONE_MAX = 128;
 
+// Most massive bodies of the test-particle kick that evaluates a pair once
+// for both bodies (csrc/tp.hip: a lane per massive body, one word of a bitmap).
+constexpr int TP_MAX = 64;
+
 // Launch shape of the kick.
 struct KickCfg {
     int nt = KB;              // threads per block (64 or 256)
@@ -151,6 +155,8 @@ struct KickCfg {
     int symb_W = 0;           // columns per slice of every system (512, 256 or 128)
     // binary64 forces of one small all-massive system: the row-group kick
     bool use_rows = false;
+    // binary64 forces in a test-particle mode with 1 .. TP_MAX massive bodies
+    bool use_tp = false;
 };
 
 // Byte offsets of the workspace regions.
@@ -226,6 +232,13 @@ hipError_t launch_hc_rows(genga_bodies *b, double m_star, double h, const Layout
                           hipStream_t s);
 hipError_t launch_step_rows(KickLaunch &k, genga_bodies *b, const genga_params *p, const Layout &L,
                             char *ws, hipStream_t s);
+
+// Few massive bodies among test particles (KickCfg::use_tp): the kick, and the
+// base step with its critical radii (k as above).
+hipError_t launch_kick_tp(const KickLaunch &k, const KickCfg &c, const Layout &L, char *ws,
+                          hipStream_t s);
+hipError_t launch_step_tp(KickLaunch &k, genga_bodies *b, const genga_params *p, const KickCfg &c,
+                          const Layout &L, char *ws, hipStream_t s);
 
 hipError_t launch_rcrit(const genga_bodies *b, const genga_params *p, char *ws, hipStream_t s);
 // x_i += h P / m_star for every body, P summed over bodies [0, nsum).

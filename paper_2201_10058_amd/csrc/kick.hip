@@ -1349,6 +1349,10 @@ KickCfg choose_kick_cfg(int64_t n, const genga_params *p)
         c.mpad = ((nm + 63) / 64) * 64;
         c.slices = (int)(c.s_t + ((int64_t)c.s_m * c.mpad + npad - 1) / npad);
         if (c.slices < 1) c.slices = 1;
+        // few massive bodies: one evaluation of a pair for both of its bodies,
+        // unless the caller sets the tile shape
+        c.use_tp = nm >= 1 && nm <= TP_MAX && c.ipt == 1 && p->slices == 0 &&
+                   p->precision == GENGA_FP64;
         c.gx = (int)c.ntiles;    // one-dimensional launch over the tile numbers
         c.gy = 1;
     }
@@ -1503,6 +1507,7 @@ hipError_t launch_kick(const KickLaunch &k, const KickCfg &c, const Layout &L, c
                        hipStream_t s)
 {
     if (c.use_rows && k.forces && !k.tiles) return launch_kick_rows(k, L, ws, s);
+    if (c.use_tp && k.forces && !k.tiles) return launch_kick_tp(k, c, L, ws, s);
     KickDev d;
     d.x = k.x; d.y = k.y; d.z = k.z; d.m = k.m; d.rc = k.rc;
     d.n = k.n;

@@ -140,3 +140,68 @@ def test_tp_unsupported_combinations(dev):
     with pytest.raises(N.GengaError) as e:
         N.kick(st, cfg, ws, 0.0)
     assert e.value.code == N.E_INVAL
+
+
+# the kick that evaluates a pair once for both bodies (1 to 64 massive bodies)
+# and its neighbour above: sizes around its blocks (256), waves (64) and groups
+# of 4 massive bodies, sparse and with every pair inside its radius
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("n,nm", [(2, 1), (65, 64), (256, 4), (257, 5), (300, 63), (513, 64),
+                                  (600, 65), (4100, 17)])
+def test_tp_kick_edges(dev, mode, dense, n, nm):
+    d = _cloud(n, nm, seed=3 * n + nm)
+    _check(d, d["rc"] * (8.0 if dense else 0.2), nm, mode)
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("n,nm", [(2, 1), (257, 3), (700, 64), (700, 65)])
+def test_tp_step_matches_operators(dev, mode, n, nm):
+    # the fused step against its operators one by one: the same sums, except
+    # that its second kick sees the positions before their common shift
+    d = W.make_tp_disk(n, nm, seed=33)
+    cfg = N.Config(G=G, tp_mode=mode, n_massive=nm)
+    ws = N.Workspace(n, cfg)
+    st, op = N.State.from_numpy(d), N.State.from_numpy(d)
+    pl, pl_op = N.PairList(64 * n), N.PairList(64 * n)
+    ref = oracle.state_copy(d)
+    for _ in range(3):
+        assert N.step(st, cfg, ws, pl) == N.OK
+        oracle.step_tp(ref, G, 1.0, 6.0, 3.0, 0.4, nm, mode)
+        N.rcrit(op, cfg, ws)
+        N.kick(op, cfg, ws, 3.0, pairs=pl_op)
+        N.hc(op, cfg, ws, 3.0)
+        N.drift(op, cfg, ws, 6.0)
+        N.hc(op, cfg, ws, 3.0)
+        N.kick(op, cfg, ws, 3.0)
+        assert N.read_status(ws) == N.OK
+        a, b = pl.result(), pl_op.result()
+        assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    out = st.numpy()
+    for k in ("x", "y", "vx", "vy", "rc"):
+        assert (st.t[k] - op.t[k]).abs().max() <= 1e-14 * op.t[k].abs().max(), k
+    for k in ("x", "y", "z", "vx", "vy", "vz"):
+        assert np.max(np.abs(out[k] - ref[k])) <= 3e-12 * max(np.max(np.abs(ref[k])), 1e-3), k
+
+
+def test_tp_graph_replay(dev):
+    d = W.make_tp_disk(3000, 16, seed=34)
+    cfg = N.Config(G=G, tp_mode=2, n_massive=16, flags=N.FLAG_NOSYNC)
+    ws, ws_e = N.Workspace(3000, cfg), N.Workspace(3000, cfg)
+    st, st_e = N.State.from_numpy(d), N.State.from_numpy(d)
+    pl, pl_e = N.PairList(8192), N.PairList(8192)
+    N.step(st, cfg, ws, pl)
+    N.step(st_e, cfg, ws_e, pl_e)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        N.step(st, cfg, ws, pl)
+    for rep in range(4):
+        g.replay()
+        N.step(st_e, cfg, ws_e, pl_e)
+        torch.cuda.synchronize()
+        for k in N.State.KEYS:
+            assert torch.equal(st.t[k], st_e.t[k]), (rep, k)
+        a, b = pl.result(), pl_e.result()
+        assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    assert N.read_status(ws) == N.OK and N.read_status(ws_e) == N.OK
