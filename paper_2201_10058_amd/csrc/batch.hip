@@ -52,8 +52,8 @@ static double sym_tile_cost(const SymShape &h, int64_t g, int64_t s)
 {
     const int64_t row0 = g * SYM_RG;
     const int64_t rowend = std::min<int64_t>(row0 + SYM_RG, h.n);
-    const int64_t col0 = row0 + s * h.W;
-    const int64_t col1 = std::min<int64_t>(col0 + h.W, h.n);
+    int64_t col0, col1;
+    h.cols(g, s, col0, col1);
     const int64_t nch = (col1 - col0 + 63) / 64;
     double t = 0.5;
     for (int64_t kc = 0; kc < nch; ++kc) {

@@ -36,10 +36,13 @@ struct TileDesc {
 // Symmetric binary64 kick of one system (each unordered pair evaluated once,
 // its force applied to both bodies).  Rows are cut into groups of SYM_RG (one
 // block of SYM_NW waves, SYM_IPT rows per lane); group g works on the columns
-// [g SYM_RG, n) in slices of W columns (W divides SYM_RG, d = SYM_RG / W of
-// them cover the group's own rows).  A tile is (group g, slice s), stored as
-// sid = tb(g) + s; launched as the d..ns(g)-1 slices of every group first,
-// then the d diagonal slices of every group.
+// [g SYM_RG, n) in slices: first up to A narrow ones of W columns (W divides
+// SYM_RG, the first d = SYM_RG / W cover the group's own rows, A >= d is a
+// multiple of d), then wide ones of M W columns (M divides d).  A tile is
+// (group g, slice s), stored as sid = tb(g) + s; launched as every group's wide
+// slices first, then the narrow ones, those over the groups' own rows last.
+// Wide slices write fewer row sums, narrow ones at the end even out what the
+// compute units have to do (A = d, M = 1: slices of one width).
 constexpr int SYM_NW = 4;
 constexpr int SYM_IPT = 2;
 constexpr int SYM_NT = SYM_NW * 64;
@@ -48,23 +51,63 @@ constexpr int SYM_RG = SYM_NT * SYM_IPT;
 struct SymShape {
     int64_t n = 0;
     int64_t G = 0;       // row groups
-    int64_t S0 = 0;      // slices of group 0 (ceil(n / W))
-    int W = 0, d = 0;    // columns per slice, slices over a group's own rows
+    int64_t S0 = 0;      // narrow slices that group 0 would have (ceil(n / W))
+    int W = 0, d = 0;    // columns per narrow slice, slices over a group's own rows
+    int A = 0, M = 1;    // narrow slices of a group, width of the wide ones in W
+    int64_t gl = 0;      // groups with wide slices
+    int64_t nb0 = 0;     // wide slices of group 0 (group g < gl: nb0 - g d / M)
     int64_t T = 0;       // tiles
-    int64_t tfull = 0;   // tiles off the diagonal (launched first)
+    int64_t tfull = 0;   // wide tiles (launched first)
     // slices of group g, first storage tile of group g
-    __host__ __device__ int64_t ns(int64_t g) const { return S0 - g * d; }
-    __host__ __device__ int64_t tb(int64_t g) const { return g * S0 - d * ((g * (g - 1)) / 2); }
+    __host__ __device__ int64_t ns(int64_t g) const
+    {
+        return g < gl ? A + nb0 - g * (d / M) : S0 - g * d;
+    }
+    __host__ __device__ int64_t tb(int64_t g) const
+    {
+        const int64_t k = g < gl ? g : gl;
+        return k * (A + nb0) - (d / M) * ((k * (k - 1)) / 2) + (g - k) * S0 -
+               d * ((g * (g - 1)) / 2 - (k * (k - 1)) / 2);
+    }
+    // columns [c0, c1) of slice s of group g
+    __host__ __device__ void cols(int64_t g, int64_t s, int64_t &c0, int64_t &c1) const
+    {
+        const bool wide = g < gl && s >= A;
+        const int64_t u = wide ? A + (s - A) * M : s;
+        c0 = g * SYM_RG + u * W;
+        c1 = c0 + (wide ? M * W : W);
+        c1 = c1 < n ? c1 : n;
+    }
     // column sums of group g: 3 rows of collen(g) doubles from 3 coloff(g)
     __host__ __device__ int64_t collen(int64_t g) const { return n - g * SYM_RG; }
     __host__ __device__ int64_t coloff(int64_t g) const
     {
         return g * n - (int64_t)SYM_RG * ((g * (g - 1)) / 2);
     }
-    // tiles off the diagonal before group g
-    __host__ __device__ int64_t bf(int64_t g) const { return g * S0 - d * ((g * (g + 1)) / 2); }
+    // wide tiles before group g
+    __host__ __device__ int64_t bf(int64_t g) const { return g * nb0 - (d / M) * ((g * (g - 1)) / 2); }
+    // blocks of a launch (sym_tile): the wide tiles, then A slots per group
+    __host__ __device__ int64_t blocks() const { return tfull + G * A; }
 };
-SymShape sym_shape(int64_t n, int W);
+// A = 0: slices of W columns only.
+inline SymShape sym_shape(int64_t n, int W, int A = 0, int M = 1)
+{
+    SymShape h;
+    h.n = n;
+    h.W = W;
+    h.d = SYM_RG / W;
+    h.A = A > 0 ? A : h.d;
+    h.M = M;
+    h.G = (n + SYM_RG - 1) / SYM_RG;
+    h.S0 = (n + W - 1) / W;
+    if (h.S0 > h.A) {
+        h.gl = (h.S0 - h.A + h.d - 1) / h.d;
+        h.nb0 = (h.S0 - h.A + M - 1) / M;
+    }
+    h.T = h.tb(h.G);
+    h.tfull = h.bf(h.gl);
+    return h;
+}
 
 // Batch of systems in the symmetric kick: per system its shape (n = its
 // bodies), first body o, first storage tile tbase and the offset cbase of

@@ -795,10 +795,16 @@ __global__ __launch_bounds__(RB) void k_kick_reduce(ReduceDev r)
         double mag = 0.0;
         if (r.sym && r.fold) {
             // the SYM_FOLD part sums of k_sym_fold, in part order
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            double acc[4] = {0.0, 0.0, 0.0, 0.0}, v[SYM_FOLD][4];
+#pragma unroll
             for (int k = 0; k < SYM_FOLD; ++k)
-                for (int c = 0; c < r.pstride; ++c)
-                    acc[c] += r.fold[((size_t)k * r.pstride + c) * r.npad + i];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    v[k][c] = c < r.pstride ? r.fold[((size_t)k * r.pstride + c) * r.npad + i] : 0.0;
+#pragma unroll
+            for (int k = 0; k < SYM_FOLD; ++k)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[c] += v[k][c];
             a3[0] = acc[0];
             a3[1] = acc[1];
             a3[2] = acc[2];
@@ -851,21 +857,35 @@ __global__ __launch_bounds__(RB) void k_kick_reduce(ReduceDev r)
     if (r.emit) {
         int64_t c = 0;
         if (valid) {
+            // counts of the row's slices -> offsets within the row.  An offset
+            // is read back only where pairs were found, and few slices have
+            // any, so the others are not written; the loads of 32 slices are
+            // in flight together (a row has some hundred)
             int32_t *cp = r.cnt + cr.base + i;
             int s = 0;
-            for (; s + 8 <= nsl; s += 8) {
-                int32_t t[8];
+            for (; s + 32 <= nsl; s += 32) {
+                int32_t t[32];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) t[k] = cp[(size_t)(s + k) * cr.stride];
+                for (int k = 0; k < 32; ++k) t[k] = cp[(size_t)(s + k) * cr.stride];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    cp[(size_t)(s + k) * cr.stride] = (int32_t)c;
+                for (int k = 0; k < 32; ++k) {
+                    if (t[k]) cp[(size_t)(s + k) * cr.stride] = (int32_t)c;
+                    c += t[k];
+                }
+            }
+            for (; s + 4 <= nsl; s += 4) {
+                int32_t t[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t[k] = cp[(size_t)(s + k) * cr.stride];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (t[k]) cp[(size_t)(s + k) * cr.stride] = (int32_t)c;
                     c += t[k];
                 }
             }
             for (; s < nsl; ++s) {
                 const int32_t t = cp[(size_t)s * cr.stride];
-                cp[(size_t)s * cr.stride] = (int32_t)c;
+                if (t) cp[(size_t)s * cr.stride] = (int32_t)c;
                 c += t;
             }
         }
@@ -1280,16 +1300,30 @@ __global__ __launch_bounds__(64) void k_pairs_scatter(ScatterDev d)
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-// Symmetric kick: columns per slice, the widest (up to SYM_RG) that still
-// gives about 4096 tiles, so that row sums cost little HBM traffic while the
-// chip holds several rounds of tiles (65,536 bodies: 512 columns, 8,256
-// tiles; 128 and 256 columns measured within 0.3 % of its kick time, with
-// longer reductions).
-static int sym_width(int64_t n)
+// Symmetric kick: the slices of a row group.  Wide ones write few row sums
+// (at 20,011 bodies slices of 64 columns write and read back 80 MB a kick, of
+// 256 columns 25 MB), but too few tiles leave some compute units waiting for
+// others (820 tiles of 512 columns there, 3.2 to each); so most columns go into
+// wide slices, launched first, and the first 16 or 24 of a group into narrow
+// ones, which fill up what the wide ones leave.  Measured (step, us; slices of
+// one width, then narrow width, their number, wide ones' multiple):
+//   10,000: 175 -> 163 (64, 16, 2)    16,384: 326 -> 310 (64, 24, 4)
+//   20,011: 457 -> 428 (64, 24, 4)    32,768: 994 -> 974 (64, 24, 4)
+//   45,000: 1802 -> 1734 (128, 16, 4) 65,536: 3614 -> 3535 (128, 16, 4)
+// at 20,011 with 2, 4 and 8 as multiple: 432, 428, 456.  From 131,072 bodies on
+// 512 columns alone are some hundred tiles to a compute unit.
+static SymShape sym_default_shape(int64_t n)
 {
-    int W = SYM_RG;
-    while (W > 64 && sym_shape(n, W).T < 4096) W /= 2;
-    return W;
+    if (n < SYM_MIN_N) {
+        // (by flag only) the widest with 4,096 tiles, or 64
+        int W = SYM_RG;
+        while (W > 64 && sym_shape(n, W).T < 4096) W /= 2;
+        return sym_shape(n, W);
+    }
+    if (n < 13000) return sym_shape(n, 64, 16, 2);
+    if (n < 40000) return sym_shape(n, 64, 24, 4);
+    if (n < 131072) return sym_shape(n, 128, 16, 4);
+    return sym_shape(n, SYM_RG);
 }
 
 KickCfg choose_kick_cfg(int64_t n, const genga_params *p)
@@ -1363,14 +1397,13 @@ KickCfg choose_kick_cfg(int64_t n, const genga_params *p)
     const bool plain = !p || p->tp_mode == 0 || p->n_massive >= n;
     if (plain && !(flags & GENGA_FLAG_DIRECTED) &&
         (n >= SYM_MIN_N || (flags & GENGA_FLAG_SYMMETRIC))) {
-        int W = sym_width(n);
+        SymShape h = sym_default_shape(n);
         if (p && p->slices > 0) {
             // slices over a row group's own rows: 1, 2, 4, 8 or 16
             int dd = 1;
             while (dd * 2 <= p->slices && dd < SYM_RG / 64) dd *= 2;
-            W = SYM_RG / dd;
+            h = sym_shape(n, SYM_RG / dd);
         }
-        const SymShape h = sym_shape(n, W);
         // its row and column sums (up to 5 per row and tile or group: the
         // adjoint's) grow as n^2 / SYM_RG: by default the symmetric form stays
         // within SYM_WS_MAX bytes of them

@@ -46,19 +46,6 @@
 
 namespace genga {
 
-SymShape sym_shape(int64_t n, int W)
-{
-    SymShape h;
-    h.n = n;
-    h.W = W;
-    h.d = SYM_RG / W;
-    h.G = (n + SYM_RG - 1) / SYM_RG;
-    h.S0 = (n + W - 1) / W;
-    h.T = h.tb(h.G);
-    h.tfull = h.bf(h.G - 1);
-    return h;
-}
-
 struct SymDev {
     const double *x, *y, *z, *m, *rc;
     SymShape sh;
@@ -398,8 +385,8 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
     const int64_t n = h.n;
     const int64_t row0 = g * SYM_RG;
     const int64_t rowend = row0 + SYM_RG < n ? row0 + SYM_RG : n;
-    const int64_t col0 = row0 + s * h.W;
-    const int64_t col1 = col0 + h.W < n ? col0 + h.W : n;
+    int64_t col0, col1;
+    h.cols(g, s, col0, col1);
     const int nch = (int)((col1 - col0 + 63) / 64);
     const int64_t wave_g = sid * SYM_NW + w;
     const bool diag = s < h.d;
@@ -603,8 +590,8 @@ __global__ __launch_bounds__(SYM_NT) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     sym_tile_run<false>(a, t.g, t.s, sid, sm);
 }
 
-// Place the staged pairs of the symmetric kick (one wave of 64 threads per
-// kick wave).  Rank of a pair inside its (row, tile): the number of pairs of
+// Place the staged pairs of the symmetric kick (a block per tile, one wave of
+// 64 threads per kick wave).  Rank of a pair inside its (row, tile): the number of pairs of
 // the same row with a smaller j in the wave's segment.  A wave whose segment
 // overflowed is recomputed over its rows and the tile's columns, j ascending.
 struct SymScatterDev {
@@ -618,13 +605,16 @@ struct SymScatterDev {
     int64_t capacity;
 };
 
-__global__ __launch_bounds__(64) void k_pairs_scatter_sym(SymScatterDev d)
+__global__ __launch_bounds__(SYM_NT) void k_pairs_scatter_sym(SymScatterDev d)
 {
-    __shared__ int32_t si_[WSEG], sj_[WSEG];
-    const int lane = threadIdx.x;
-    const int64_t wave_g = blockIdx.x;
-    const int64_t sid = wave_g / SYM_NW;
-    const int w = (int)(wave_g % SYM_NW);
+    __shared__ int32_t si_all[SYM_NW][WSEG], sj_all[SYM_NW][WSEG];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int32_t *si_ = si_all[w], *sj_ = sj_all[w];
+    const int64_t sid = blockIdx.x;
+    const int64_t wave_g = sid * SYM_NW + w;
+    const int nst = d.wcount[wave_g];
+    if (nst == 0) return;   // (most waves; no block barrier below)
     SymShape h;
     int64_t g, s, o = 0;
     if (d.b.tiles) {
@@ -640,14 +630,15 @@ __global__ __launch_bounds__(64) void k_pairs_scatter_sym(SymScatterDev d)
         s = sid - h.tb(g);
     }
     const int64_t row0 = g * SYM_RG;   // (local to the system)
-    const int nst = d.wcount[wave_g];
     if (nst <= WSEG) {
         for (int e = lane; e < nst; e += 64) {
             const int32_t *e3 = d.stage + ((size_t)wave_g * WSEG + e) * 3;
             si_[e] = e3[0];
             sj_[e] = e3[1];
         }
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         for (int e = lane; e < nst; e += 64) {
             const int32_t i = si_[e], j = sj_[e];
             int rank = 0;
@@ -663,8 +654,8 @@ __global__ __launch_bounds__(64) void k_pairs_scatter_sym(SymScatterDev d)
     }
     const int64_t n = h.n;
     const int64_t rowend = row0 + SYM_RG < n ? row0 + SYM_RG : n;
-    const int64_t col0 = row0 + s * h.W;
-    const int64_t col1 = col0 + h.W < n ? col0 + h.W : n;
+    int64_t col0, col1;
+    h.cols(g, s, col0, col1);
     for (int q = 0; q < SYM_IPT; ++q) {
         const int64_t li = row0 + (int64_t)(q * SYM_NW + w) * 64 + lane;
         if (li >= rowend) continue;
@@ -726,7 +717,7 @@ hipError_t launch_kick_sym(const SymShape &h, bool mixed, double widen, const do
 {
     const SymDev a = sym_dev(h, mixed, widen, x, y, z, m, rc, rowpart, colpart, cnt, stage,
                              wcount, status, refine_cnt, emit);
-    const int64_t blocks = h.tfull + h.G * h.d;
+    const int64_t blocks = h.blocks();
     if (mixed)
         hipLaunchKernelGGL(k_kick_sym<true>, dim3((unsigned)blocks), dim3(SYM_NT), 0, s, a);
     else
@@ -766,7 +757,7 @@ hipError_t launch_scatter_sym(const SymShape &h, const SymBatch *b, const double
     d.capacity = pairs->capacity;
     const int64_t T = b ? b->T : h.T;
     if (T == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pairs_scatter_sym, dim3((unsigned)(T * SYM_NW)), dim3(64), 0, s, d);
+    hipLaunchKernelGGL(k_pairs_scatter_sym, dim3((unsigned)T), dim3(SYM_NT), 0, s, d);
     return hipGetLastError();
 }
 

@@ -19,36 +19,41 @@ __device__ __forceinline__ float rotate_down(float v)
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xF, 0xF, false));
 }
 
-// Tile of launch index t: group g and slice s (s = -1: an empty diagonal slot
-// of the last group).
-__device__ __forceinline__ void sym_tile(const SymShape &h, int64_t t, int64_t &g, int64_t &s)
+// Tile of launch index t: group g and slice s (s = -1: an empty narrow slot of
+// one of the last groups).
+__host__ __device__ __forceinline__ void sym_tile(const SymShape &h, int64_t t, int64_t &g, int64_t &s)
 {
     if (t < h.tfull) {
-        // largest g with bf(g) <= t: root of d/2 g^2 - (S0 - d/2) g + t = 0
-        const double b = (double)h.S0 - 0.5 * h.d;
-        double r = b * b - 2.0 * h.d * (double)t;
+        // largest g with bf(g) <= t: root of e/2 g^2 - (nb0 + e/2) g + t = 0
+        const double e = (double)(h.d / h.M), b = (double)h.nb0 + 0.5 * e;
+        double r = b * b - 2.0 * e * (double)t;
         r = r > 0.0 ? r : 0.0;
-        int64_t gg = (int64_t)((b - __builtin_sqrt(r)) / h.d);
-        gg = gg < 0 ? 0 : (gg > h.G - 2 ? h.G - 2 : gg);
+        int64_t gg = (int64_t)((b - __builtin_sqrt(r)) / e);
+        gg = gg < 0 ? 0 : (gg > h.gl - 1 ? h.gl - 1 : gg);
         while (gg > 0 && h.bf(gg) > t) --gg;
-        while (gg < h.G - 2 && h.bf(gg + 1) <= t) ++gg;
+        while (gg < h.gl - 1 && h.bf(gg + 1) <= t) ++gg;
         g = gg;
-        s = h.d + (t - h.bf(gg));
+        s = h.A + (t - h.bf(gg));
         return;
     }
     const int64_t u = t - h.tfull;
-    g = u / h.d;
-    s = u % h.d;
+    g = u % h.G;
+    s = h.A - 1 - u / h.G;
     if (s >= h.ns(g)) s = -1;
 }
 
 // Group of storage tile sid: largest g with tb(g) <= sid.
-__device__ __forceinline__ int64_t sym_group_of(const SymShape &h, int64_t sid)
+__host__ __device__ __forceinline__ int64_t sym_group_of(const SymShape &h, int64_t sid)
 {
-    const double b = (double)h.S0 + 0.5 * h.d;
-    double r = b * b - 2.0 * h.d * (double)sid;
-    r = r > 0.0 ? r : 0.0;
-    int64_t g = (int64_t)((b - __builtin_sqrt(r)) / h.d);
+    int64_t g;
+    if (sid < h.tb(h.gl)) {
+        const double e = (double)(h.d / h.M), b = (double)(h.A + h.nb0) + 0.5 * e;
+        double r = b * b - 2.0 * e * (double)sid;
+        r = r > 0.0 ? r : 0.0;
+        g = (int64_t)((b - __builtin_sqrt(r)) / e);
+    } else {
+        g = h.gl;   // (at most A / d more groups)
+    }
     g = g < 0 ? 0 : (g > h.G - 1 ? h.G - 1 : g);
     while (g > 0 && h.tb(g) > sid) --g;
     while (g < h.G - 1 && h.tb(g + 1) <= sid) ++g;

@@ -221,8 +221,8 @@ __global__ __launch_bounds__(SYM_NT) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const int64_t n = h.n;
     const int64_t row0 = g * SYM_RG;
     const int64_t rowend = row0 + SYM_RG < n ? row0 + SYM_RG : n;
-    const int64_t col0 = row0 + s * h.W;
-    const int64_t col1 = col0 + h.W < n ? col0 + h.W : n;
+    int64_t col0, col1;
+    h.cols(g, s, col0, col1);
     const int nch = (int)((col1 - col0 + 63) / 64);
     const bool diag = s < h.d;
     const int vzero = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
@@ -429,7 +429,7 @@ hipError_t launch_kick_vjp_sym(const SymShape &h, const genga_bodies *b, double 
     a.far_row = 1e18;
     a.far_col = -1e18;
     a.c53 = 5.0 / 3.0;
-    const int64_t blocks = h.tfull + h.G * h.d;
+    const int64_t blocks = h.blocks();
     hipLaunchKernelGGL(k_kick_vjp_sym, dim3((unsigned)blocks), dim3(SYM_NT), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
