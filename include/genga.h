@@ -269,7 +269,9 @@ int genga_drift(genga_bodies *b, const genga_params *p, double dt, void *ws, voi
  *   rc <- Rcrit(x, v); Kick(dt/2) [+ pairs]; HC(dt/2); FG(dt); HC(dt/2);
  *   Kick(dt/2) with the same rc.
  * pairs (nullable) receives the list of the first half kick.  Unless
- * GENGA_FLAG_NOSYNC, synchronises the stream and returns the status.
+ * GENGA_FLAG_NOSYNC, synchronises the stream and returns the status.  With
+ * GENGA_MIXED, systems below 8,192 bodies take the binary64 kick, which is
+ * faster there, unless p->ipt, p->slices or a form flag is set.
  *
  * Symplectic levels (p->slevels = L > 1; Sect. 6.2 and Appendix A): the
  * bodies of the level-0 list E_0 are not drifted for dt; from their state

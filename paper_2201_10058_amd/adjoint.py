@@ -36,7 +36,13 @@ class _Runner:
             # the adjoint covers the base step's operators only
             raise N.GengaError(N.E_UNSUPPORTED, "adjoint of a step with GR, levels, the direct "
                                "solver or test particles")
-        self.cfg = N.Config(**{**cfg.__dict__, "flags": N.FLAG_NOSYNC, "events": (None,) * 4})
+        flags = N.FLAG_NOSYNC
+        if cfg.precision == N.MIXED and n < 8192:
+            # genga_step would take the binary64 kick here: name the default
+            # form, so that the forward pass runs the kicks that the backward
+            # pass recomputes
+            flags |= N.FLAG_DIRECTED
+        self.cfg = N.Config(**{**cfg.__dict__, "flags": flags, "events": (None,) * 4})
         self.ws = N.Workspace(n, self.cfg, device=device)
         self.h = 0.5 * cfg.dt
 

@@ -208,3 +208,27 @@ def test_step_graph_replay_bitwise(dev, precision):
     _say(precision, "rows refined in binary64 per replayed step", refined)
     if prec == N.MIXED:
         assert min(refined) > 0
+
+
+@pytest.mark.parametrize("n", [100, 3000, 8191])
+def test_mixed_step_of_small_systems_is_the_binary64_step(dev, n):
+    # below 8,192 bodies genga_step takes the binary64 kick, the faster one
+    # there; a form flag keeps the mixed one
+    d = W.make_disk(W.DiskSpec(f"disk_n{n}", n, 0.5, 2.0, 3.0, seed=60 + n))
+    out = {}
+    for name, prec, flags in (("fp64", N.FP64, 0), ("mixed", N.MIXED, 0), ("form", N.MIXED, N.FLAG_DIRECTED)):
+        st = N.State.from_numpy(d)
+        cfg = N.Config(G=G, precision=prec, flags=flags)
+        ws = N.Workspace(n, cfg)
+        pl = N.PairList(64 * n)
+        assert N.step(st, cfg, ws, pl) == N.OK
+        out[name] = (st, pl.result())
+    for k in N.State.KEYS:
+        assert torch.equal(out["fp64"][0].t[k], out["mixed"][0].t[k]), k
+        a, b = out["fp64"][0].t[k], out["form"][0].t[k]
+        assert (a - b).abs().max() <= 1e-9 * a.abs().max(), k
+    for k in (0, 1):
+        assert np.array_equal(out["fp64"][1][k], out["mixed"][1][k])
+        assert np.array_equal(out["fp64"][1][k], out["form"][1][k])
+    # binary32 rounding shows in the velocities of the mixed kick
+    assert not torch.equal(out["fp64"][0].t["vx"], out["form"][0].t["vx"])
