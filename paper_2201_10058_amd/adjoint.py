@@ -30,6 +30,18 @@ def _state(X, V, m, rc) -> N.State:
                     "m": m, "rc": rc})
 
 
+class _Fixed(N.Config):
+    """A pass's own configuration, never changed: its structure is filled once
+    (several microseconds each time, at fourteen calls per step)."""
+
+    def __init__(self, **values):
+        super().__init__(**values)
+        self._params = super().params()
+
+    def params(self) -> N.Params:
+        return self._params
+
+
 class _Runner:
     def __init__(self, n, cfg: N.Config, device):
         if cfg.c_light or cfg.slevels > 1 or cfg.direct or cfg.tp_mode:
@@ -42,54 +54,66 @@ class _Runner:
             # form, so that the forward pass runs the kicks that the backward
             # pass recomputes
             flags |= N.FLAG_DIRECTED
-        self.cfg = N.Config(**{**cfg.__dict__, "flags": flags, "events": (None,) * 4})
+        self.cfg = _Fixed(**{**cfg.__dict__, "flags": flags, "events": (None,) * 4})
         self.ws = N.Workspace(n, self.cfg, device=device)
         self.h = 0.5 * cfg.dt
 
-    def step_saving(self, X, V, m, rc):
-        """One step in place on (X, V); returns the intermediates the adjoint needs."""
-        st = _state(X, V, m, rc)
-        cfg, ws, h = self.cfg, self.ws, self.h
-        x0, v0 = X.clone(), V.clone()
-        N.rcrit(st, cfg, ws)
-        rc_used = rc.clone()
-        N.kick(st, cfg, ws, h)
-        v1 = V.clone()
-        N.hc(st, cfg, ws, h)
-        xa = X.clone()
-        N.drift(st, cfg, ws, cfg.dt)
-        v2 = V.clone()
-        N.hc(st, cfg, ws, h)
-        xc = X.clone()
-        N.kick(st, cfg, ws, h)
-        return dict(x0=x0, v0=v0, rc=rc_used, v1=v1, xa=xa, v2=v2, xc=xc)
-
-    def step(self, X, V, m, rc):
-        st = _state(X, V, m, rc)
+    def step(self, st):
         code = N.step(st, self.cfg, self.ws)
         if code not in (N.OK,):
             raise N.GengaError(code, "genga_step")
 
-    def step_adjoint(self, sv, m, adj: N.AdjointState):
+    def segment_saving(self, X, V, m, steps):
+        """The steps of a segment from (X, V); per step the states that the
+        adjoint needs: the step's input, that of the drift (after the first
+        kick and HC) and its output after the second HC, with the step's
+        radii.  The operators work in place, each on its own copy in one
+        buffer.  The last step's second kick is left out: nothing reads it."""
+        n, cfg, ws, h = m.shape[0], self.cfg, self.ws, self.h
+        buf = torch.empty((3 * steps, 6, n), dtype=torch.float64, device=m.device)
+        buf[0, :3].copy_(X)
+        buf[0, 3:].copy_(V)
+        S = buf.unbind(0)
+        rows = buf.view(18 * steps, n).unbind(0)
+        RC = torch.empty((steps, n), dtype=torch.float64, device=m.device).unbind(0)
+        _state(buf[0, :3], buf[0, 3:], m, RC[0])    # checks m, as saved by the graph
+        saved = []
+        for k in range(steps):
+            at = [rows[6 * (3 * k + j):6 * (3 * k + j + 1)] for j in range(3)]
+            first, drift, second = st = [N.State._of_rows(r, m, RC[k]) for r in at]
+            if k:
+                # the second half kick of the step before, with its radii
+                S[3 * k].copy_(S[3 * k - 1])
+                N.kick(N.State._of_rows(at[0], m, RC[k - 1]), cfg, ws, h)
+            N.rcrit(first, cfg, ws)
+            S[3 * k + 1].copy_(S[3 * k])
+            N.kick(drift, cfg, ws, h)
+            N.hc(drift, cfg, ws, h)
+            S[3 * k + 2].copy_(S[3 * k + 1])
+            N.drift(second, cfg, ws, cfg.dt)
+            N.hc(second, cfg, ws, h)
+            saved.append(st)
+        return saved
+
+    def step_adjoint(self, saved, adj: N.AdjointState):
         """Reverse one step: adj holds (xbar, vbar) of the step's output on entry
-        and of its input on exit; adj.m accumulates."""
+        and of its input on exit; adj.m accumulates.  A kick's adjoint leaves
+        vbar as it is, so the accelerations' adjoint is read there."""
         cfg, ws, h = self.cfg, self.ws, self.h
+        first, drift, second = saved
+        vbar = [adj.t[k] for k in _V]
         adj.t["rc"].zero_()
         # second half kick at (xc, m, rc): abar = h vbar
-        st = _state(sv["xc"], sv["v2"], m, sv["rc"])
-        vb = [adj.t[k].clone() for k in _V]
-        N.kick_vjp(st, cfg, ws, h, vb, adj)
+        N.kick_vjp(second, cfg, ws, h, vbar, adj)
         # HC at v2
-        N.hc_vjp(_state(sv["xc"], sv["v2"], m, sv["rc"]), cfg, ws, h, adj)
+        N.hc_vjp(second, cfg, ws, h, adj)
         # drift at its input (xa, v1)
-        N.drift_vjp(_state(sv["xa"], sv["v1"], m, sv["rc"]), cfg, ws, cfg.dt, adj)
+        N.drift_vjp(drift, cfg, ws, cfg.dt, adj)
         # HC at v1
-        N.hc_vjp(_state(sv["xa"], sv["v1"], m, sv["rc"]), cfg, ws, h, adj)
-        # first half kick at (x0, m, rc)
-        vb = [adj.t[k].clone() for k in _V]
-        N.kick_vjp(_state(sv["x0"], sv["v1"], m, sv["rc"]), cfg, ws, h, vb, adj)
-        # critical radii at (x0, v0, m)
-        N.rcrit_vjp(_state(sv["x0"], sv["v0"], m, sv["rc"]), cfg, ws, adj)
+        N.hc_vjp(drift, cfg, ws, h, adj)
+        # first half kick and critical radii at the step's input
+        N.kick_vjp(first, cfg, ws, h, vbar, adj)
+        N.rcrit_vjp(first, cfg, ws, adj)
 
 
 class Trajectory(torch.autograd.Function):
@@ -105,10 +129,11 @@ class Trajectory(torch.autograd.Function):
         mm = m.detach().contiguous()
         rc = torch.zeros(n, dtype=torch.float64, device=device)
         ckpts = []
+        st = _state(X, V, mm, rc)
         for k in range(steps):
             if k % checkpoint_every == 0:
                 ckpts.append((k, X.clone(), V.clone()))
-            run.step(X, V, mm, rc)
+            run.step(st)
         code = N.read_status(run.ws)
         if code != N.OK:
             raise N.GengaError(code, "trajectory forward")
@@ -132,13 +157,10 @@ class Trajectory(torch.autograd.Function):
             adj.t[k].copy_(gX[c])
         for c, k in enumerate(_V):
             adj.t[k].copy_(gV[c])
-        rc = torch.zeros(n, dtype=torch.float64, device=device)
         for (k0, Xc, Vc) in reversed(ctx.ckpts):
             k1 = min(k0 + ctx.ce, ctx.steps)
-            X, V = Xc.clone(), Vc.clone()
-            saved = [run.step_saving(X, V, m, rc) for _ in range(k0, k1)]
-            for sv in reversed(saved):
-                run.step_adjoint(sv, m, adj)
+            for saved in reversed(run.segment_saving(Xc, Vc, m, k1 - k0)):
+                run.step_adjoint(saved, adj)
         code = N.read_status(run.ws)
         if code != N.OK:
             raise N.GengaError(code, "trajectory backward")

@@ -319,6 +319,9 @@ struct BatchDev {
 hipError_t launch_kick_vjp(const genga_bodies *b, const genga_params *p, double scale,
                            const double *abx, const double *aby, const double *abz,
                            genga_adjoint *adj, char *ws, hipStream_t s);
+hipError_t launch_kick_vjp_rows(const genga_bodies *b, double G, double scale, const double *abx,
+                                const double *aby, const double *abz, const genga_adjoint *adj,
+                                int32_t *status, hipStream_t s);
 hipError_t launch_rcrit_vjp(const genga_bodies *b, const genga_params *p, genga_adjoint *adj,
                             hipStream_t s);
 hipError_t launch_hc_vjp(const genga_bodies *b, const genga_params *p, double h, genga_adjoint *adj,

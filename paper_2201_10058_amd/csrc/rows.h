@@ -86,7 +86,7 @@ __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROW
                                             const double (&rc2i)[ROWS_G], double rg, int n, int r0,
                                             int j, double xj, double yj, double zj, double mj,
                                             double rcj, double c53, int word, int lane,
-                                            int32_t *status, double (&acc)[3 * ROWS_G])
+                                            int32_t &bad, double (&acc)[3 * ROWS_G])
 {
     double dx[ROWS_G], dy[ROWS_G], dz[ROWS_G], r2[ROWS_G], sc[ROWS_G];
     const double m15 = 1.5 * mj, rc2j = rcj * rcj;
@@ -107,11 +107,12 @@ __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROW
     if (__any(near <= vmax_f64(rg, rc2j))) {
 #pragma unroll
         for (int q = 0; q < ROWS_G; ++q) {
-            const double rho2 = rc2i[q] > rc2j ? rc2i[q] : rc2j;
+            const double rho2 = vmax_f64(rc2i[q], rc2j);
+            if (!__any(r2[q] <= rho2)) continue;
             const bool same = r2[q] == 0.0;
             // (a column past the end repeats the last body without its mass)
             const bool inside = r2[q] < rho2 && !same && j < n;
-            if (same && j < n && j != r0 + q) atomicOr(status, ST_NONFINITE);
+            if (same && j < n && j != r0 + q) bad |= ST_NONFINITE;
             if (inside || same) sc[q] = 0.0;
             const uint64_t mask = __ballot(inside);
             if (mask && lane == 0) sm.bits[q][word] = mask;
@@ -168,15 +169,16 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
     }
     rg = wave_uniform(rg);
     double acc[3 * ROWS_G] = {};
+    int32_t bad = 0;
     __syncthreads();
 
     auto column = [&](int j0, RowsColumn v) {
         const int j = j0 + tid;
         if (j >= n) v.m = 0.0;
         // (the rows of team 0 meet every column)
-        if (r0 == 0 && !(v.rc >= 0.0 && v.rc < INFINITY)) atomicOr(status, ST_RCRIT);
+        if (r0 == 0 && !(v.rc >= 0.0 && v.rc < INFINITY)) bad |= ST_RCRIT;
         rows_column(sm, xi, yi, zi, rc2i, rg, n, r0, j, v.x, v.y, v.z, v.m, v.rc, c53,
-                    (j0 >> 6) + w, lane, status, acc);
+                    (j0 >> 6) + w, lane, bad, acc);
     };
     for (int j0 = 0; j0 < n; j0 += 512) {
         B = rows_load(c, n, j0 + 256 + tid);
@@ -185,6 +187,7 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
         A = rows_load(c, n, j0 + 512 + tid);
         column(j0 + 256, B);
     }
+    if (bad) atomicOr(status, bad);
     // 12 sums over the wave: two halvings, then the 16 lanes of a row; row h
     // of the wave ends with the sums of row group member h
     double v[6];

@@ -6,7 +6,7 @@
 // bodies: 3 us of pair work per kick on the whole chip).  The tiled kick cuts
 // the columns into slices, whose sums a second kernel adds; its diagonal
 // waves enter the rare path once per column for the self pair (14 of the 15.6
-// us of that kick).  Here a block owns 8 rows and every column
+// us of that kick).  Here a block owns 4 rows and every column
 // (csrc/rows.h), so that the block ends with the accelerations themselves:
 // the velocities, the rows' momentum and, in the second half kick, the Sun
 // kick of the step are applied in the same kernel.

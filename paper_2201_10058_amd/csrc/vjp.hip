@@ -310,6 +310,8 @@ hipError_t launch_kick_vjp(const genga_bodies *b, const genga_params *p, double 
         return launch_kick_vjp_sym(c.sym, b, p->G, scale, abx, aby, abz, adj,
                                    (double *)(ws + L.part), (int32_t *)(ws + L.status), s);
     }
+    if (c.use_rows)
+        return launch_kick_vjp_rows(b, p->G, scale, abx, aby, abz, adj, (int32_t *)ws, s);
     // one row per thread for the adjoint (its register footprint is larger)
     c.ipt = 1;
     c.gx = (int)((b->n + KB - 1) / KB);

@@ -189,7 +189,9 @@ def _require_gpu(t: torch.Tensor, dtype=torch.float64):
 
 
 def _stream_ptr() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # torch.cuda.current_stream().cuda_stream without its wrapper objects, whose
+    # 3 us were a third of the host's time for a call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 @dataclass
@@ -218,20 +220,12 @@ class Config:
     coll_tol: float = 0.0
 
     def params(self) -> Params:
-        p = Params(self.G, self.m_star, self.dt, self.n1, self.n2, self.precision, self.flags,
-                   self.ipt, self.slices, self.block, self.tile_cols, self.grid)
-        for k, e in enumerate(tuple(self.events)[:4]):
-            p.prof_events[k] = e
-        p.tp_mode = self.tp_mode
-        p.n_massive = self.n_massive
-        p.slevels = self.slevels
-        p.substeps = self.substeps
-        p.level_capacity = self.level_capacity
-        p.direct = self.direct
-        p.bs_eps = self.bs_eps
-        p.c_light = self.c_light
-        p.coll_tol = self.coll_tol
-        return p
+        # (in one call: setting the fields one by one takes twice the time)
+        return Params(self.G, self.m_star, self.dt, self.n1, self.n2, self.precision, self.flags,
+                      self.ipt, self.slices, self.block, self.tile_cols, self.grid,
+                      tuple(self.events)[:4], self.tp_mode, self.slevels, self.n_massive,
+                      self.substeps, self.direct, self.level_capacity, self.bs_eps, self.c_light,
+                      self.coll_tol)
 
 
 class State:
@@ -262,13 +256,21 @@ class State:
             t["R"] = torch.as_tensor(radius, dtype=torch.float64).to(device).contiguous()
         return cls(t)
 
+    @classmethod
+    def _of_rows(cls, rows, m, rc):
+        """A state over six rows (x, y, z, vx, vy, vz) of one checked buffer and
+        checked m and rc of the same length."""
+        st = cls.__new__(cls)
+        st.t = dict(zip(cls.KEYS, (*rows, m, rc)))
+        st.n = m.shape[0]
+        return st
+
     def bodies(self) -> Bodies:
-        b = Bodies()
-        b.n = self.n
-        for k in self.KEYS:
-            setattr(b, k, self.t[k].data_ptr())
-        b.R = self.t["R"].data_ptr() if "R" in self.t else None
-        return b
+        t = self.t
+        R = t.get("R")
+        return Bodies(self.n, t["x"].data_ptr(), t["y"].data_ptr(), t["z"].data_ptr(),
+                      t["vx"].data_ptr(), t["vy"].data_ptr(), t["vz"].data_ptr(), t["m"].data_ptr(),
+                      t["rc"].data_ptr(), None if R is None else R.data_ptr())
 
     def numpy(self) -> dict:
         return {k: v.detach().cpu().numpy().copy() for k, v in self.t.items()}
@@ -310,7 +312,7 @@ class Workspace:
 
 
 def read_status(ws: Workspace) -> int:
-    return load().genga_read_status(ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr()))
+    return load().genga_read_status(ws.ptr, _stream_ptr())
 
 
 def kick_static(state: State, cfg: Config, h: float, acc: bool = False,
@@ -328,15 +330,15 @@ def kick_static(state: State, cfg: Config, h: float, acc: bool = False,
     ps = pairs.struct() if pairs is not None else None
     _check(load().genga_kick_static(ctypes.byref(b), ctypes.byref(p), float(h), ptrs[0], ptrs[1],
                                     ptrs[2], ctypes.byref(ps) if ps is not None else None,
-                                    ctypes.c_void_p(status.data_ptr()),
-                                    ctypes.c_void_p(_stream_ptr())), "genga_kick_static")
+                                    status.data_ptr(),
+                                    _stream_ptr()), "genga_kick_static")
     return a, status
 
 
 def rcrit(state: State, cfg: Config, ws: Workspace):
     b, p = state.bodies(), cfg.params()
-    _check(load().genga_rcrit(ctypes.byref(b), ctypes.byref(p), ctypes.c_void_p(ws.ptr),
-                              ctypes.c_void_p(_stream_ptr())), "genga_rcrit")
+    _check(load().genga_rcrit(ctypes.byref(b), ctypes.byref(p), ws.ptr,
+                              _stream_ptr()), "genga_rcrit")
 
 
 def kick(state: State, cfg: Config, ws: Workspace, h: float, acc: bool = False,
@@ -350,28 +352,28 @@ def kick(state: State, cfg: Config, ws: Workspace, h: float, acc: bool = False,
         ptrs = (a[0].data_ptr(), a[1].data_ptr(), a[2].data_ptr())
     ps = pairs.struct() if pairs is not None else None
     _check(load().genga_kick(ctypes.byref(b), ctypes.byref(p), float(h), ptrs[0], ptrs[1], ptrs[2],
-                             ctypes.byref(ps) if ps is not None else None, ctypes.c_void_p(ws.ptr),
-                             ctypes.c_void_p(_stream_ptr())), "genga_kick")
+                             ctypes.byref(ps) if ps is not None else None, ws.ptr,
+                             _stream_ptr()), "genga_kick")
     return a
 
 
 def encounter_pairs(state: State, cfg: Config, ws: Workspace, pairs: PairList):
     b, p, ps = state.bodies(), cfg.params(), pairs.struct()
     _check(load().genga_encounter_pairs(ctypes.byref(b), ctypes.byref(p), ctypes.byref(ps),
-                                        ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+                                        ws.ptr, _stream_ptr()),
            "genga_encounter_pairs")
 
 
 def hc(state: State, cfg: Config, ws: Workspace, h: float):
     b, p = state.bodies(), cfg.params()
-    _check(load().genga_hc(ctypes.byref(b), ctypes.byref(p), float(h), ctypes.c_void_p(ws.ptr),
-                           ctypes.c_void_p(_stream_ptr())), "genga_hc")
+    _check(load().genga_hc(ctypes.byref(b), ctypes.byref(p), float(h), ws.ptr,
+                           _stream_ptr()), "genga_hc")
 
 
 def drift(state: State, cfg: Config, ws: Workspace, dt: float):
     b, p = state.bodies(), cfg.params()
-    _check(load().genga_drift(ctypes.byref(b), ctypes.byref(p), float(dt), ctypes.c_void_p(ws.ptr),
-                              ctypes.c_void_p(_stream_ptr())), "genga_drift")
+    _check(load().genga_drift(ctypes.byref(b), ctypes.byref(p), float(dt), ws.ptr,
+                              _stream_ptr()), "genga_drift")
 
 
 def step(state: State, cfg: Config, ws: Workspace, pairs: PairList | None = None) -> int:
@@ -379,8 +381,8 @@ def step(state: State, cfg: Config, ws: Workspace, pairs: PairList | None = None
     b, p = state.bodies(), cfg.params()
     ps = pairs.struct() if pairs is not None else None
     code = load().genga_step(ctypes.byref(b), ctypes.byref(p),
-                             ctypes.byref(ps) if ps is not None else None, ctypes.c_void_p(ws.ptr),
-                             ctypes.c_void_p(_stream_ptr()))
+                             ctypes.byref(ps) if ps is not None else None, ws.ptr,
+                             _stream_ptr())
     if code in (E_INVAL, E_HIP, E_UNSUPPORTED):
         raise GengaError(code, "genga_step")
     return code
@@ -392,9 +394,9 @@ def level_counts(n: int, cfg: Config, ws: Workspace):
     import numpy as np
     out = np.zeros(max(cfg.slevels, 1), dtype=np.int64)
     p = cfg.params()
-    _check(load().genga_level_counts(n, ctypes.byref(p), ctypes.c_void_p(ws.ptr),
+    _check(load().genga_level_counts(n, ctypes.byref(p), ws.ptr,
                                      out.ctypes.data_as(ctypes.c_void_p),
-                                     ctypes.c_void_p(_stream_ptr())), "genga_level_counts")
+                                     _stream_ptr()), "genga_level_counts")
     return out
 
 
@@ -405,8 +407,8 @@ def energy_k(state: State, cfg: Config, ws: Workspace, pairs: PairList, out=None
         out = torch.empty(6, dtype=torch.float64, device=state.t["x"].device)
     b, p, ps = state.bodies(), cfg.params(), pairs.struct()
     _check(load().genga_energy_k(ctypes.byref(b), ctypes.byref(p), ctypes.byref(ps),
-                                 ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(ws.ptr),
-                                 ctypes.c_void_p(_stream_ptr())), "genga_energy_k")
+                                 out.data_ptr(), ws.ptr,
+                                 _stream_ptr()), "genga_energy_k")
     return out
 
 
@@ -414,7 +416,7 @@ def gr_kick(state: State, cfg: Config, ws: Workspace, h: float) -> None:
     """Post-Newtonian velocity update over h (asynchronous)."""
     b, p = state.bodies(), cfg.params()
     _check(load().genga_gr_kick(ctypes.byref(b), ctypes.byref(p), ctypes.c_double(h),
-                                ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+                                ws.ptr, _stream_ptr()),
            "genga_gr_kick")
 
 
@@ -427,10 +429,10 @@ def collisions(n: int, cfg: Config, ws: Workspace, cap: int = 4096):
     j = np.zeros(max(cap, 1), dtype=np.int32)
     du = np.zeros(max(cap, 1), dtype=np.float64)
     p = cfg.params()
-    _check(load().genga_collisions(n, ctypes.byref(p), ctypes.c_void_p(ws.ptr),
+    _check(load().genga_collisions(n, ctypes.byref(p), ws.ptr,
                                    c.ctypes.data_as(ctypes.c_void_p), i.ctypes.data_as(ctypes.c_void_p),
                                    j.ctypes.data_as(ctypes.c_void_p), du.ctypes.data_as(ctypes.c_void_p),
-                                   int(cap), ctypes.c_void_p(_stream_ptr())), "genga_collisions")
+                                   int(cap), _stream_ptr()), "genga_collisions")
     k = int(min(c[0], cap, 4096))
     return int(c[0]), [(int(i[q]), int(j[q]), float(du[q])) for q in range(k)]
 
@@ -440,9 +442,9 @@ def group_stats(n: int, cfg: Config, ws: Workspace):
     import numpy as np
     out = np.zeros(2, dtype=np.int64)
     p = cfg.params()
-    _check(load().genga_group_stats(n, ctypes.byref(p), ctypes.c_void_p(ws.ptr),
+    _check(load().genga_group_stats(n, ctypes.byref(p), ws.ptr,
                                     out.ctypes.data_as(ctypes.c_void_p),
-                                    ctypes.c_void_p(_stream_ptr())), "genga_group_stats")
+                                    _stream_ptr()), "genga_group_stats")
     return int(out[0]), int(out[1])
 
 
@@ -452,8 +454,8 @@ def energy(state: State, cfg: Config, ws: Workspace, out=None):
     if out is None:
         out = torch.empty(5, dtype=torch.float64, device=state.t["x"].device)
     b, p = state.bodies(), cfg.params()
-    _check(load().genga_energy(ctypes.byref(b), ctypes.byref(p), ctypes.c_void_p(out.data_ptr()),
-                               ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+    _check(load().genga_energy(ctypes.byref(b), ctypes.byref(p), out.data_ptr(),
+                               ws.ptr, _stream_ptr()),
            "genga_energy")
     return out
 
@@ -497,7 +499,7 @@ class BatchWorkspace:
         self.buf = torch.zeros(int(nbytes), dtype=torch.uint8, device=device)
         self.nbytes = int(nbytes)
         _check(lib.genga_batch_plan(ctypes.byref(self.bt), ctypes.byref(p), ctypes.c_void_p(self.ptr),
-                                    ctypes.c_void_p(_stream_ptr())), "genga_batch_plan")
+                                    _stream_ptr()), "genga_batch_plan")
         info = (ctypes.c_int64 * 5)()
         _check(lib.genga_batch_info(ctypes.byref(self.bt), ctypes.byref(p), info), "genga_batch_info")
         self.info = dict(tiles=info[0], grid=info[1], block=info[2], ipt=info[3], tile_cols=info[4])
@@ -519,7 +521,7 @@ def kick_batched(state: State, ws: BatchWorkspace, cfg: Config, hfac: float, acc
     _check(load().genga_kick_batched(ctypes.byref(b), ctypes.byref(ws.bt), ctypes.byref(p), float(hfac),
                                      ptrs[0], ptrs[1], ptrs[2],
                                      ctypes.byref(ps) if ps is not None else None,
-                                     ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+                                     ws.ptr, _stream_ptr()),
            "genga_kick_batched")
     return a
 
@@ -529,7 +531,7 @@ def step_batched(state: State, ws: BatchWorkspace, cfg: Config, pairs: PairList 
     ps = pairs.struct() if pairs is not None else None
     code = load().genga_step_batched(ctypes.byref(b), ctypes.byref(ws.bt), ctypes.byref(p),
                                      ctypes.byref(ps) if ps is not None else None,
-                                     ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr()))
+                                     ws.ptr, _stream_ptr())
     if code in (E_INVAL, E_HIP, E_UNSUPPORTED):
         raise GengaError(code, "genga_step_batched")
     return code
@@ -564,26 +566,26 @@ def kick_vjp(state: State, cfg: Config, ws: Workspace, scale: float, abar, adj: 
     b, p, a = state.bodies(), cfg.params(), adj.struct()
     ptrs = [_require_gpu(t) for t in abar]
     _check(load().genga_kick_vjp(ctypes.byref(b), ctypes.byref(p), float(scale), ptrs[0], ptrs[1],
-                                 ptrs[2], ctypes.byref(a), ctypes.c_void_p(ws.ptr),
-                                 ctypes.c_void_p(_stream_ptr())), "genga_kick_vjp")
+                                 ptrs[2], ctypes.byref(a), ws.ptr,
+                                 _stream_ptr()), "genga_kick_vjp")
 
 
 def rcrit_vjp(state: State, cfg: Config, ws: Workspace, adj: AdjointState):
     b, p, a = state.bodies(), cfg.params(), adj.struct()
     _check(load().genga_rcrit_vjp(ctypes.byref(b), ctypes.byref(p), ctypes.byref(a),
-                                  ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+                                  ws.ptr, _stream_ptr()),
            "genga_rcrit_vjp")
 
 
 def hc_vjp(state: State, cfg: Config, ws: Workspace, h: float, adj: AdjointState):
     b, p, a = state.bodies(), cfg.params(), adj.struct()
     _check(load().genga_hc_vjp(ctypes.byref(b), ctypes.byref(p), float(h), ctypes.byref(a),
-                               ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+                               ws.ptr, _stream_ptr()),
            "genga_hc_vjp")
 
 
 def drift_vjp(state: State, cfg: Config, ws: Workspace, dt: float, adj: AdjointState):
     b, p, a = state.bodies(), cfg.params(), adj.struct()
     _check(load().genga_drift_vjp(ctypes.byref(b), ctypes.byref(p), float(dt), ctypes.byref(a),
-                                  ctypes.c_void_p(ws.ptr), ctypes.c_void_p(_stream_ptr())),
+                                  ws.ptr, _stream_ptr()),
            "genga_drift_vjp")

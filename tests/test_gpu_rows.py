@@ -116,3 +116,36 @@ def test_step_graph_replay(dev):
         a, b = pl.result(), pl_e.result()
         assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     assert N.read_status(ws) == N.OK and N.read_status(ws_e) == N.OK
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 64, 65, 255, 256, 257, 511, 513, 1031, 4097, 8191])
+def test_kick_vjp_against_tiled_form(dev, n, dense):
+    # the row-group VJP against the tiled gather form (column slices given),
+    # which the autograd test pins.  Both round every term of a sum to a few
+    # units of 2^-52 and add n of them in different orders, so they differ by
+    # less than 64 * 2^-52 * sqrt(n) of the sum of the terms' sizes; the
+    # largest gradient component stands for that sum with a factor of 64 more
+    # for cancellation in it.  64 * 64 * 2^-52 * sqrt(8191) = 8e-11
+    d = W.random_cloud(n, seed=40 + n, rc_scale=0.6 if dense else 0.03)
+    st = N.State.from_numpy(d)
+    rng = np.random.default_rng(n)
+    ab = [torch.tensor(rng.normal(size=n), device="cuda") for _ in range(3)]
+    base = {k: rng.normal(size=n) for k in N.AdjointState.KEYS}
+    out = []
+    for slices in (0, 3):
+        cfg = N.Config(G=G, slices=slices)
+        ws = N.Workspace(n, cfg)
+        adj = N.AdjointState(n, tensors={k: torch.tensor(v, device="cuda") for k, v in base.items()})
+        N.kick_vjp(st, cfg, ws, 0.7, ab, adj)
+        assert N.read_status(ws) == N.OK
+        out.append({k: adj.t[k].cpu().numpy() for k in adj.KEYS})
+    for k in ("vx", "vy", "vz"):
+        assert np.array_equal(out[0][k], base[k])
+    for k in ("x", "y", "z", "m", "rc"):
+        size = max(np.abs(out[1][k] - base[k]).max(), 1.0)
+        assert np.abs(out[0][k] - out[1][k]).max() <= 8e-11 * size, k
+    if n == 1:
+        assert all(np.array_equal(out[0][k], base[k]) for k in base)
+    else:
+        assert np.array_equal(out[0]["rc"] != base["rc"], out[1]["rc"] != base["rc"])
