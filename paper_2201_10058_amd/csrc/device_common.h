@@ -21,6 +21,15 @@ __device__ __forceinline__ double changeover_k(double r, double rho)
     return y2 / (2.0 * y2 - 2.0 * yv + 1.0);
 }
 
+// 1/sqrt(v) from v_rsq_f64 with a second-order correction (relative error a
+// few 2^-53).
+__device__ __forceinline__ double rsq_full(double v)
+{
+    const double y = __builtin_amdgcn_rsq(v);
+    const double e = __builtin_fma(-v, y * y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
 // K(y) of the same changeover on a precomputed y: the division by
 // 2y^2 - 2y + 1 (in [1/2, 1] on the band) by v_rcp_f64 and two Newton steps.
 __device__ __forceinline__ double changeover_of_y(double yv)

@@ -344,30 +344,28 @@ struct LevelLayout {
     size_t lcount = 0;                  // int64 [L]   summed list sizes per level
     size_t cnt = 0;                     // int64 [L]   current size of list l
     size_t nbod = 0;                    // int32 [L]   bodies of list l
-    size_t bcnt = 0;                    // int64 [DB]  detection block counts / offsets
-    size_t tsum = 0;                    // int64 [2][n / 256] adjacency tile sums / offsets
+    size_t bcnt = 0;                    // int64 [DB]  detection block counts
     size_t pi[GENGA_MAX_LEVELS] = {}, pj[GENGA_MAX_LEVELS] = {};   // int32 [cap]
-    size_t start[GENGA_MAX_LEVELS] = {};   // int32 [n + 1]  adjacency offsets
+    size_t start[GENGA_MAX_LEVELS] = {};   // int32 [n + 1]  first entry per body; the total
     size_t adj[GENGA_MAX_LEVELS] = {};     // int32 [2 cap]  partners, ascending per body
     size_t adj_tmp[GENGA_MAX_LEVELS] = {}; // int32 [2 cap]  partners in arrival order
     size_t owner[GENGA_MAX_LEVELS] = {};   // int32 [2 cap]  body of each arrival entry
     size_t deg[GENGA_MAX_LEVELS] = {};     // int32 [n]      degrees / fill counters
-    size_t bodies[GENGA_MAX_LEVELS] = {};  // int32 [n]      bodies of the list, ascending
+    size_t bodies[GENGA_MAX_LEVELS] = {};  // int32 [n]      bodies of the list
     size_t rc[GENGA_MAX_LEVELS] = {};      // double [n]     rc of level l (l >= 1)
-    size_t shadow[GENGA_MAX_LEVELS] = {};  // double [6][n]  state saved before a drift
+    size_t shadow[GENGA_MAX_LEVELS] = {};  // double [6][n]  level 0: state saved before the drift
     // direct solver (groups of the deepest list L - 1)
     int direct = 0;
-    size_t glab = 0;       // int32 [n]  parent in the union-find, then the group's root
+    size_t glab = 0;       // int32 [n]  the group's root
     size_t gflag = 0;      // int32 [n]  body in the deepest list
     size_t gsize = 0;      // int32 [n]  members per root
-    size_t gfill = 0;      // int32 [n]  fill counters per root
+    size_t gslot = 0;      // int32 [n]  the member's number in its group
     size_t gstart = 0;     // int32 [n]  first member slot per root
-    size_t groot = 0;      // int32 [n]  roots in ascending order (one per group)
-    size_t gtmp = 0;       // int32 [n]  members in arrival order
-    size_t gmem = 0;       // int32 [n]  members, ascending within each group of <= 512
-    size_t gcount = 0;     // int32 [2]  groups, members
+    size_t groot = 0;      // int32 [n]  roots: small groups from the front, medium ones from the back
+    size_t gtmp = 0;       // int32 [n]  parents of the union-find
+    size_t gmem = 0;       // int32 [n]  members by group, in arrival order
+    size_t gcount = 0;     // int32 [3]  small groups, members, medium groups
     size_t gstats = 0;     // int64 [2]  groups integrated, largest group (per step)
-    size_t gtsum = 0;      // int64 [2][n / 256] tile sums of the group scan
     size_t coll_count = 0; // uint64     collisions of the step
     size_t coll_i = 0, coll_j = 0;   // int32 [LEVEL_COLL_CAP] survivor, absorbed
     size_t coll_du = 0;    // double [LEVEL_COLL_CAP] lost energy

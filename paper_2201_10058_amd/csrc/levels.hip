@@ -31,10 +31,8 @@ namespace {
 
 constexpr int LT = 256;     // threads per block of the list kernels
 constexpr int LG = 1024;    // blocks of the grid-stride list kernels
-constexpr int LG_BIG = 512; // workgroups of the Bulirsch-Stoer class of 9-512 bodies (2 per CU)
 constexpr int GROUP_BLOCK = 512;   // largest group of the one-workgroup class
 constexpr int DB = 256;     // blocks (and chunks) of the list compaction
-constexpr int ST = 1024;    // threads of the one-block scan of the adjacency tile sums
 
 __device__ __forceinline__ int64_t list_len(const int64_t *cnt, int64_t cap)
 {
@@ -84,101 +82,119 @@ __global__ __launch_bounds__(LT) void k_copy_pairs(const int32_t *si, const int3
     }
 }
 
-__global__ __launch_bounds__(LT) void k_zero_i32(int32_t *a, int64_t n)
+// The bodies that a list kernel runs over: a list, or (bodies null) all n.
+struct ListDev {
+    const int32_t *bodies;
+    const int32_t *nbod;
+    int64_t n;
+};
+
+__device__ __forceinline__ int64_t list_count(const ListDev &a) { return a.bodies ? *a.nbod : a.n; }
+__device__ __forceinline__ int32_t list_body(const ListDev &a, int64_t q)
 {
-    for (int64_t k = (int64_t)blockIdx.x * LT + threadIdx.x; k < n; k += (int64_t)gridDim.x * LT)
-        a[k] = 0;
+    return a.bodies ? a.bodies[q] : (int32_t)q;
 }
 
 // ---------------------------------------------------------------------------
-// Adjacency of a list: degrees, their scan (offsets and the ascending list of
-// bodies), fill in arrival order, and placement of each entry at its rank
-// among the body's partners (so every segment is sorted ascending).
+// Adjacency of a list: degrees, a segment of the partner array per body, fill
+// in arrival order, and placement of each entry at its rank among the body's
+// partners (so every segment is sorted ascending).
 // ---------------------------------------------------------------------------
+struct AdjDev {
+    int32_t *deg;             // [n] degrees
+    int32_t *start;           // [n] first entry of the body's segment; [n]: entries of the list
+    int32_t *bodies, *nbod;   // the list's bodies
+    int64_t n;
+};
+
+// Everything of the list is empty before its degrees are counted.
+__device__ __forceinline__ void adj_begin(const AdjDev &A)
+{
+    A.start[A.n] = 0;
+    *A.nbod = 0;
+}
+
+// atomicAdd(ctr + key, 1) by the active lanes, equal keys of neighbouring lanes
+// (a list's pairs of one body i) by one atomic; returns such a slot.
+__device__ __forceinline__ int32_t run_add(int32_t *ctr, int32_t key)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned long long on = __ballot(true);
+    const int32_t prev = __shfl_up(key, 1, 64);
+    const bool head = lane == 0 || !((on >> (lane - 1)) & 1) || prev != key;
+    const unsigned long long heads = __ballot(head) | ~on;   // (an inactive lane ends a run)
+    const unsigned long long upto = heads & on & (~0ull >> (63 - lane));
+    const int lead = 63 - __builtin_clzll(upto);
+    int32_t base = 0;
+    if (head) {
+        const unsigned long long next = lane == 63 ? 0 : heads >> (lane + 1);
+        base = atomicAdd(ctr + key, next ? __builtin_ctzll(next) + 1 : 64 - lane);
+    }
+    return __shfl(base, lead, 64) + lane - lead;
+}
+
+__device__ __forceinline__ void adj_pair(const AdjDev &A, int32_t i, int32_t j)
+{
+    run_add(A.deg, i);
+    atomicAdd(A.deg + j, 1);
+}
+
+__global__ __launch_bounds__(LT) void k_adj_begin(AdjDev A)
+{
+    const int64_t t0 = (int64_t)blockIdx.x * LT + threadIdx.x;
+    for (int64_t k = t0; k < A.n; k += (int64_t)gridDim.x * LT) A.deg[k] = 0;
+    if (t0 == 0) adj_begin(A);
+}
+
 __global__ __launch_bounds__(LT) void k_adj_count(const int32_t *pi, const int32_t *pj,
-                                                  const int64_t *cnt, int64_t cap, int32_t *deg)
+                                                  const int64_t *cnt, int64_t cap, AdjDev A)
 {
     const int64_t m = list_len(cnt, cap);
-    for (int64_t p = (int64_t)blockIdx.x * LT + threadIdx.x; p < m; p += (int64_t)gridDim.x * LT) {
-        atomicAdd(deg + pi[p], 1);
-        atomicAdd(deg + pj[p], 1);
-    }
+    for (int64_t p = (int64_t)blockIdx.x * LT + threadIdx.x; p < m; p += (int64_t)gridDim.x * LT)
+        adj_pair(A, pi[p], pj[p]);
 }
 
-// Offsets and body list in three passes over tiles of LT bodies: tile sums
-// of the degrees and of the bodies with a pair, one block scanning the tile
-// sums, and the tiles again with those offsets.
-__global__ __launch_bounds__(LT) void k_adj_tiles(const int32_t *deg, int64_t n, int64_t *tsum)
+// Segments and the list of bodies with a pair (a superset of them: `up`).
+// Blocks take their shares of both by one atomic each, in the order in which they
+// arrive: nothing reads the order of the bodies or of the segments.
+__global__ __launch_bounds__(LT) void k_adj_alloc(ListDev up, AdjDev A)
 {
     __shared__ int64_t sm[LT / 64];
-    const int64_t k = (int64_t)blockIdx.x * LT + threadIdx.x;
-    const int32_t d = k < n ? deg[k] : 0;
-    int64_t td, tb;
-    block_excl_scan<LT>(d, &td, sm);
-    block_excl_scan<LT>(d > 0 ? 1 : 0, &tb, sm);
-    if (threadIdx.x == 0) {
-        tsum[2 * blockIdx.x] = td;
-        tsum[2 * blockIdx.x + 1] = tb;
+    __shared__ int32_t base[2];
+    const int64_t nb = list_count(up);
+    for (int64_t k0 = (int64_t)blockIdx.x * LT; k0 < nb; k0 += (int64_t)gridDim.x * LT) {
+        const int64_t k = k0 + threadIdx.x;
+        const int32_t i = k < nb ? list_body(up, k) : 0;
+        const int32_t d = k < nb ? A.deg[i] : 0;
+        int64_t tot;   // (entries, bodies) in one scan
+        const int64_t ex = block_excl_scan<LT>(((int64_t)d << 32) | (d > 0 ? 1 : 0), &tot, sm);
+        if (threadIdx.x == 0) {
+            base[0] = atomicAdd(A.start + A.n, (int32_t)(tot >> 32));
+            base[1] = atomicAdd(A.nbod, (int32_t)tot);
+        }
+        __syncthreads();
+        if (k < nb) {
+            A.start[i] = base[0] + (int32_t)(ex >> 32);
+            if (d > 0) A.bodies[base[1] + (int32_t)ex] = i;
+            A.deg[i] = 0;   // fill counter of k_adj_fill
+        }
+        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(ST) void k_adj_top(int64_t *tsum, int64_t ntiles, int32_t *start,
-                                                int64_t n, int32_t *nbod)
-{
-    __shared__ int64_t sm[ST / 64];
-    const int t = threadIdx.x;
-    const int64_t ch = (ntiles + ST - 1) / ST;
-    const int64_t k0 = min(ntiles, t * ch), k1 = min(ntiles, k0 + ch);
-    int64_t sd = 0, sb = 0;
-    for (int64_t k = k0; k < k1; ++k) {
-        sd += tsum[2 * k];
-        sb += tsum[2 * k + 1];
-    }
-    int64_t td, tb;
-    int64_t od = block_excl_scan<ST>(sd, &td, sm);
-    int64_t ob = block_excl_scan<ST>(sb, &tb, sm);
-    for (int64_t k = k0; k < k1; ++k) {
-        const int64_t a = tsum[2 * k], b = tsum[2 * k + 1];
-        tsum[2 * k] = od;
-        tsum[2 * k + 1] = ob;
-        od += a;
-        ob += b;
-    }
-    if (t == 0) {
-        start[n] = (int32_t)td;
-        *nbod = (int32_t)tb;
-    }
-}
-
-__global__ __launch_bounds__(LT) void k_adj_write(int32_t *deg, int64_t n, const int64_t *tsum,
-                                                  int32_t *start, int32_t *bodies)
-{
-    __shared__ int64_t sm[LT / 64];
-    const int64_t k = (int64_t)blockIdx.x * LT + threadIdx.x;
-    const int32_t d = k < n ? deg[k] : 0;
-    int64_t td, tb;
-    const int64_t od = block_excl_scan<LT>(d, &td, sm);
-    const int64_t ob = block_excl_scan<LT>(d > 0 ? 1 : 0, &tb, sm);
-    if (k < n) {
-        start[k] = (int32_t)(tsum[2 * blockIdx.x] + od);
-        if (d > 0) bodies[tsum[2 * blockIdx.x + 1] + ob] = (int32_t)k;
-        deg[k] = 0;   // fill counter of k_adj_fill
-    }
-}
-
-// Each pair into both bodies' segments, in arrival order (owner recorded).
+// Each pair into both bodies' segments, in arrival order (owner recorded); the
+// fill counters end as the degrees again.
 __global__ __launch_bounds__(LT) void k_adj_fill(const int32_t *pi, const int32_t *pj,
-                                                 const int64_t *cnt, int64_t cap,
-                                                 const int32_t *start, int32_t *fill, int32_t *tmp,
-                                                 int32_t *owner)
+                                                 const int64_t *cnt, int64_t cap, AdjDev A,
+                                                 int32_t *tmp, int32_t *owner)
 {
     const int64_t m = list_len(cnt, cap);
     for (int64_t p = (int64_t)blockIdx.x * LT + threadIdx.x; p < m; p += (int64_t)gridDim.x * LT) {
         const int32_t i = pi[p], j = pj[p];
-        const int32_t si = start[i] + atomicAdd(fill + i, 1);
+        const int32_t si = A.start[i] + run_add(A.deg, i);
         tmp[si] = j;
         owner[si] = i;
-        const int32_t sj = start[j] + atomicAdd(fill + j, 1);
+        const int32_t sj = A.start[j] + atomicAdd(A.deg + j, 1);
         tmp[sj] = i;
         owner[sj] = j;
     }
@@ -186,14 +202,14 @@ __global__ __launch_bounds__(LT) void k_adj_fill(const int32_t *pi, const int32_
 
 // Sorted placement: an entry's rank among its body's partners (all distinct)
 // is the number of smaller partners in the segment.
-__global__ __launch_bounds__(LT) void k_adj_rank(const int32_t *start, int64_t n, const int32_t *tmp,
-                                                 const int32_t *owner, int32_t *adj)
+__global__ __launch_bounds__(LT) void k_adj_rank(AdjDev A, const int32_t *tmp, const int32_t *owner,
+                                                 int32_t *adj)
 {
-    const int64_t total = start[n];
+    const int64_t total = A.start[A.n];
     for (int64_t e = (int64_t)blockIdx.x * LT + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * LT) {
         const int32_t b = owner[e], v = tmp[e];
-        const int32_t s0 = start[b], s1 = start[b + 1];
+        const int32_t s0 = A.start[b], s1 = s0 + A.deg[b];
         int32_t r = 0;
         for (int32_t q = s0; q < s1; ++q) r += tmp[q] < v;
         adj[s0 + r] = v;
@@ -201,202 +217,31 @@ __global__ __launch_bounds__(LT) void k_adj_rank(const int32_t *start, int64_t n
 }
 
 // ---------------------------------------------------------------------------
-// Next level's list: the pairs of list `in` closer than this level's
-// critical radius, in the same order.  DB chunks of the input: counts, one
-// scan, ordered writes.
-// ---------------------------------------------------------------------------
-struct DetectDev {
-    const int32_t *in_i, *in_j;
-    const int64_t *in_cnt;
-    int32_t *out_i, *out_j;
-    int64_t *out_cnt;
-    int64_t *lcount;          // summed sizes of this level's lists
-    int64_t cap;
-    const double *x, *y, *z, *rc;
-    int64_t *bcnt;            // [DB]
-};
-
-__device__ __forceinline__ bool detect_pair(const DetectDev &d, int64_t p)
-{
-    const int64_t i = d.in_i[p], j = d.in_j[p];
-    const double rho = rho_of(d.rc, i, j);
-    return sep2(d.x, d.y, d.z, i, j) < rho * rho;
-}
-
-__device__ __forceinline__ void chunk_of(const DetectDev &d, int64_t &p0, int64_t &p1)
-{
-    const int64_t m = list_len(d.in_cnt, d.cap);
-    const int64_t len = (m + DB - 1) / DB;
-    p0 = min(m, (int64_t)blockIdx.x * len);
-    p1 = min(m, p0 + len);
-}
-
-__global__ __launch_bounds__(LT) void k_detect_count(DetectDev d)
-{
-    __shared__ int64_t sm[LT / 64];
-    int64_t p0, p1;
-    chunk_of(d, p0, p1);
-    int64_t c = 0;
-    for (int64_t p = p0 + threadIdx.x; p < p1; p += LT) c += detect_pair(d, p);
-    int64_t tot;
-    block_excl_scan<LT>(c, &tot, sm);
-    if (threadIdx.x == 0) d.bcnt[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(DB) void k_detect_scan(DetectDev d)
-{
-    __shared__ int64_t sm[DB / 64];
-    const int64_t v = d.bcnt[threadIdx.x];
-    int64_t tot;
-    const int64_t ex = block_excl_scan<DB>(v, &tot, sm);
-    d.bcnt[threadIdx.x] = ex;
-    if (threadIdx.x == 0) {
-        *d.out_cnt = tot;
-        *d.lcount += tot;
-    }
-}
-
-__global__ __launch_bounds__(LT) void k_detect_write(DetectDev d)
-{
-    __shared__ int64_t sm[LT / 64];
-    int64_t p0, p1;
-    chunk_of(d, p0, p1);
-    int64_t run = d.bcnt[blockIdx.x];
-    for (int64_t t0 = p0; t0 < p1; t0 += LT) {
-        const int64_t p = t0 + threadIdx.x;
-        const bool f = p < p1 && detect_pair(d, p);
-        int64_t tot;
-        const int64_t ex = block_excl_scan<LT>(f ? 1 : 0, &tot, sm);
-        if (f) {
-            d.out_i[run + ex] = d.in_i[p];
-            d.out_j[run + ex] = d.in_j[p];
-        }
-        run += tot;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Per-body operators over a list's bodies.
-// ---------------------------------------------------------------------------
-struct BodyDev {
-    const int32_t *bodies;
-    const int32_t *nbod;
-    double *x, *y, *z, *vx, *vy, *vz;
-    const double *m;
-    int32_t *status;
-};
-
-__global__ __launch_bounds__(LT) void k_rcrit_list(BodyDev a, double *rc, double m_star, double dt,
-                                                   double n1, double n2)
-{
-    const int64_t nb = *a.nbod;
-    for (int64_t q = (int64_t)blockIdx.x * LT + threadIdx.x; q < nb; q += (int64_t)gridDim.x * LT) {
-        const int32_t i = a.bodies[q];
-        const double r = __builtin_sqrt(a.x[i] * a.x[i] + a.y[i] * a.y[i] + a.z[i] * a.z[i]);
-        const double v =
-            __builtin_sqrt(a.vx[i] * a.vx[i] + a.vy[i] * a.vy[i] + a.vz[i] * a.vz[i]);
-        const double rh = r * cbrt(a.m[i] / (3.0 * m_star));
-        const double h1 = n1 * rh, h2 = n2 * fabs(dt) * v;
-        const double out = h1 > h2 ? h1 : h2;
-        if (!(out >= 0.0 && out < INFINITY)) atomicOr(a.status, ST_RCRIT);
-        rc[i] = out;
-    }
-}
-
-__global__ __launch_bounds__(LT) void k_drift_list(BodyDev a, double mu, double dt)
-{
-    const int64_t nb = *a.nbod;
-    for (int64_t q = (int64_t)blockIdx.x * LT + threadIdx.x; q < nb; q += (int64_t)gridDim.x * LT) {
-        const int32_t i = a.bodies[q];
-        double X = a.x[i], Y = a.y[i], Z = a.z[i], VX = a.vx[i], VY = a.vy[i], VZ = a.vz[i];
-        const int st = kepler_uv(mu, dt, X, Y, Z, VX, VY, VZ);
-        if (st) atomicOr(a.status, st);
-        a.x[i] = X; a.y[i] = Y; a.z[i] = Z;
-        a.vx[i] = VX; a.vy[i] = VY; a.vz[i] = VZ;
-    }
-}
-
-// save = 1: shadow <- state; save = 0: state <- shadow (bodies of the list).
-__global__ __launch_bounds__(LT) void k_state_list(BodyDev a, double *shadow, int64_t n, int save)
-{
-    const int64_t nb = *a.nbod;
-    double *c[6] = {a.x, a.y, a.z, a.vx, a.vy, a.vz};
-    for (int64_t q = (int64_t)blockIdx.x * LT + threadIdx.x; q < nb; q += (int64_t)gridDim.x * LT) {
-        const int32_t i = a.bodies[q];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            if (save) shadow[(size_t)k * n + i] = c[k][i];
-            else c[k][i] = shadow[(size_t)k * n + i];
-        }
-    }
-}
-
-// Kick of level l over a list: v_b += h G sum_j m_j W_l(r_bj) (x_j - x_b) / r^3
-// for every body b of the list.  A group of GL lanes takes one body: lane u
-// adds the partners u, u + GL, ... of the body's ascending partner list, and
-// the GL partial sums are combined by a fixed butterfly, so the result does
-// not depend on scheduling.
-constexpr int GL = 8;
-
-struct LevelKickDev {
-    BodyDev a;
-    const int32_t *start, *adj;
-    const double *rc[GENGA_MAX_LEVELS];   // rc[0]: level 0 (the bodies' rc)
-    int level;
-    double G, h;
-};
-
-__global__ __launch_bounds__(LT) void k_level_kick(LevelKickDev k)
-{
-    const BodyDev &a = k.a;
-    const int64_t nb = *a.nbod;
-    const int u = threadIdx.x & (GL - 1);
-    const int64_t g0 = ((int64_t)blockIdx.x * LT + threadIdx.x) / GL;
-    const int64_t gstride = (int64_t)gridDim.x * (LT / GL);
-    // every lane of a group runs the same trip count (the body loop is
-    // uniform per group), so the butterfly below sees all GL lanes
-    for (int64_t q = g0; q < nb; q += gstride) {
-        const int32_t b = a.bodies[q];
-        const double xb = a.x[b], yb = a.y[b], zb = a.z[b];
-        double ax = 0.0, ay = 0.0, az = 0.0;
-        for (int32_t e = k.start[b] + u; e < k.start[b + 1]; e += GL) {
-            const int32_t j = k.adj[e];
-            const double dx = a.x[j] - xb, dy = a.y[j] - yb, dz = a.z[j] - zb;
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            if (r2 == 0.0) {
-                atomicOr(a.status, ST_NONFINITE);
-                continue;
-            }
-            const double r = __builtin_sqrt(r2);
-            double w = 1.0;
-            for (int l = 0; l < k.level; ++l) w *= 1.0 - changeover_k(r, rho_of(k.rc[l], b, j));
-            w *= changeover_k(r, rho_of(k.rc[k.level], b, j));
-            const double s = k.G * a.m[j] * w / (r2 * r);
-            ax += s * dx;
-            ay += s * dy;
-            az += s * dz;
-        }
-#pragma unroll
-        for (int d = GL / 2; d > 0; d >>= 1) {
-            ax += __shfl_xor(ax, d, GL);
-            ay += __shfl_xor(ay, d, GL);
-            az += __shfl_xor(az, d, GL);
-        }
-        if (u == 0) {
-            a.vx[b] += k.h * ax;
-            a.vy[b] += k.h * ay;
-            a.vz[b] += k.h * az;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Close-encounter groups of a list: connected components of its pair graph
 // by a lock-free union-find (a root is hooked under the smaller root, so each
 // group's root is its smallest body, whatever the order of the unions), then
-// per-root sizes, a scan over the roots in ascending order, and the members
-// of each group placed in ascending order (rank among the group's members).
+// the sizes per root, each member's arrival number in its group, and a slot per
+// group in the member array.  The solvers put a group's members into ascending
+// order themselves, so no result depends on an order of arrival.
 // ---------------------------------------------------------------------------
+struct GroupDev {
+    int32_t *parent;              // [n] union-find
+    int32_t *flag;                // [n] body in the list
+    int32_t *lab;                 // [n] its group's root
+    int32_t *size;                // [n] members per root
+    int32_t *slot;                // [n] the member's number in its group
+    int32_t *start;               // [n] the root's first slot in mem
+    int32_t *mem;                 // [n] members by group
+    int32_t *root;                // [n] roots: of groups of 2 .. BS_GS from the front, of
+                                  // GROUP_BLOCK from the back (k-th at n - 1 - k)
+    int32_t *count;               // [0] small groups, [1] members, [2] medium groups
+    int32_t *big;                 // optional: [0] larger groups, [1 ..] their roots
+    unsigned long long *gsync;    // the grid solver's barrier state
+    unsigned long long *gstats;   // groups integrated, largest of them
+    int32_t limit;                // members of the largest group that a solver takes
+    int64_t n;
+};
+
 // A parent read through the caches (workgroup scope) may be an older value:
 // every value a body's parent ever held is still one of its ancestors (trees
 // only merge) and a root's parent was itself until it was hooked, so an old
@@ -424,188 +269,419 @@ __device__ __forceinline__ int32_t uf_find(int32_t *parent, int32_t x)
     }
 }
 
-// atomicAdd(ctr + key, 1) for every active lane, one atomic per distinct key
-// of the wave; returns the lane's slot (the old value plus its rank among
-// the wave's lanes with the same key).
+// atomicAdd(ctr + key, 1) for every active lane; returns the old value, or
+// such a slot.  While the first lane left shares its key with more than three others (the
+// bodies of a large group), these take one atomic together; the rest of the
+// wave then takes one each, all in flight at once.
 __device__ __forceinline__ int32_t wave_add_by_key(int32_t *ctr, int32_t key, bool active)
 {
     unsigned long long todo = __ballot(active);
+    const int lane = threadIdx.x & 63;
     int32_t slot = 0;
     while (todo) {
         const int lead = __builtin_ctzll(todo);
         const int32_t k = __shfl(key, lead, 64);
-        const unsigned long long same = __ballot(active && key == k);
+        const unsigned long long same = __ballot(((todo >> lane) & 1) && key == k);
+        if (__popcll(same) <= 4) break;
         int32_t base = 0;
-        if ((int)(threadIdx.x & 63) == lead) base = atomicAdd(ctr + k, __popcll(same));
+        if (lane == lead) base = atomicAdd(ctr + k, __popcll(same));
         base = __shfl(base, lead, 64);
-        if (active && key == k) {
-            const unsigned long long lower = same & ((1ull << (threadIdx.x & 63)) - 1ull);
-            slot = base + __popcll(lower);
-        }
+        if ((same >> lane) & 1) slot = base + __popcll(same & ((1ull << lane) - 1ull));
         todo &= ~same;
     }
+    if ((todo >> lane) & 1) slot = atomicAdd(ctr + key, 1);
     return slot;
 }
 
-__global__ __launch_bounds__(LT) void k_group_init(int32_t *parent, int32_t *flag, int32_t *gsize,
-                                                   int32_t *gfill, int64_t n)
+constexpr int BS_GS = 8;      // lanes of a small group in the direct solver
+
+__device__ __forceinline__ void group_begin(const GroupDev &g, int32_t i)
 {
-    for (int64_t k = (int64_t)blockIdx.x * LT + threadIdx.x; k < n; k += (int64_t)gridDim.x * LT) {
-        parent[k] = (int32_t)k;
-        flag[k] = 0;
-        gsize[k] = 0;
-        gfill[k] = 0;
+    g.parent[i] = i;
+    g.flag[i] = 0;
+    g.size[i] = 0;
+}
+
+__device__ __forceinline__ void group_begin_all(const GroupDev &g)
+{
+    g.count[0] = g.count[1] = g.count[2] = 0;
+    if (g.big) {
+        // the grid solver's list and barrier state, fresh for its launch:
+        // arrivals, abort flag, three maximum slots, three minimum slots
+        g.big[0] = 0;
+        for (int k = 0; k < 5; ++k) g.gsync[k] = 0;
+        for (int k = 5; k < 8; ++k) g.gsync[k] = (unsigned long long)LLONG_MAX;
     }
+}
+
+__device__ __forceinline__ void group_union(const GroupDev &g, int32_t i, int32_t j)
+{
+    g.flag[i] = 1;
+    g.flag[j] = 1;
+    int32_t a0 = i, b0 = j;
+    for (;;) {
+        int32_t ra = uf_find(g.parent, a0), rb = uf_find(g.parent, b0);
+        if (ra == rb) break;   // a common ancestor: one tree
+        if (ra < rb) {
+            const int32_t t = ra;
+            ra = rb;
+            rb = t;
+        }
+        // hook the larger root under the smaller (a root is the smallest
+        // body of its tree, so rb < ra lies in another tree); a failed
+        // exchange means ra was hooked meanwhile: go on from its current
+        // parent, which the exchange returns
+        const int32_t old = atomicCAS(g.parent + ra, ra, rb);
+        if (old == ra) break;
+        a0 = old;
+        b0 = rb;
+    }
+}
+
+__global__ __launch_bounds__(LT) void k_group_begin(GroupDev g)
+{
+    const int64_t t0 = (int64_t)blockIdx.x * LT + threadIdx.x;
+    for (int64_t k = t0; k < g.n; k += (int64_t)gridDim.x * LT) group_begin(g, (int32_t)k);
+    if (t0 == 0) group_begin_all(g);
 }
 
 __global__ __launch_bounds__(LT) void k_group_union(const int32_t *pi, const int32_t *pj,
-                                                    const int64_t *cnt, int64_t cap,
-                                                    int32_t *parent, int32_t *flag)
+                                                    const int64_t *cnt, int64_t cap, GroupDev g)
 {
     const int64_t m = list_len(cnt, cap);
-    for (int64_t p = (int64_t)blockIdx.x * LT + threadIdx.x; p < m; p += (int64_t)gridDim.x * LT) {
-        const int32_t i = pi[p], j = pj[p];
-        flag[i] = 1;
-        flag[j] = 1;
-        int32_t a0 = i, b0 = j;
-        for (;;) {
-            int32_t ra = uf_find(parent, a0), rb = uf_find(parent, b0);
-            if (ra == rb) break;   // a common ancestor: one tree
-            if (ra < rb) {
-                const int32_t t = ra;
-                ra = rb;
-                rb = t;
-            }
-            // hook the larger root under the smaller (a root is the smallest
-            // body of its tree, so rb < ra lies in another tree); a failed
-            // exchange means ra was hooked meanwhile: go on from its current
-            // parent, which the exchange returns
-            const int32_t old = atomicCAS(parent + ra, ra, rb);
-            if (old == ra) break;
-            a0 = old;
-            b0 = rb;
-        }
-    }
+    for (int64_t p = (int64_t)blockIdx.x * LT + threadIdx.x; p < m; p += (int64_t)gridDim.x * LT)
+        group_union(g, pi[p], pj[p]);
 }
 
-// Root of every listed body (into lab), members counted per root.
-__global__ __launch_bounds__(LT) void k_group_root(int32_t *parent, const int32_t *flag,
-                                                   int32_t *lab, int32_t *gsize, int64_t n)
+// Root of every listed body, members counted and numbered per root.
+__global__ __launch_bounds__(LT) void k_group_root(ListDev up, GroupDev g)
 {
-    for (int64_t k0 = (int64_t)blockIdx.x * LT; k0 < n; k0 += (int64_t)gridDim.x * LT) {
+    const int64_t nb = list_count(up);
+    for (int64_t k0 = (int64_t)blockIdx.x * LT; k0 < nb; k0 += (int64_t)gridDim.x * LT) {
         const int64_t k = k0 + threadIdx.x;
-        const bool on = k < n && flag[k];
+        const int32_t i = k < nb ? list_body(up, k) : 0;
+        const bool on = k < nb && g.flag[i];
         int32_t r = 0;
         if (on) {
-            r = uf_find(parent, (int32_t)k);
-            lab[k] = r;
+            r = uf_find(g.parent, i);
+            g.lab[i] = r;
         }
-        wave_add_by_key(gsize, r, on);
+        const int32_t slot = wave_add_by_key(g.size, r, on);
+        if (on) g.slot[i] = slot;
     }
 }
 
-// Tile sums of (members of the groups whose root is in the tile, roots).
-__global__ __launch_bounds__(LT) void k_group_tiles(const int32_t *flag, const int32_t *lab,
-                                                    const int32_t *gsize, int64_t n, int64_t *tsum)
+// Slots of the groups in the member array and the lists of their roots, by one
+// atomic per block and list.
+__global__ __launch_bounds__(LT) void k_group_alloc(ListDev up, GroupDev g)
 {
     __shared__ int64_t sm[LT / 64];
-    const int64_t k = (int64_t)blockIdx.x * LT + threadIdx.x;
-    const bool root = k < n && flag[k] && lab[k] == k;
-    int64_t tm, tr;
-    block_excl_scan<LT>(root ? gsize[k] : 0, &tm, sm);
-    block_excl_scan<LT>(root ? 1 : 0, &tr, sm);
-    if (threadIdx.x == 0) {
-        tsum[2 * blockIdx.x] = tm;
-        tsum[2 * blockIdx.x + 1] = tr;
-    }
-}
-
-__global__ __launch_bounds__(ST) void k_group_top(int64_t *tsum, int64_t ntiles, int32_t *gcount,
-                                                  int32_t *big, unsigned long long *gsync)
-{
-    __shared__ int64_t sm[ST / 64];
-    const int t = threadIdx.x;
-    const int64_t ch = (ntiles + ST - 1) / ST;
-    const int64_t k0 = min(ntiles, t * ch), k1 = min(ntiles, k0 + ch);
-    int64_t sa = 0, sb = 0;
-    for (int64_t k = k0; k < k1; ++k) {
-        sa += tsum[2 * k];
-        sb += tsum[2 * k + 1];
-    }
-    int64_t ta, tb;
-    int64_t oa = block_excl_scan<ST>(sa, &ta, sm);
-    int64_t ob = block_excl_scan<ST>(sb, &tb, sm);
-    for (int64_t k = k0; k < k1; ++k) {
-        const int64_t a = tsum[2 * k], b = tsum[2 * k + 1];
-        tsum[2 * k] = oa;
-        tsum[2 * k + 1] = ob;
-        oa += a;
-        ob += b;
-    }
-    if (t == 0) {
-        gcount[0] = (int32_t)tb;   // groups
-        gcount[1] = (int32_t)ta;   // members
-        if (big) {
-            // the grid solver's list and barrier state, fresh for its launch:
-            // arrivals, abort flag, three maximum slots, three minimum slots
-            big[0] = 0;
-            for (int k = 0; k < 5; ++k) gsync[k] = 0;
-            for (int k = 5; k < 8; ++k) gsync[k] = (unsigned long long)LLONG_MAX;
-        }
-    }
-}
-
-__global__ __launch_bounds__(LT) void k_group_write(const int32_t *flag, const int32_t *lab,
-                                                    const int32_t *gsize, int64_t n,
-                                                    const int64_t *tsum, int32_t *gstart,
-                                                    int32_t *groot, int32_t *big)
-{
-    __shared__ int64_t sm[LT / 64];
-    const int64_t k = (int64_t)blockIdx.x * LT + threadIdx.x;
-    const bool root = k < n && flag[k] && lab[k] == k;
-    int64_t tm, tr;
-    const int64_t om = block_excl_scan<LT>(root ? gsize[k] : 0, &tm, sm);
-    const int64_t orr = block_excl_scan<LT>(root ? 1 : 0, &tr, sm);
-    if (root) {
-        gstart[k] = (int32_t)(tsum[2 * blockIdx.x] + om);
-        groot[tsum[2 * blockIdx.x + 1] + orr] = (int32_t)k;
-        // groups beyond one workgroup, for the grid solver (any order)
-        if (big && gsize[k] > GROUP_BLOCK) big[1 + atomicAdd(big, 1)] = (int32_t)k;
-    }
-}
-
-__global__ __launch_bounds__(LT) void k_group_fill(const int32_t *flag, const int32_t *lab,
-                                                   const int32_t *gstart, int32_t *gfill,
-                                                   int32_t *gtmp, int64_t n)
-{
-    for (int64_t k0 = (int64_t)blockIdx.x * LT; k0 < n; k0 += (int64_t)gridDim.x * LT) {
+    __shared__ int32_t base[3];
+    const int64_t nb = list_count(up);
+    for (int64_t k0 = (int64_t)blockIdx.x * LT; k0 < nb; k0 += (int64_t)gridDim.x * LT) {
         const int64_t k = k0 + threadIdx.x;
-        const bool on = k < n && flag[k];
-        const int32_t r = on ? lab[k] : 0;
-        const int32_t slot = wave_add_by_key(gfill, r, on);
-        if (on) gtmp[gstart[r] + slot] = (int32_t)k;
+        const int32_t i = k < nb ? list_body(up, k) : 0;
+        const bool root = k < nb && g.flag[i] && g.lab[i] == i;
+        const int32_t size = root ? g.size[i] : 0;
+        const bool small = root && size <= BS_GS, large = size > GROUP_BLOCK;
+        const bool medium = root && !small && !large;
+        // (members, medium, small) in one scan
+        int64_t tot;
+        const int64_t ex = block_excl_scan<LT>(
+            ((int64_t)size << 32) | (medium ? 1 << 16 : 0) | (small ? 1 : 0), &tot, sm);
+        if (threadIdx.x == 0 && tot) {
+            base[0] = atomicAdd(g.count, (int32_t)(tot & 0xffff));
+            base[1] = atomicAdd(g.count + 1, (int32_t)(tot >> 32));
+            base[2] = atomicAdd(g.count + 2, (int32_t)(tot >> 16 & 0xffff));
+        }
+        __syncthreads();
+        if (root) {
+            g.start[i] = base[1] + (int32_t)(ex >> 32);
+            if (small) g.root[base[0] + (int32_t)(ex & 0xffff)] = i;
+            if (medium) g.root[g.n - 1 - (base[2] + (int32_t)(ex >> 16 & 0xffff))] = i;
+            if (large) {
+                if (g.big) g.big[1 + atomicAdd(g.big, 1)] = i;
+            }
+        }
+        // statistics of the groups that are integrated (a maximum that is
+        // there already costs no atomic)
+        const bool taken = root && size <= g.limit;
+        if (taken && (unsigned long long)size > g.gstats[1])
+            atomicMax(g.gstats + 1, (unsigned long long)size);
+        const unsigned long long some = __ballot(taken);
+        if (some && (threadIdx.x & 63) == 0)
+            atomicAdd(g.gstats, (unsigned long long)__popcll(some));
+        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(LT) void k_group_rank(const int32_t *lab, const int32_t *gstart,
-                                                   const int32_t *gsize, const int32_t *gtmp,
-                                                   const int32_t *gcount, int32_t *gmem)
+// Per-body operators over a list's bodies.
+struct BodyDev {
+    const int32_t *bodies;
+    const int32_t *nbod;
+    double *x, *y, *z, *vx, *vy, *vz;
+    const double *m;
+    int32_t *status;
+};
+
+// What a level's pass does with its next list: nothing, its adjacency (a level
+// follows) or its groups (the direct solver follows).
+enum NextList { NEXT_NONE, NEXT_ADJ, NEXT_GROUPS };
+
+// Start of a level's sub-step over the bodies of the upper list: their critical
+// radii, and empty structures for the next list.
+template <int NEXT>
+__global__ __launch_bounds__(LT) void k_level_radii(BodyDev a, double *rc, double m_star, double dt,
+                                                    double n1, double n2, AdjDev A, GroupDev g)
 {
-    const int64_t total = gcount[1];
-    for (int64_t e = (int64_t)blockIdx.x * LT + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * LT) {
-        const int32_t k = gtmp[e], r = lab[k];
-        const int32_t s0 = gstart[r], g = gsize[r];
-        // the grid solver orders a large group's members itself (by cell,
-        // then body): its slots keep the arrival order, sparing the
-        // quadratic ranking
-        if (g > GROUP_BLOCK) {
-            gmem[e] = k;
-            continue;
+    const int64_t nb = *a.nbod;
+    const int64_t t0 = (int64_t)blockIdx.x * LT + threadIdx.x;
+    if (t0 == 0) {
+        if (NEXT == NEXT_ADJ) adj_begin(A);
+        if (NEXT == NEXT_GROUPS) group_begin_all(g);
+    }
+    for (int64_t q = t0; q < nb; q += (int64_t)gridDim.x * LT) {
+        const int32_t i = a.bodies[q];
+        const double r = __builtin_sqrt(a.x[i] * a.x[i] + a.y[i] * a.y[i] + a.z[i] * a.z[i]);
+        const double v =
+            __builtin_sqrt(a.vx[i] * a.vx[i] + a.vy[i] * a.vy[i] + a.vz[i] * a.vz[i]);
+        const double rh = r * cbrt(a.m[i] / (3.0 * m_star));
+        const double h1 = n1 * rh, h2 = n2 * fabs(dt) * v;
+        const double out = h1 > h2 ? h1 : h2;
+        if (!(out >= 0.0 && out < INFINITY)) atomicOr(a.status, ST_RCRIT);
+        rc[i] = out;
+        if (NEXT == NEXT_ADJ) A.deg[i] = 0;
+        if (NEXT == NEXT_GROUPS) group_begin(g, i);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Next level's list: the pairs of list `in` closer than this level's
+// critical radius, in the same order.  DB chunks of the input: counts (in the
+// launch of the level's kick, which leaves positions and radii as they are), then
+// ordered writes behind the counts of the chunks before.
+// ---------------------------------------------------------------------------
+struct DetectDev {
+    const int32_t *in_i, *in_j;
+    const int64_t *in_cnt;
+    int32_t *out_i, *out_j;
+    int64_t *out_cnt;
+    int64_t *lcount;          // summed sizes of this level's lists
+    int64_t cap;
+    const double *x, *y, *z, *rc;
+    int64_t *bcnt;            // [DB]
+};
+
+__device__ __forceinline__ bool detect_pair(const DetectDev &d, int32_t i, int32_t j)
+{
+    const double rho = rho_of(d.rc, i, j);
+    return sep2(d.x, d.y, d.z, i, j) < rho * rho;
+}
+
+__device__ __forceinline__ void chunk_of(const DetectDev &d, int64_t &p0, int64_t &p1)
+{
+    const int64_t m = list_len(d.in_cnt, d.cap);
+    const int64_t len = (m + DB - 1) / DB;
+    p0 = min(m, (int64_t)blockIdx.x * len);
+    p1 = min(m, p0 + len);
+}
+
+__device__ __forceinline__ void detect_count(const DetectDev &d)
+{
+    __shared__ int64_t sm[LT / 64];
+    int64_t p0, p1;
+    chunk_of(d, p0, p1);
+    int64_t c = 0;
+    for (int64_t p = p0 + threadIdx.x; p < p1; p += LT) c += detect_pair(d, d.in_i[p], d.in_j[p]);
+    int64_t tot;
+    block_excl_scan<LT>(c, &tot, sm);
+    if (threadIdx.x == 0) d.bcnt[blockIdx.x] = tot;
+}
+
+static_assert(DB == LT, "k_detect_write: a thread per chunk");
+
+template <int NEXT>
+__global__ __launch_bounds__(LT) void k_detect_write(DetectDev d, AdjDev A, GroupDev g)
+{
+    __shared__ int64_t sm[LT / 64];
+    __shared__ int64_t before;
+    int64_t p0, p1;
+    chunk_of(d, p0, p1);
+    int64_t all;
+    const int64_t mine = block_excl_scan<DB>(d.bcnt[threadIdx.x], &all, sm);
+    if (threadIdx.x == blockIdx.x) before = mine;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *d.out_cnt = all;
+        *d.lcount += all;
+    }
+    __syncthreads();
+    int64_t run = before;
+    for (int64_t t0 = p0; t0 < p1; t0 += LT) {
+        const int64_t p = t0 + threadIdx.x;
+        const int32_t i = p < p1 ? d.in_i[p] : 0, j = p < p1 ? d.in_j[p] : 0;
+        const bool f = p < p1 && detect_pair(d, i, j);
+        int64_t tot;
+        const int64_t ex = block_excl_scan<LT>(f ? 1 : 0, &tot, sm);
+        if (f) {
+            d.out_i[run + ex] = i;
+            d.out_j[run + ex] = j;
+            if (NEXT == NEXT_ADJ) adj_pair(A, i, j);
+            if (NEXT == NEXT_GROUPS) group_union(g, i, j);
         }
-        int32_t rank = 0;
-        for (int32_t q = s0; q < s0 + g; ++q) rank += gtmp[q] < k;
-        gmem[s0 + rank] = k;
+        run += tot;
+    }
+}
+
+// The drift of a level's bodies that no deeper list advances: the others start
+// their sub-steps or their group's integration from the state they have.  (A
+// group too large for every solver is drifted.)  Members go to their slots here.
+template <int NEXT>
+__global__ __launch_bounds__(LT) void k_drift_list(BodyDev a, double mu, double dt, AdjDev A,
+                                                   GroupDev g)
+{
+    const int64_t nb = *a.nbod;
+    for (int64_t q = (int64_t)blockIdx.x * LT + threadIdx.x; q < nb; q += (int64_t)gridDim.x * LT) {
+        const int32_t i = a.bodies[q];
+        if (NEXT == NEXT_ADJ && A.deg[i] > 0) continue;
+        if (NEXT == NEXT_GROUPS && g.flag[i]) {
+            const int32_t r = g.lab[i];
+            g.mem[g.start[r] + g.slot[i]] = i;
+            if (g.size[r] <= g.limit) continue;
+        }
+        double X = a.x[i], Y = a.y[i], Z = a.z[i], VX = a.vx[i], VY = a.vy[i], VZ = a.vz[i];
+        const int st = kepler_uv(mu, dt, X, Y, Z, VX, VY, VZ);
+        if (st) atomicOr(a.status, st);
+        a.x[i] = X; a.y[i] = Y; a.z[i] = Z;
+        a.vx[i] = VX; a.vy[i] = VY; a.vz[i] = VZ;
+    }
+}
+
+// Members to their slots, their state to `shadow` (the whole system drifts next).
+__global__ __launch_bounds__(LT) void k_group_place(BodyDev a, GroupDev g, double *shadow)
+{
+    const double *c[6] = {a.x, a.y, a.z, a.vx, a.vy, a.vz};
+    for (int64_t i = (int64_t)blockIdx.x * LT + threadIdx.x; i < g.n; i += (int64_t)gridDim.x * LT) {
+        if (!g.flag[i]) continue;
+        g.mem[g.start[g.lab[i]] + g.slot[i]] = (int32_t)i;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) shadow[(size_t)k * g.n + i] = c[k][i];
+    }
+}
+
+// save = 1: shadow <- state; save = 0: state <- shadow (bodies of the list).
+__global__ __launch_bounds__(LT) void k_state_list(BodyDev a, double *shadow, int64_t n, int save)
+{
+    const int64_t nb = *a.nbod;
+    double *c[6] = {a.x, a.y, a.z, a.vx, a.vy, a.vz};
+    for (int64_t q = (int64_t)blockIdx.x * LT + threadIdx.x; q < nb; q += (int64_t)gridDim.x * LT) {
+        const int32_t i = a.bodies[q];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            if (save) shadow[(size_t)k * n + i] = c[k][i];
+            else c[k][i] = shadow[(size_t)k * n + i];
+        }
+    }
+}
+
+// 1/x from v_rcp_f64 with a second-order correction (relative error a few
+// 2^-53); a chain half as long as the IEEE division.
+__device__ __forceinline__ double rcp_full(double x)
+{
+    const double t = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, t, 1.0);
+    return __builtin_fma(t, __builtin_fma(e, e, e), t);
+}
+
+// The changeover K(y) = y^2 / (2 y^2 - 2 y + 1) of y = (r / rho - 0.1) / 0.9 in
+// [0, 1], as num^2 / den: `up` takes y for a factor K and 1 - y for a factor
+// 1 - K, so that a product over levels needs one reciprocal.
+struct LevelWeight {
+    double num = 1.0, den = 1.0;
+    __device__ void add(double r, double irho, bool up)
+    {
+        double y = __builtin_fma(r * irho, 10.0 / 9.0, -1.0 / 9.0);
+        y = vmin_f64(vmax_f64(y, 0.0), 1.0);
+        num *= up ? y : 1.0 - y;
+        den *= __builtin_fma(2.0 * y, y - 1.0, 1.0);
+    }
+    __device__ double value() const { return (num * num) * rcp_full(den); }
+};
+
+// Kick of level l over a list: v_b += h G sum_j m_j W_l(r_bj) (x_j - x_b) / r^3
+// for every body b of the list.  A group of GL lanes takes one body: lane u
+// adds the partners u, u + GL, ... of the body's ascending partner list, and
+// the GL partial sums are combined by a fixed butterfly, so the result does
+// not depend on scheduling.  Bound by its dependent loads (body, segment,
+// partner, its state) and the chain of one pair, hence the corrected hardware
+// estimates, the level as a template argument (all radii in flight at once)
+// and one reciprocal for all levels.
+constexpr int GL = 8;
+constexpr int KB_DETECT = DB;   // blocks in front that count the next list
+
+struct LevelKickDev {
+    BodyDev a;
+    const int32_t *start, *deg, *adj;
+    const double *rc[GENGA_MAX_LEVELS];   // rc[0]: level 0 (the bodies' rc)
+    double G, h;
+};
+
+template <int LEVEL, bool DETECT>
+__global__ __launch_bounds__(LT) void k_level_kick(LevelKickDev k, DetectDev d)
+{
+    if (DETECT && blockIdx.x < KB_DETECT) {
+        detect_count(d);
+        return;
+    }
+    const unsigned bx = DETECT ? blockIdx.x - KB_DETECT : blockIdx.x;
+    const unsigned blocks = DETECT ? gridDim.x - KB_DETECT : gridDim.x;
+    const BodyDev &a = k.a;
+    const int64_t nb = *a.nbod;
+    const int u = threadIdx.x & (GL - 1);
+    const int64_t g0 = ((int64_t)bx * LT + threadIdx.x) / GL;
+    const int64_t gstride = (int64_t)blocks * (LT / GL);
+    // every lane of a group runs the same trip count (the body loop is
+    // uniform per group), so the butterfly below sees all GL lanes
+    for (int64_t q = g0; q < nb; q += gstride) {
+        const int32_t b = a.bodies[q];
+        const double xb = a.x[b], yb = a.y[b], zb = a.z[b];
+        double rb[LEVEL + 1];
+#pragma unroll
+        for (int l = 0; l <= LEVEL; ++l) rb[l] = k.rc[l][b];
+        double ax = 0.0, ay = 0.0, az = 0.0;
+        const int32_t e0 = k.start[b], e1 = e0 + k.deg[b];
+        for (int32_t e = e0 + u; e < e1; e += GL) {
+            const int32_t j = k.adj[e];
+            const double dx = a.x[j] - xb, dy = a.y[j] - yb, dz = a.z[j] - zb;
+            double rho[LEVEL + 1];
+#pragma unroll
+            for (int l = 0; l <= LEVEL; ++l) rho[l] = vmax_f64(rb[l], k.rc[l][j]);
+            const double mj = a.m[j];
+            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+            if (r2 == 0.0) {
+                atomicOr(a.status, ST_NONFINITE);
+                continue;
+            }
+            const double ir = rsq_full(r2), r = r2 * ir;
+            LevelWeight w;
+#pragma unroll
+            for (int l = 0; l <= LEVEL; ++l)
+                w.add(r, rho[l] > 0.0 ? rcp_full(rho[l]) : 1e300, l == LEVEL);
+            const double s = (k.G * mj) * w.value() * (ir * ir * ir);
+            ax = __builtin_fma(s, dx, ax);
+            ay = __builtin_fma(s, dy, ay);
+            az = __builtin_fma(s, dz, az);
+        }
+#pragma unroll
+        for (int o = GL / 2; o > 0; o >>= 1) {
+            ax += __shfl_xor(ax, o, GL);
+            ay += __shfl_xor(ay, o, GL);
+            az += __shfl_xor(az, o, GL);
+        }
+        if (u == 0) {
+            a.vx[b] += k.h * ax;
+            a.vy[b] += k.h * ay;
+            a.vz[b] += k.h * az;
+        }
     }
 }
 
@@ -628,7 +704,7 @@ constexpr int BS_TRIES = 4096;
 
 struct BsDev {
     const int32_t *groot, *gstart, *gsize, *gmem, *gcount;
-    const double *shadow;               // [6][n] state before the drift
+    const double *state[6];             // x, y, z, vx, vy, vz before the drift
     int64_t n;
     double *x, *y, *z, *vx, *vy, *vz;
     double *m;                          // written by mergers
@@ -636,7 +712,6 @@ struct BsDev {
     int nlev;
     double G, mu, H, eps;
     int32_t *status;
-    unsigned long long *gstats;         // groups, largest group
     // collisions (radius non-null): radii (written by mergers), contact
     // tolerance, records (survivor, absorbed, lost energy)
     double *radius;
@@ -647,43 +722,23 @@ struct BsDev {
     int64_t coll_cap;
 };
 
-// 1/sqrt(x) and 1/x from the hardware estimates (v_rsq_f64, v_rcp_f64) and two
-// Newton steps each: the serial chain of the group derivative is dominated
-// by latency, and these are several times shorter than the IEEE square root
-// and division; two steps take the estimates' 2^-24-level error below the
-// binary64 rounding level, far inside the Bulirsch-Stoer tolerance.
-__device__ __forceinline__ double rsq2(double x)
+// R = prod_l (1 - K(r; rho_l)) with irho_l = 1 / rho_l = min(1 / rc_i, 1 / rc_j).
+// The members' reciprocal critical radii are formed once per group (the radii
+// do not change during the integration) and read from LDS: level l of member i at
+// ia[l * sa], of member j at ib[l * sb].  NL: the number of levels (straight code:
+// the serial chain of the group derivative is dominated by latency), or 0.
+template <int NL>
+__device__ __forceinline__ double bs_remainder(double r, const double *ia, int sa,
+                                               const double *ib, int sb, int nlev)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    double e = __builtin_fma(-x, y * y, 1.0);
-    y = __builtin_fma(0.5 * y, e, y);
-    e = __builtin_fma(-x, y * y, 1.0);
-    return __builtin_fma(0.5 * y, e, y);
-}
-
-__device__ __forceinline__ double rcp2(double x)
-{
-    double t = __builtin_amdgcn_rcp(x);
-    t = __builtin_fma(t, __builtin_fma(-x, t, 1.0), t);
-    return __builtin_fma(t, __builtin_fma(-x, t, 1.0), t);
-}
-
-// R = prod_l (1 - K(r; rho_l)) with y_l = r / (0.9 rho_l) - 1/9, from
-// irho_l = 1 / rho_l = min(1 / rc_i, 1 / rc_j).  The members' reciprocal
-// critical radii are formed once per group (the radii do not change during
-// the integration) and read from LDS: level l of member i at ia[l * sa], of
-// member j at ib[l * sb].
-__device__ __forceinline__ double bs_remainder(double r, const double *ia, int sa, const double *ib,
-                                               int sb, int nlev)
-{
-    double R = 1.0;
-    for (int l = 0; l < nlev; ++l) {
-        const double xa = ia[l * sa], xb = ib[l * sb];
-        const double irho = xa < xb ? xa : xb;
-        const double yv = __builtin_fma(r * irho, 10.0 / 9.0, -1.0 / 9.0);
-        R *= 1.0 - changeover_of_y(yv);
+    LevelWeight w;
+    if constexpr (NL > 0) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) w.add(r, vmin_f64(ia[l * sa], ib[l * sb]), false);
+    } else {
+        for (int l = 0; l < nlev; ++l) w.add(r, vmin_f64(ia[l * sa], ib[l * sb]), false);
     }
-    return R;
+    return w.value();
 }
 
 __device__ __forceinline__ double wave_min_all(double v)
@@ -830,7 +885,7 @@ struct BsEntries {
 // `sub` names.  A partner wave whose box stays beyond the larger deepest-level
 // critical radius of the two waves from the own wave's box holds no partner
 // with R > 0 and is skipped.  All lanes of the wave pass here.
-template <int BT>
+template <int BT, int NL>
 __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const BsFrame &fr, int t,
                                          int g, int S, int sub, double rcd, double acc[3])
 {
@@ -852,8 +907,8 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const B
             const double dx = sm.px[q] - sm.px[i], dy = sm.py[q] - sm.py[i],
                          dz = sm.pz[q] - sm.pz[i];
             const double r2 = dx * dx + dy * dy + dz * dz;
-            const double ir = rsq2(r2);
-            const double R = bs_remainder(r2 * ir, &sm.irc[0][i], BT, &sm.irc[0][q], BT, a.nlev);
+            const double ir = rsq_full(r2);
+            const double R = bs_remainder<NL>(r2 * ir, &sm.irc[0][i], BT, &sm.irc[0][q], BT, a.nlev);
             const double s = a.G * sm.m[q] * R * (ir * ir * ir);
             fo[0][p] = s * dx;
             fo[1][p] = s * dy;
@@ -916,7 +971,7 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const B
 // at them: the star's pull plus the S shares' partner sums, added in share
 // order (the waves of a share hold copies of the same members; only share 0
 // writes).  The shares' sums pass through pv, which no evaluation uses.
-template <int BT>
+template <int BT, int NL>
 __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, const BsFrame &fr, int t,
                                          int g, int S, int sub, double rcd, const double z[6],
                                          double f[6])
@@ -943,11 +998,11 @@ __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, const B
     f[1] = z[4];
     f[2] = z[5];
     double p[3] = {0.0, 0.0, 0.0};
-    if (t - (int)(threadIdx.x & 63) < g) bs_accel<BT>(a, sm, fr, t, g, S, sub, rcd, p);
+    if (t - (int)(threadIdx.x & 63) < g) bs_accel<BT, NL>(a, sm, fr, t, g, S, sub, rcd, p);
     double k[3] = {0.0, 0.0, 0.0};
     if (mem) {
         const double r2s = z[0] * z[0] + z[1] * z[1] + z[2] * z[2];
-        const double irs = rsq2(r2s);
+        const double irs = rsq_full(r2s);
         const double ks = -a.mu * (irs * irs * irs);
         k[0] = ks * z[0];
         k[1] = ks * z[1];
@@ -993,7 +1048,7 @@ __device__ __forceinline__ double bs_block_max(BsSmem<BT> &sm, double v)
 // whole state of member q after publish(), its mass, radius and body index,
 // a group-wide minimum of an integer key, and updates of the own member's
 // mass and radius.
-template <int BT>
+template <int BT, int NL>
 struct BlockPol {
     BsSmem<BT> &sm;
     int t, g;
@@ -1002,7 +1057,7 @@ struct BlockPol {
     BsFrame fr;   // the group's plane (bs_cell)
     __device__ void deriv(const BsDev &a, const double z[6], double f[6])
     {
-        bs_deriv<BT>(a, sm, fr, t, g, S, sub, rcd, z, f);
+        bs_deriv<BT, NL>(a, sm, fr, t, g, S, sub, rcd, z, f);
     }
     __device__ double gmax(double v) { return bs_block_max<BT>(sm, v); }
     __device__ bool member() const { return t < g; }
@@ -1057,13 +1112,14 @@ struct BlockPol {
     }
 };
 
-template <int GS>
+template <int GS, int NL>
 struct LanePol {
     int u, g;
     double m, R;
     int32_t bidx;
     double zc[6];
-    const double *irc;   // 1 / rc of each level: LDS, level l at irc[l * LT]; lane q at + q - u
+    const double *irc;   // 1 / rc of each level: LDS, level l at irc[l * stride]; lane q at + q - u
+    static constexpr int stride = GROUP_BLOCK;
     __device__ bool member() const { return u < g; }
     __device__ bool owner() const { return true; }
     __device__ int self() const { return u; }
@@ -1096,31 +1152,26 @@ struct LanePol {
         }
         return v;
     }
-    // every lane of the group runs the same partner loop (the shuffles need
-    // all GS lanes); only members add terms
+    // lane u takes the partners u + 1, u + 2, ... around the group, so that every
+    // member works on each pass of the loop (a group of two: one pass); the
+    // lanes beyond the group compute values that nothing reads
     __device__ void deriv(const BsDev &a, const double z[6], double f[6])
     {
         f[0] = z[3];
         f[1] = z[4];
         f[2] = z[5];
-        double acc[3] = {0.0, 0.0, 0.0};
-        const bool mem = u < g;
-        if (mem) {
-            const double r2s = z[0] * z[0] + z[1] * z[1] + z[2] * z[2];
-            const double irs = rsq2(r2s);
-            const double ks = -a.mu * (irs * irs * irs);
-            acc[0] = ks * z[0];
-            acc[1] = ks * z[1];
-            acc[2] = ks * z[2];
-        }
-        for (int q = 0; q < g; ++q) {
+        const double irs = rsq_full(z[0] * z[0] + z[1] * z[1] + z[2] * z[2]);
+        const double ks = -a.mu * (irs * irs * irs);
+        double acc[3] = {ks * z[0], ks * z[1], ks * z[2]};
+        for (int k = 1; k < g; ++k) {
+            int q = u + k;
+            q = q >= g ? q - g : q;
             const double xq = __shfl(z[0], q, GS), yq = __shfl(z[1], q, GS),
                          zq = __shfl(z[2], q, GS), mq = __shfl(m, q, GS);
-            if (!mem || q == u) continue;
             const double dx = xq - z[0], dy = yq - z[1], dz = zq - z[2];
             const double r2 = dx * dx + dy * dy + dz * dz;
-            const double ir = rsq2(r2);
-            const double R = bs_remainder(r2 * ir, irc, LT, irc + (q - u), LT, a.nlev);
+            const double ir = rsq_full(r2);
+            const double R = bs_remainder<NL>(r2 * ir, irc, stride, irc + (q - u), stride, a.nlev);
             const double s = a.G * mq * R * (ir * ir * ir);
             acc[0] += s * dx;
             acc[1] += s * dy;
@@ -1249,8 +1300,8 @@ __device__ long long bs_overlap(const BsDev &a, Pol &P, const double z[6])
 }
 
 // (positions and radii only, the share's own partners)
-template <int BT>
-__device__ long long BlockPol<BT>::overlap(const BsDev &a, const double z[6])
+template <int BT, int NL>
+__device__ long long BlockPol<BT, NL>::overlap(const BsDev &a, const double z[6])
 {
     publish(z);
     long long key = NO_PAIR;
@@ -1268,8 +1319,8 @@ __device__ long long BlockPol<BT>::overlap(const BsDev &a, const double z[6])
     return gmin(key);
 }
 
-template <int GS>
-__device__ long long LanePol<GS>::overlap(const BsDev &a, const double z[6])
+template <int GS, int NL>
+__device__ long long LanePol<GS, NL>::overlap(const BsDev &a, const double z[6])
 {
     return bs_overlap(a, *this, z);
 }
@@ -1395,40 +1446,42 @@ __device__ __forceinline__ void bs_store(const BsDev &a, int32_t b, const double
     a.vz[b] = y[5];
 }
 
-// Groups of at most GS bodies, GS lanes each (the many small groups).
-constexpr int BS_GS = 8;
-
-template <int GS>
-__global__ __launch_bounds__(LT) void k_bs_lanes(BsDev a)
+// Groups of at most GS bodies, GS lanes each (the many small groups): wave `w`
+// of block `blk` of `blocks`, the groups eight at a time, first over the blocks.
+template <int GS, int NL>
+__device__ __forceinline__ void bs_lanes(const BsDev &a, double (*irc)[GROUP_BLOCK], int blk, int blocks)
 {
-    __shared__ double irc_sm[GENGA_MAX_LEVELS][LT];
-    const int u = threadIdx.x % GS;
+    const int lane = threadIdx.x & 63, u = lane % GS;
     const int64_t ng = a.gcount[0];
-    const int64_t stride = (int64_t)gridDim.x * (LT / GS);
-    for (int64_t gi = ((int64_t)blockIdx.x * LT + threadIdx.x) / GS; gi < ng; gi += stride) {
+    const int64_t wave = (int64_t)(threadIdx.x >> 6) * blocks + blk;
+    const int64_t stride = (int64_t)blocks * (GROUP_BLOCK / 64) * (64 / GS);
+    for (int64_t gi = wave * (64 / GS) + lane / GS; gi < ng; gi += stride) {
         const int32_t root = a.groot[gi];
         const int g = a.gsize[root];
-        if (g > GS) continue;                        // a workgroup class's group
-        if (u == 0) {
-            atomicAdd(a.gstats, 1ull);
-            atomicMax(a.gstats + 1, (unsigned long long)g);
-        }
-        LanePol<GS> P;
+        LanePol<GS, NL> P;
         P.u = u;
         P.g = g;
         P.m = 0.0;
         P.R = 0.0;
         for (int c = 0; c < 6; ++c) P.zc[c] = 0.0;
-        P.irc = &irc_sm[0][threadIdx.x];
-        const int32_t b = u < g ? a.gmem[a.gstart[root] + u] : 0;
+        P.irc = &irc[0][threadIdx.x];
+        // members in ascending order: each to the lane of its rank
+        int32_t b = u < g ? a.gmem[a.gstart[root] + u] : INT_MAX;
+        int rank = 0;
+#pragma unroll
+        for (int q = 0; q < GS; ++q) {
+            const int32_t o = __shfl(b, q, GS);
+            rank += o < b || (o == b && q < u);
+        }
+        b = __builtin_amdgcn_ds_permute((lane - u + rank) * 4, b);
         P.bidx = b;
         double y[6] = {0, 0, 0, 0, 0, 0};
         if (u < g) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) y[c] = a.shadow[(size_t)c * a.n + b];
+            for (int c = 0; c < 6; ++c) y[c] = a.state[c][b];
             P.m = a.m[b];
             P.R = a.radius ? a.radius[b] : 0.0;
-            for (int l = 0; l < a.nlev; ++l) irc_sm[l][threadIdx.x] = rcp2(a.rc[l][b]);
+            for (int l = 0; l < a.nlev; ++l) irc[l][threadIdx.x] = rcp_full(a.rc[l][b]);
         }
         const bool failed = bs_run(a, P, y);
         if (failed && u == 0) atomicOr(a.status, ST_NOCONV);
@@ -1442,46 +1495,49 @@ __global__ __launch_bounds__(LT) void k_bs_lanes(BsDev a)
     }
 }
 
-// Groups of lo < size <= BT, one workgroup each (larger ones are the grid
-// solver's).  A group of fewer members than threads spreads each member over
-// S waves (S = BT / 64 over the member waves, a power of two): the waves of
-// member wave I are I * S ... I * S + S - 1, each taking one share of the
-// partners, and the first of them (the owner) alone writes.
-template <int BT>
-__global__ __launch_bounds__(BT) void k_bs(BsDev a, int lo)
+// Groups of more than BS_GS and at most GROUP_BLOCK bodies, one workgroup each
+// (larger ones are the grid solver's).  A group of fewer members than threads
+// spreads each member over S waves (S = GROUP_BLOCK / 64 over the member waves, a
+// power of two): the waves of member wave I are I * S ... I * S + S - 1, each
+// taking one share of the partners, and the first of them (the owner) alone
+// writes.
+template <int NL>
+__device__ __forceinline__ void bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &sm, int blk, int blocks)
 {
-    __shared__ BsSmem<BT> sm;
     // (the wave index is uniform: the partner loops then run on scalar registers)
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int ng = a.gcount[0];
-    for (int gi = blockIdx.x; gi < ng; gi += gridDim.x) {
-        const int32_t root = a.groot[gi];
+    const int ng = a.gcount[2];
+    for (int gi = blk; gi < ng; gi += blocks) {
+        const int32_t root = a.groot[a.n - 1 - gi];
         const int g = a.gsize[root];
-        if (g <= lo || g > BT) continue;             // another class's group
-        if (threadIdx.x == 0) {
-            atomicAdd(a.gstats, 1ull);
-            atomicMax(a.gstats + 1, (unsigned long long)g);
-        }
         const int nw = (g + 63) >> 6;
         int S = 1;
-        while (nw * S * 2 <= BT / 64) S *= 2;
+        while (nw * S * 2 <= GROUP_BLOCK / 64) S *= 2;
         const int t = (w / S) * 64 + lane, sub = w % S;
-        BlockPol<BT> P{sm, t, g, S, sub, 0.0, {}};
-        const int32_t b = t < g ? a.gmem[a.gstart[root] + t] : 0;
+        BlockPol<GROUP_BLOCK, NL> P{sm, t, g, S, sub, 0.0, {}};
+        // the member of rank t
+        const int32_t start = a.gstart[root];
+        if (P.owner()) sm.idx[t] = a.gmem[start + t];
+        __syncthreads();
+        int32_t b = t < g ? sm.idx[t] : 0, rank = 0;
+        for (int q = 0; q < g; ++q) rank += sm.idx[q] < b;
+        __syncthreads();
+        if (P.owner()) sm.idx[rank] = b;
+        __syncthreads();
+        b = t < g ? sm.idx[t] : 0;
         double y[6] = {0, 0, 0, 0, 0, 0};
         double rcd = 0.0;
         if (t < g) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) y[c] = a.shadow[(size_t)c * a.n + b];
+            for (int c = 0; c < 6; ++c) y[c] = a.state[c][b];
             rcd = a.rc[a.nlev - 1][b];
         }
         P.rcd = rcd;
         if (P.owner()) {
             sm.m[t] = a.m[b];
             sm.R[t] = a.radius ? a.radius[b] : 0.0;
-            sm.idx[t] = b;
             for (int l = 0; l < a.nlev; ++l)
-                sm.irc[l][t] = rcp2(a.rc[l][b]);
+                sm.irc[l][t] = rcp_full(a.rc[l][b]);
         }
         {
             const double tr = wave_max_all(rcd);
@@ -1513,6 +1569,27 @@ __global__ __launch_bounds__(BT) void k_bs(BsDev a, int lo)
         }
         __syncthreads();   // LDS reuse by the next group
     }
+}
+
+// Both classes in one launch, so that the small groups run beside the medium
+// ones and an empty class costs no launch: blocks [0, BS_MEDIUM) the medium groups (a
+// compute unit holds one of them), the blocks behind them the small ones.
+constexpr int BS_MEDIUM = 256, BS_SMALL = 256;
+
+union BsLds {
+    BsSmem<GROUP_BLOCK> medium;
+    double irc[GENGA_MAX_LEVELS][GROUP_BLOCK];
+    __device__ BsLds() {}
+};
+
+template <int NL>
+__global__ __launch_bounds__(GROUP_BLOCK) void k_bs(BsDev a)
+{
+    __shared__ BsLds sm;
+    if (blockIdx.x < BS_MEDIUM)
+        bs_medium<NL>(a, sm.medium, (int)blockIdx.x, BS_MEDIUM);
+    else
+        bs_lanes<BS_GS, NL>(a, sm.irc, (int)blockIdx.x - BS_MEDIUM, BS_SMALL);
 }
 
 // ---------------------------------------------------------------------------
@@ -1807,8 +1884,8 @@ struct GridPol {
                         const double dx = S.sx[w][q] - x0, dy = S.sy[w][q] - y0,
                                      dz = S.sz[w][q] - z0;
                         const double r2 = dx * dx + dy * dy + dz * dz;
-                        const double ir = rsq2(r2);
-                        const double Rw = bs_remainder(r2 * ir, &S.oirc[0][threadIdx.x], GT,
+                        const double ir = rsq_full(r2);
+                        const double Rw = bs_remainder<0>(r2 * ir, &S.oirc[0][threadIdx.x], GT,
                                                        &S.sirc[w][0][q], 64, nl);
                         const double s = Gc * S.sm[w][q] * Rw * (ir * ir * ir);
                         ax += s * dx;
@@ -1823,7 +1900,7 @@ struct GridPol {
         double kx = 0.0, ky = 0.0, kz = 0.0;
         if (member()) {
             const double r2s = x0 * x0 + y0 * y0 + z0 * z0;
-            const double irs = rsq2(r2s);
+            const double irs = rsq_full(r2s);
             const double ks = -a.mu * (irs * irs * irs);
             kx = ks * x0;
             ky = ks * y0;
@@ -1957,8 +2034,8 @@ __device__ void grid_order(const BsDev &a, GridPol &P, int32_t root, int32_t *pe
     const int32_t b = own ? a.gmem[a.gstart[root] + t] : 0;
     double x = 0.0, y = 0.0;
     if (own) {
-        x = a.shadow[b];
-        y = a.shadow[(size_t)a.n + b];
+        x = a.state[0][b];
+        y = a.state[1][b];
     }
     for (int c = tid; c < GCELL * GCELL; c += nthr) {
         G.ccnt[c] = 0;
@@ -2084,10 +2161,6 @@ __global__ __launch_bounds__(GT, 2) void k_bs_grid(BsDev a, GridDev G)
         P.split = split;
         P.sub = gw % split;
         P.t = gw / split * 64 + lane;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            atomicAdd(a.gstats, 1ull);
-            atomicMax(a.gstats + 1, (unsigned long long)g);
-        }
         grid_order(a, P, root, perm);
         const int t = P.t;
         const bool mem = t < g;
@@ -2098,12 +2171,12 @@ __global__ __launch_bounds__(GT, 2) void k_bs_grid(BsDev a, GridDev G)
         P.rcd = 0.0;
         if (mem) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) y[c] = a.shadow[(size_t)c * a.n + b];
+            for (int c = 0; c < 6; ++c) y[c] = a.state[c][b];
             P.m = a.m[b];
             P.R = a.radius ? a.radius[b] : 0.0;
             P.rcd = a.rc[a.nlev - 1][b];
             for (int l = 0; l < a.nlev; ++l) {
-                const double ir = rcp2(a.rc[l][b]);
+                const double ir = rcp_full(a.rc[l][b]);
                 S.oirc[l][threadIdx.x] = ir;
                 if (P.owner()) G.mirc[(size_t)l * G.cap + t] = ir;
             }
@@ -2143,6 +2216,11 @@ struct LevelRun {
     template <typename T>
     T *at(size_t off) const { return (T *)(ws + off); }
     int32_t *status() const { return (int32_t *)ws; }
+    unsigned list_blocks() const
+    {
+        return (unsigned)std::min<int64_t>(LG, (b->n + LT - 1) / LT);
+    }
+    ListDev all() const { return {nullptr, nullptr, b->n}; }
     BodyDev bodies_of(int l) const
     {
         BodyDev a;
@@ -2156,78 +2234,61 @@ struct LevelRun {
     }
 };
 
-static hipError_t build_adj(const LevelRun &R, int l)
+static AdjDev adj_of(const LevelRun &R, int l)
 {
     const LevelLayout &V = *R.V;
-    int32_t *pi = R.at<int32_t>(V.pi[l]), *pj = R.at<int32_t>(V.pj[l]);
+    AdjDev A{};
+    if (l >= V.L - 1) return A;
+    A.deg = R.at<int32_t>(V.deg[l]);
+    A.start = R.at<int32_t>(V.start[l]);
+    A.bodies = R.at<int32_t>(V.bodies[l]);
+    A.nbod = R.at<int32_t>(V.nbod) + l;
+    A.n = R.b->n;
+    return A;
+}
+
+// Adjacency of list l, whose degrees are counted; its bodies are among `up`.
+static hipError_t build_adj(const LevelRun &R, int l, const ListDev &up)
+{
+    const LevelLayout &V = *R.V;
+    const AdjDev A = adj_of(R, l);
+    const int32_t *pi = R.at<int32_t>(V.pi[l]), *pj = R.at<int32_t>(V.pj[l]);
     const int64_t *cnt = R.at<int64_t>(V.cnt) + l;
-    int32_t *deg = R.at<int32_t>(V.deg[l]), *start = R.at<int32_t>(V.start[l]);
-    int32_t *adj = R.at<int32_t>(V.adj[l]), *bod = R.at<int32_t>(V.bodies[l]);
     int32_t *tmp = R.at<int32_t>(V.adj_tmp[l]), *owner = R.at<int32_t>(V.owner[l]);
-    int64_t *tsum = R.at<int64_t>(V.tsum);
-    const int64_t n = R.b->n;
-    const unsigned nt = (unsigned)((n + LT - 1) / LT);
-    hipLaunchKernelGGL(k_zero_i32, dim3(LG), dim3(LT), 0, R.s, deg, n);
-    hipLaunchKernelGGL(k_adj_count, dim3(LG), dim3(LT), 0, R.s, pi, pj, cnt, V.cap, deg);
-    hipLaunchKernelGGL(k_adj_tiles, dim3(nt), dim3(LT), 0, R.s, deg, n, tsum);
-    hipLaunchKernelGGL(k_adj_top, dim3(1), dim3(ST), 0, R.s, tsum, (int64_t)nt, start, n,
-                       R.at<int32_t>(V.nbod) + l);
-    hipLaunchKernelGGL(k_adj_write, dim3(nt), dim3(LT), 0, R.s, deg, n, tsum, start, bod);
-    hipLaunchKernelGGL(k_adj_fill, dim3(LG), dim3(LT), 0, R.s, pi, pj, cnt, V.cap, start, deg, tmp,
-                       owner);
-    hipLaunchKernelGGL(k_adj_rank, dim3(LG), dim3(LT), 0, R.s, start, n, tmp, owner, adj);
+    hipLaunchKernelGGL(k_adj_alloc, dim3(R.list_blocks()), dim3(LT), 0, R.s, up, A);
+    hipLaunchKernelGGL(k_adj_fill, dim3(LG), dim3(LT), 0, R.s, pi, pj, cnt, V.cap, A, tmp, owner);
+    hipLaunchKernelGGL(k_adj_rank, dim3(LG), dim3(LT), 0, R.s, A, tmp, owner,
+                       R.at<int32_t>(V.adj[l]));
     return hipGetLastError();
 }
 
-static hipError_t level_kick(const LevelRun &R, int l, double h)
+template <int LEVEL>
+static void launch_level_kick(const LevelKickDev &k, int l, const DetectDev *d, hipStream_t s)
+{
+    if constexpr (LEVEL < GENGA_MAX_LEVELS - 1) {
+        if (l != LEVEL) return launch_level_kick<LEVEL + 1>(k, l, d, s);
+    }
+    if (d)
+        hipLaunchKernelGGL((k_level_kick<LEVEL, true>), dim3(KB_DETECT + LG), dim3(LT), 0, s, k, *d);
+    else
+        hipLaunchKernelGGL((k_level_kick<LEVEL, false>), dim3(LG), dim3(LT), 0, s, k, DetectDev{});
+}
+
+// The kick of level l, 1 <= l < GENGA_MAX_LEVELS (d: and the count of its next list).
+static hipError_t level_kick(const LevelRun &R, int l, double h, const DetectDev *d)
 {
     const LevelLayout &V = *R.V;
     LevelKickDev k;
     k.a = R.bodies_of(l - 1);
     k.start = R.at<int32_t>(V.start[l - 1]);
+    k.deg = R.at<int32_t>(V.deg[l - 1]);
     k.adj = R.at<int32_t>(V.adj[l - 1]);
     for (int q = 0; q < GENGA_MAX_LEVELS; ++q) k.rc[q] = nullptr;
     k.rc[0] = R.b->rc;
     for (int q = 1; q <= l; ++q) k.rc[q] = R.at<double>(V.rc[q]);
-    k.level = l;
     k.G = R.p->G;
     k.h = h;
-    hipLaunchKernelGGL(k_level_kick, dim3(LG), dim3(LT), 0, R.s, k);
-    return hipGetLastError();
-}
-
-// Groups of list l and their members' state saved into shadow[l].
-static hipError_t group_and_save(const LevelRun &R, int l)
-{
-    const LevelLayout &V = *R.V;
-    const int64_t n = R.b->n;
-    const unsigned nt = (unsigned)((n + LT - 1) / LT);
-    int32_t *lab = R.at<int32_t>(V.glab), *flag = R.at<int32_t>(V.gflag);
-    int32_t *gsize = R.at<int32_t>(V.gsize), *gfill = R.at<int32_t>(V.gfill);
-    int32_t *gstart = R.at<int32_t>(V.gstart), *groot = R.at<int32_t>(V.groot);
-    int32_t *gtmp = R.at<int32_t>(V.gtmp), *gmem = R.at<int32_t>(V.gmem);
-    int32_t *gcount = R.at<int32_t>(V.gcount);
-    int64_t *tsum = R.at<int64_t>(V.gtsum);
-    const int32_t *pi = R.at<int32_t>(V.pi[l]), *pj = R.at<int32_t>(V.pj[l]);
-    const int64_t *cnt = R.at<int64_t>(V.cnt) + l;
-    // the union-find's parents live in gtmp until the roots are known
-    hipLaunchKernelGGL(k_group_init, dim3(LG), dim3(LT), 0, R.s, gtmp, flag, gsize, gfill, n);
-    hipLaunchKernelGGL(k_group_union, dim3(LG), dim3(LT), 0, R.s, pi, pj, cnt, V.cap, gtmp, flag);
-    hipLaunchKernelGGL(k_group_root, dim3(LG), dim3(LT), 0, R.s, gtmp, flag, lab, gsize, n);
-    hipLaunchKernelGGL(k_group_tiles, dim3(nt), dim3(LT), 0, R.s, flag, lab, gsize, n, tsum);
-    int32_t *big = V.gbig ? R.at<int32_t>(V.gbig) : nullptr;
-    unsigned long long *gsync = V.gbig ? R.at<unsigned long long>(V.gsync) : nullptr;
-    hipLaunchKernelGGL(k_group_top, dim3(1), dim3(ST), 0, R.s, tsum, (int64_t)nt, gcount, big, gsync);
-    hipLaunchKernelGGL(k_group_write, dim3(nt), dim3(LT), 0, R.s, flag, lab, gsize, n, tsum, gstart,
-                       groot, big);
-    hipLaunchKernelGGL(k_group_fill, dim3(LG), dim3(LT), 0, R.s, flag, lab, gstart, gfill, gtmp, n);
-    hipLaunchKernelGGL(k_group_rank, dim3(LG), dim3(LT), 0, R.s, lab, gstart, gsize, gtmp, gcount,
-                       gmem);
-    BodyDev mem = R.bodies_of(0);
-    mem.bodies = gmem;
-    mem.nbod = gcount + 1;
-    hipLaunchKernelGGL(k_state_list, dim3(LG), dim3(LT), 0, R.s, mem, R.at<double>(V.shadow[l]), n,
-                       1);
+    launch_level_kick<1>(k, l, d, R.s);
     return hipGetLastError();
 }
 
@@ -2257,8 +2318,59 @@ static hipError_t grid_resident_blocks(int *out)
     return hipSuccess;
 }
 
-// The groups of list l over dt_l from the saved state, weights of levels 0..l.
-static hipError_t direct_solve(const LevelRun &R, int l, double dt_l)
+// Workgroups of the grid solver's launch (as many as fit the capacity and are
+// resident on the device together: the barriers need them all) and the members
+// of the largest group it takes.
+static hipError_t grid_size(const LevelLayout &V, int *nb, int32_t *cap)
+{
+    int resident = 0;
+    const hipError_t e = grid_resident_blocks(&resident);
+    if (e != hipSuccess) return e;
+    *nb = (int)std::min<int64_t>(V.gcap / 64, resident);
+    *cap = (int32_t)std::min<int64_t>(V.gcap, (int64_t)*nb * GT);
+    return hipSuccess;
+}
+
+static hipError_t groups_of(const LevelRun &R, GroupDev *out)
+{
+    const LevelLayout &V = *R.V;
+    GroupDev g{};
+    if (V.direct) {
+        g.parent = R.at<int32_t>(V.gtmp);
+        g.flag = R.at<int32_t>(V.gflag);
+        g.lab = R.at<int32_t>(V.glab);
+        g.size = R.at<int32_t>(V.gsize);
+        g.slot = R.at<int32_t>(V.gslot);
+        g.start = R.at<int32_t>(V.gstart);
+        g.mem = R.at<int32_t>(V.gmem);
+        g.root = R.at<int32_t>(V.groot);
+        g.count = R.at<int32_t>(V.gcount);
+        g.big = V.gbig ? R.at<int32_t>(V.gbig) : nullptr;
+        g.gsync = V.gbig ? R.at<unsigned long long>(V.gsync) : nullptr;
+        g.gstats = R.at<unsigned long long>(V.gstats);
+        g.limit = GROUP_BLOCK;
+        g.n = R.b->n;
+        if (V.gbig) {
+            int nb = 0;
+            const hipError_t e = grid_size(V, &nb, &g.limit);
+            if (e != hipSuccess) return e;
+        }
+    }
+    *out = g;
+    return hipSuccess;
+}
+
+// Roots, sizes and slots of the groups whose pairs are joined; their members
+// are among `up`.
+static void build_groups(const LevelRun &R, const ListDev &up, const GroupDev &g)
+{
+    const dim3 nb(R.list_blocks());
+    hipLaunchKernelGGL(k_group_root, nb, dim3(LT), 0, R.s, up, g);
+    hipLaunchKernelGGL(k_group_alloc, nb, dim3(LT), 0, R.s, up, g);
+}
+
+// The groups of list l over dt_l from `state`, weights of levels 0..l.
+static hipError_t direct_solve(const LevelRun &R, int l, double dt_l, const double *const *state)
 {
     const LevelLayout &V = *R.V;
     BsDev a;
@@ -2267,7 +2379,7 @@ static hipError_t direct_solve(const LevelRun &R, int l, double dt_l)
     a.gsize = R.at<int32_t>(V.gsize);
     a.gmem = R.at<int32_t>(V.gmem);
     a.gcount = R.at<int32_t>(V.gcount);
-    a.shadow = R.at<double>(V.shadow[l]);
+    for (int c = 0; c < 6; ++c) a.state[c] = state[c];
     a.n = R.b->n;
     a.x = R.b->x; a.y = R.b->y; a.z = R.b->z;
     a.vx = R.b->vx; a.vy = R.b->vy; a.vz = R.b->vz;
@@ -2281,7 +2393,6 @@ static hipError_t direct_solve(const LevelRun &R, int l, double dt_l)
     a.H = dt_l;
     a.eps = R.p->bs_eps > 0.0 ? R.p->bs_eps : 1e-12;
     a.status = R.status();
-    a.gstats = R.at<unsigned long long>(V.gstats);
     a.radius = R.b->R;
     a.coll_tol = R.p->coll_tol > 0.0 ? R.p->coll_tol : 1e-6;
     a.coll_i = R.at<int32_t>(V.coll_i);
@@ -2289,20 +2400,14 @@ static hipError_t direct_solve(const LevelRun &R, int l, double dt_l)
     a.coll_du = R.at<double>(V.coll_du);
     a.coll_count = R.at<unsigned long long>(V.coll_count);
     a.coll_cap = LEVEL_COLL_CAP;
-    hipLaunchKernelGGL(k_bs_lanes<BS_GS>, dim3(LG), dim3(LT), 0, R.s, a);
-    // groups of more than 8 bodies are rare at the deepest level: one
-    // launch of 512-thread workgroups takes all of them (an empty launch per
-    // class cost ~4.5 us per deepest sub-step)
-    hipLaunchKernelGGL(k_bs<GROUP_BLOCK>, dim3(LG_BIG), dim3(GROUP_BLOCK), 0, R.s, a, BS_GS);
+    auto *bs = a.nlev == 1 ? k_bs<1> : a.nlev == 2 ? k_bs<2> : a.nlev == 3 ? k_bs<3> : k_bs<0>;
+    hipLaunchKernelGGL(bs, dim3(BS_MEDIUM + BS_SMALL), dim3(GROUP_BLOCK), 0, R.s, a);
     if (!V.gbig) return hipGetLastError();
-    // groups beyond one workgroup: as many workgroups as fit the capacity
-    // and are resident on the device together (the barriers need them all)
-    int resident = 0;
-    hipError_t e = grid_resident_blocks(&resident);
-    if (e != hipSuccess) return e;
-    const int nb = (int)std::min<int64_t>(V.gcap / 64, resident);
+    // groups beyond one workgroup
+    int nb = 0;
     GridDev G;
-    G.cap = (int32_t)std::min<int64_t>(V.gcap, (int64_t)nb * GT);
+    const hipError_t e = grid_size(V, &nb, &G.cap);
+    if (e != hipSuccess) return e;
     G.big = R.at<int32_t>(V.gbig);
     G.pub = R.at<double>(V.gpub);
     G.box = R.at<double>(V.gbox);
@@ -2322,54 +2427,59 @@ static hipError_t direct_solve(const LevelRun &R, int l, double dt_l)
     return hipGetLastError();
 }
 
+template <int NEXT>
+static hipError_t sub_step(const LevelRun &R, int l, double dt_l, const AdjDev &A, const GroupDev &g);
+
 // Level l >= 1 over list l - 1, sub-steps of dt_l.
 static hipError_t advance(const LevelRun &R, int l, double dt_l)
 {
     const LevelLayout &V = *R.V;
-    const genga_params *p = R.p;
-    const int64_t n = R.b->n;
-    const bool deeper = l < V.L - 1;
-    const bool direct = V.direct && l == V.L - 1;
-    hipError_t e;
-    for (int sub = 0; sub < p->substeps; ++sub) {
-        BodyDev up = R.bodies_of(l - 1);
-        hipLaunchKernelGGL(k_rcrit_list, dim3(LG), dim3(LT), 0, R.s, up, R.at<double>(V.rc[l]),
-                           p->m_star, dt_l, p->n1, p->n2);
-        DetectDev d;
-        d.in_i = R.at<int32_t>(V.pi[l - 1]);
-        d.in_j = R.at<int32_t>(V.pj[l - 1]);
-        d.in_cnt = R.at<int64_t>(V.cnt) + (l - 1);
-        d.out_i = R.at<int32_t>(V.pi[l]);
-        d.out_j = R.at<int32_t>(V.pj[l]);
-        d.out_cnt = R.at<int64_t>(V.cnt) + l;
-        d.lcount = R.at<int64_t>(V.lcount) + l;
-        d.cap = V.cap;
-        d.x = R.b->x; d.y = R.b->y; d.z = R.b->z;
-        d.rc = R.at<double>(V.rc[l]);
-        d.bcnt = R.at<int64_t>(V.bcnt);
-        hipLaunchKernelGGL(k_detect_count, dim3(DB), dim3(LT), 0, R.s, d);
-        hipLaunchKernelGGL(k_detect_scan, dim3(1), dim3(DB), 0, R.s, d);
-        hipLaunchKernelGGL(k_detect_write, dim3(DB), dim3(LT), 0, R.s, d);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = level_kick(R, l, 0.5 * dt_l)) != hipSuccess) return e;
-        if (deeper) {
-            if ((e = build_adj(R, l)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k_state_list, dim3(LG), dim3(LT), 0, R.s, R.bodies_of(l),
-                               R.at<double>(V.shadow[l]), n, 1);
-        }
-        if (direct && (e = group_and_save(R, l)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_drift_list, dim3(LG), dim3(LT), 0, R.s, up, p->G * p->m_star, dt_l);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (deeper) {
-            hipLaunchKernelGGL(k_state_list, dim3(LG), dim3(LT), 0, R.s, R.bodies_of(l),
-                               R.at<double>(V.shadow[l]), n, 0);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            if ((e = advance(R, l + 1, dt_l / p->substeps)) != hipSuccess) return e;
-        }
-        if (direct && (e = direct_solve(R, l, dt_l)) != hipSuccess) return e;
-        if ((e = level_kick(R, l, 0.5 * dt_l)) != hipSuccess) return e;
+    const AdjDev A = adj_of(R, l);
+    GroupDev g{};
+    hipError_t e = groups_of(R, &g);
+    for (int sub = 0; sub < R.p->substeps && e == hipSuccess; ++sub) {
+        if (l < V.L - 1) e = sub_step<NEXT_ADJ>(R, l, dt_l, A, g);
+        else if (V.direct) e = sub_step<NEXT_GROUPS>(R, l, dt_l, A, g);
+        else e = sub_step<NEXT_NONE>(R, l, dt_l, A, g);
     }
-    return hipSuccess;
+    return e;
+}
+
+template <int NEXT>
+static hipError_t sub_step(const LevelRun &R, int l, double dt_l, const AdjDev &A, const GroupDev &g)
+{
+    const LevelLayout &V = *R.V;
+    const genga_params *p = R.p;
+    const BodyDev up = R.bodies_of(l - 1);
+    const ListDev list{up.bodies, up.nbod, R.b->n};
+    hipError_t e;
+    hipLaunchKernelGGL(k_level_radii<NEXT>, dim3(LG), dim3(LT), 0, R.s, up, R.at<double>(V.rc[l]),
+                       p->m_star, dt_l, p->n1, p->n2, A, g);
+    DetectDev d;
+    d.in_i = R.at<int32_t>(V.pi[l - 1]);
+    d.in_j = R.at<int32_t>(V.pj[l - 1]);
+    d.in_cnt = R.at<int64_t>(V.cnt) + (l - 1);
+    d.out_i = R.at<int32_t>(V.pi[l]);
+    d.out_j = R.at<int32_t>(V.pj[l]);
+    d.out_cnt = R.at<int64_t>(V.cnt) + l;
+    d.lcount = R.at<int64_t>(V.lcount) + l;
+    d.cap = V.cap;
+    d.x = R.b->x; d.y = R.b->y; d.z = R.b->z;
+    d.rc = R.at<double>(V.rc[l]);
+    d.bcnt = R.at<int64_t>(V.bcnt);
+    if ((e = level_kick(R, l, 0.5 * dt_l, &d)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_detect_write<NEXT>, dim3(DB), dim3(LT), 0, R.s, d, A, g);
+    if (NEXT == NEXT_ADJ && (e = build_adj(R, l, list)) != hipSuccess) return e;
+    if (NEXT == NEXT_GROUPS) build_groups(R, list, g);
+    hipLaunchKernelGGL(k_drift_list<NEXT>, dim3(LG), dim3(LT), 0, R.s, up, p->G * p->m_star, dt_l, A,
+                       g);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (NEXT == NEXT_ADJ && (e = advance(R, l + 1, dt_l / p->substeps)) != hipSuccess) return e;
+    if (NEXT == NEXT_GROUPS) {
+        const double *now[6] = {up.x, up.y, up.z, up.vx, up.vy, up.vz};
+        if ((e = direct_solve(R, l, dt_l, now)) != hipSuccess) return e;
+    }
+    return level_kick(R, l, 0.5 * dt_l, nullptr);
 }
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -2396,7 +2506,6 @@ LevelLayout make_level_layout(int64_t n, const genga_params *p, size_t base)
     V.cnt = take(sizeof(int64_t) * V.L);
     V.nbod = take(sizeof(int32_t) * V.L);
     V.bcnt = take(sizeof(int64_t) * DB);
-    V.tsum = take(sizeof(int64_t) * 2 * (size_t)((n + LT - 1) / LT));
     for (int l = 0; l < V.L; ++l) {
         V.pi[l] = take(sizeof(int32_t) * (size_t)V.cap);
         V.pj[l] = take(sizeof(int32_t) * (size_t)V.cap);
@@ -2408,26 +2517,25 @@ LevelLayout make_level_layout(int64_t n, const genga_params *p, size_t base)
             V.owner[l] = take(sizeof(int32_t) * 2 * (size_t)V.cap);
             V.deg[l] = take(sizeof(int32_t) * (size_t)n);
             V.bodies[l] = take(sizeof(int32_t) * (size_t)n);
-            V.shadow[l] = take(sizeof(double) * 6 * (size_t)n);
+            if (l == 0) V.shadow[0] = take(sizeof(double) * 6 * (size_t)n);
         }
     }
     if (V.direct) {
-        V.shadow[V.L - 1] = take(sizeof(double) * 6 * (size_t)n);
+        if (V.L == 1) V.shadow[0] = take(sizeof(double) * 6 * (size_t)n);
         V.glab = take(sizeof(int32_t) * (size_t)n);
         V.gflag = take(sizeof(int32_t) * (size_t)n);
         V.gsize = take(sizeof(int32_t) * (size_t)n);
-        V.gfill = take(sizeof(int32_t) * (size_t)n);
+        V.gslot = take(sizeof(int32_t) * (size_t)n);
         V.gstart = take(sizeof(int32_t) * (size_t)n);
         V.groot = take(sizeof(int32_t) * (size_t)n);
         V.gtmp = take(sizeof(int32_t) * (size_t)n);
         V.gmem = take(sizeof(int32_t) * (size_t)n);
-        V.gcount = take(sizeof(int32_t) * 2);
+        V.gcount = take(sizeof(int32_t) * 3);
         V.gstats = take(sizeof(int64_t) * 2);
         V.coll_count = take(sizeof(int64_t));
         V.coll_i = take(sizeof(int32_t) * LEVEL_COLL_CAP);
         V.coll_j = take(sizeof(int32_t) * LEVEL_COLL_CAP);
         V.coll_du = take(sizeof(double) * LEVEL_COLL_CAP);
-        V.gtsum = take(sizeof(int64_t) * 2 * (size_t)((n + LT - 1) / LT));
         if (n > GROUP_BLOCK) {
             const int64_t gc = (n + GT - 1) / GT * GT;
             V.gcap = gc < GENGA_GROUP_MAX ? gc : GENGA_GROUP_MAX;
@@ -2477,8 +2585,23 @@ hipError_t levels_before_drift(const genga_bodies *b, const LevelLayout &V, geng
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (V.L == 1) return group_and_save(R, 0);   // direct solver on E_0
-    if ((e = build_adj(R, 0)) != hipSuccess) return e;
+    const int32_t *pi = R.at<int32_t>(V.pi[0]), *pj = R.at<int32_t>(V.pj[0]);
+    const dim3 nb(R.list_blocks());
+    if (V.L == 1) {
+        // direct solver on E_0
+        GroupDev g{};
+        if ((e = groups_of(R, &g)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_group_begin, nb, dim3(LT), 0, s, g);
+        hipLaunchKernelGGL(k_group_union, dim3(LG), dim3(LT), 0, s, pi, pj, cnt0, V.cap, g);
+        build_groups(R, R.all(), g);
+        hipLaunchKernelGGL(k_group_place, nb, dim3(LT), 0, s, R.bodies_of(0), g,
+                           R.at<double>(V.shadow[0]));
+        return hipGetLastError();
+    }
+    const AdjDev A = adj_of(R, 0);
+    hipLaunchKernelGGL(k_adj_begin, nb, dim3(LT), 0, s, A);
+    hipLaunchKernelGGL(k_adj_count, dim3(LG), dim3(LT), 0, s, pi, pj, cnt0, V.cap, A);
+    if ((e = build_adj(R, 0, R.all())) != hipSuccess) return e;
     hipLaunchKernelGGL(k_state_list, dim3(LG), dim3(LT), 0, s, R.bodies_of(0),
                        R.at<double>(V.shadow[0]), b->n, 1);
     return hipGetLastError();
@@ -2488,7 +2611,12 @@ hipError_t levels_after_drift(genga_bodies *b, const genga_params *p, const Leve
                               char *ws, hipStream_t s)
 {
     LevelRun R{b, p, &V, ws, s};
-    if (V.L == 1) return direct_solve(R, 0, p->dt);
+    if (V.L == 1) {
+        const double *sh = R.at<double>(V.shadow[0]);
+        const int64_t n = b->n;
+        const double *saved[6] = {sh, sh + n, sh + 2 * n, sh + 3 * n, sh + 4 * n, sh + 5 * n};
+        return direct_solve(R, 0, p->dt, saved);
+    }
     hipLaunchKernelGGL(k_state_list, dim3(LG), dim3(LT), 0, s, R.bodies_of(0),
                        R.at<double>(V.shadow[0]), b->n, 0);
     hipError_t e = hipGetLastError();

@@ -19,15 +19,6 @@
 
 namespace genga {
 
-// 1/sqrt(v) from v_rsq_f64 with a second-order correction (relative error a
-// few 2^-53).
-__device__ __forceinline__ double rsq_full(double v)
-{
-    const double y = __builtin_amdgcn_rsq(v);
-    const double e = __builtin_fma(-v, y * y, 1.0);
-    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
-}
-
 // Columns of a system (global memory or LDS).
 struct RowsCols {
     const double *x, *y, *z, *m, *rc;
