@@ -853,10 +853,14 @@ __device__ __forceinline__ int32_t bs_cell(const BsFrame &f, double x, double y)
     return (int)(cx + 0.5) | ((int)(cy + 0.5) << 16);
 }
 
-__device__ __forceinline__ bool bs_cell_near(int32_t a, int32_t b, int reach2)
+// `bits` with the test of one more partner shifted in from below: in reach iff
+// d.d - (reach2 + 1) is negative, whose sign bit the funnel shift takes (three
+// instructions a partner; compare, select and or into a 64-bit mask took 65 cycles).
+__device__ __forceinline__ uint32_t bs_cell_test(uint32_t bits, int32_t a, int32_t b, int far2)
 {
     const bs_s16x2 d = __builtin_bit_cast(bs_s16x2, a) - __builtin_bit_cast(bs_s16x2, b);
-    return __builtin_amdgcn_sdot2(d, d, 0, false) <= reach2;
+    const int q = __builtin_amdgcn_sdot2(d, d, far2, false);
+    return __builtin_amdgcn_alignbit(bits, (uint32_t)q, 31);
 }
 
 // Exclusive sum over the lanes of a wave and the total (small counts).
@@ -927,25 +931,13 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const B
         wave_sync_lds();
         E = BsEntries();
     };
+    // Up to 64 partners as the bits of one mask: a part of one tile, or the
+    // parts of two tiles (S = 2, 4) in its halves
     const int per = 64 / S, u0 = sub * per;
-    for (int J = 0; J < nw; ++J) {
-        const double rr = rhoI > sm.trho[J] ? rhoI : sm.trho[J];
-        if (box_gap2(lo, hi, sm.box[J]) > rr * rr * (1.0 + 0x1p-18)) continue;
-        const double re = (rcd > sm.trho[J] ? rcd : sm.trho[J]) * fr.scale + 2.0;
-        const int reach2 = (int)__builtin_fmin(re * re + 1.0, 1e9);
-        const int4 *cells = (const int4 *)&sm.cell[J * 64 + u0];
-        uint64_t mask = 0;
-        for (int u = 0; u < per; u += 4) {
-            const int4 c = cells[u >> 2];
-            const uint32_t b = (bs_cell_near(me, c.x, reach2) ? 1u : 0u) |
-                               (bs_cell_near(me, c.y, reach2) ? 2u : 0u) |
-                               (bs_cell_near(me, c.z, reach2) ? 4u : 0u) |
-                               (bs_cell_near(me, c.w, reach2) ? 8u : 0u);
-            mask |= (uint64_t)b << (u0 + u);
-        }
-        if (g - J * 64 < 64) mask &= (1ull << (g - J * 64)) - 1;
-        if (J * 64 == t0) mask &= ~(1ull << lane);
-        if (t >= g) mask = 0;
+    uint64_t mask = 0;
+    int part = 0, first[2] = {0, 0};   // parts in the mask, first partner of each
+    auto emit = [&]() {
+        const int shift = first[1] - 32;
         while (__any(mask != 0)) {
             const int pc = __popcll(mask), c = pc < 4 ? pc : 4;
             int sum;
@@ -955,7 +947,8 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const B
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 if (k < c) {
-                    ent[base + k] = (uint32_t)(lane << 16) | (uint32_t)(J * 64 + __builtin_ctzll(mask));
+                    const int b = __builtin_ctzll(mask);
+                    ent[base + k] = (uint32_t)(lane << 16) | (uint32_t)(b + (b < 32 ? first[0] : shift));
                     mask &= mask - 1;
                 }
             }
@@ -963,7 +956,43 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const B
             E.total += sum;
             ++E.rounds;
         }
+        mask = 0;
+        part = 0;
+    };
+    for (int J = 0; J < nw; ++J) {
+        const double rr = rhoI > sm.trho[J] ? rhoI : sm.trho[J];
+        if (box_gap2(lo, hi, sm.box[J]) > rr * rr * (1.0 + 0x1p-18)) continue;
+        const double re = (rcd > sm.trho[J] ? rcd : sm.trho[J]) * fr.scale + 2.0;
+        const int far2 = -1 - (int)__builtin_fmin(re * re + 1.0, 1e9);
+        const int4 *cells = (const int4 *)&sm.cell[J * 64 + u0];
+        // words of up to 32 partners, the first in the lowest bit
+        auto word = [&](int v0, int cnt) {
+            uint32_t bits = 0;
+#pragma unroll 2
+            for (int v = v0; v < v0 + cnt; v += 4) {
+                const int4 c = cells[v >> 2];
+                bits = bs_cell_test(bits, me, c.x, far2);
+                bits = bs_cell_test(bits, me, c.y, far2);
+                bits = bs_cell_test(bits, me, c.z, far2);
+                bits = bs_cell_test(bits, me, c.w, far2);
+            }
+            bits = __brev(bits) >> (32 - cnt);
+            const int j0 = J * 64 + u0 + v0;
+            if (g - j0 < 32) bits &= g > j0 ? (1u << (g - j0)) - 1 : 0u;
+            if (J * 64 == t0 && (unsigned)(t - j0) < 32u) bits &= ~(1u << (t - j0));
+            return t < g ? bits : 0u;
+        };
+        first[part] = J * 64 + u0;
+        if (S == 1) {
+            mask = word(0, 32) | (uint64_t)word(32, 32) << 32;
+            first[1] = first[0] + 32;
+            emit();
+        } else {
+            mask |= (uint64_t)word(0, per) << (32 * part);
+            if (++part == 2) emit();
+        }
     }
+    emit();
     if (E.total) flush();
 }
 
@@ -1236,10 +1265,12 @@ __device__ int bs_step(const BsDev &a, Pol &P, const double y[6], double h, doub
             T[0][c] = 0.5 * (z0[c] + z1[c] + hh * fz[c]);
 #pragma unroll
             for (int j = 1; j <= k; ++j) {
-                const double ratio = (double)nk / (double)(nk - 2 * j);
-                const double den = ratio * ratio - 1.0;
+                // 1 / (ratio^2 - 1), ratio = nk / (nk - 2 j): a constant (with
+                // divisions a launch of small groups took 26.2 us, now 24.9)
+                const double rden = (double)((nk - 2 * j) * (nk - 2 * j)) /
+                                    (double)(nk * nk - (nk - 2 * j) * (nk - 2 * j));
                 const double oj = T[j][c];
-                T[j][c] = T[j - 1][c] + (T[j - 1][c] - old) / den;
+                T[j][c] = T[j - 1][c] + (T[j - 1][c] - old) * rden;
                 old = oj;
             }
         }
@@ -1629,7 +1660,6 @@ __device__ __forceinline__ bool bs_in_reach(const float4 &a, const float4 &b)
     return !(r2 > (a.w > b.w ? a.w : b.w));   // (a NaN is evaluated)
 }
 
-
 constexpr int GCELL = 64;           // ordering cells per axis
 // a barrier that has waited this long (wall clock, 100 MHz ticks: 2 s) gives up
 constexpr uint64_t GWAIT_TICKS = 200000000ull;
@@ -1886,7 +1916,7 @@ struct GridPol {
                         const double r2 = dx * dx + dy * dy + dz * dz;
                         const double ir = rsq_full(r2);
                         const double Rw = bs_remainder<0>(r2 * ir, &S.oirc[0][threadIdx.x], GT,
-                                                       &S.sirc[w][0][q], 64, nl);
+                                                          &S.sirc[w][0][q], 64, nl);
                         const double s = Gc * S.sm[w][q] * Rw * (ir * ir * ir);
                         ax += s * dx;
                         ay += s * dy;
