@@ -115,17 +115,63 @@ struct SymRows {
     float axf[SYM_IPT], ayf[SYM_IPT], azf[SYM_IPT], magf[SYM_IPT];
 };
 
-// Rare path of one pair (binary64: r^2 at most the wave's gate bound, which is
-// at least max(rc_i^2, rc_j^2); mixed: r^2 <= max(rc_i^2, rc_j^2)): the self pair, coincident bodies, the changeover band
-// and encounter recording.  si, sj hold the fast weights (m_j and m_i times
-// r^-3) and are replaced by K-weighted ones inside rho_ij; a pair at or beyond
-// rho_ij keeps them (K = 1) and is not recorded.  1/r and 1/rho from
-// v_rsq_f64 with one Newton correction (relative error below 5e-15), so the
-// band variable is y = (r/rho) / 0.9 - 1/9; in the binary64 kick m_i is
-// (2/3) (3/2 m_i), to 2 ulp.  Whether a pair is inside rho_ij, and so in the
-// encounter list, is decided by r^2 < max(rc_i^2, rc_j^2) alone.
-template <bool MIXED>
-__device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<MIXED> &R, int q, int jg,
+// Rare path of the binary64 kick, entered by the whole wave when any lane's r^2
+// is at most the gate's bound g2 (which is at least max(rc_i^2, rc_j^2)): the
+// self pair, coincident bodies, the changeover band and encounter recording.
+// t holds the fast weight's r^-3 part; si, sj the fast weights (m_j and m_i
+// times r^-3), replaced by K-weighted ones inside rho_ij; a pair at or beyond
+// rho_ij keeps them (K = 1) and is not recorded.  1/r and 1/rho from v_rsq_f64
+// with one Newton correction (relative error below 5e-15), so the band
+// variable is y = (r/rho) / 0.9 - 1/9; m_i is (2/3) (3/2 m_i), to 2 ulp.
+// Whether a pair is inside rho_ij, and so in the encounter list, is decided by
+// r^2 < max(rc_i^2, rc_j^2) alone.
+//
+// An event costs the wave its instructions (a fifth of the 512-system
+// ensemble's kick, a tenth at 20,011 bodies), so the code is straight: nested
+// exec masks, a count in LDS and a second v_rsq_f64 of r^2 took 334 us for that
+// ensemble's kick, this takes 321.
+__device__ __forceinline__ void sym_near(const SymDev &a, SymRows<false> &R, int q, int jg, double r2,
+                                         double yv, double y2, double rc2c, double mc, double &si,
+                                         double &sj, int64_t wave_g, int &nst)
+{
+    const double rho2 = vmax_f64(R.rc2i[q], rc2c);
+    const bool zero = r2 == 0.0;
+    const bool inside = r2 < rho2 && !zero;
+    if (__ballot(zero)) {
+        if (zero && jg != R.ii[q]) atomicOr(a.status, ST_NONFINITE);
+        si = zero ? 0.0 : si;
+        sj = zero ? 0.0 : sj;
+    }
+    if (__ballot(inside)) {
+        const double yc = __builtin_fma(yv * __builtin_fma(-r2, y2, 1.0), 0.5, yv);
+        const double irho = rsq_nr(rho2);
+        double y = __builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0);
+        y = vmin_f64(vmax_f64(y, 0.0), 1.0);
+        const double yy = y * y;
+        const double kr = (yy * rcp_nr2(__builtin_fma(2.0, yy - y, 1.0))) *
+                          (yc * yc * yc);
+        si = inside ? mc * kr : si;
+        sj = inside ? (R.mw[q] * (2.0 / 3.0)) * kr : sj;
+        if (a.emit) {
+            const bool emit = inside && jg > R.ii[q];
+            const uint64_t mask = __ballot(emit);
+            if (emit) {
+                const int pos = nst + __popcll(mask & lanemask_lt());
+                if (pos < WSEG) {
+                    int32_t *e3 = a.stage + ((size_t)wave_g * WSEG + pos) * 3;
+                    e3[0] = (int32_t)(R.ii[q] + a.o);
+                    e3[1] = (int32_t)(jg + a.o);
+                }
+                R.kc[q] += 1;
+            }
+            nst += __popcll(mask);
+        }
+    }
+}
+
+// The mixed kernel's rare path (r^2 <= max(rc_i^2, rc_j^2)), entered by the
+// lanes concerned; the same rules.
+__device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<true> &R, int q, int jg,
                                          double r2, double rc2c, double mc, double &si,
                                          double &sj, int64_t wave_g, int *wcnt)
 {
@@ -147,7 +193,7 @@ __device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<MIXED> &R, int
             const double K = changeover_of_y(__builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0));
             const double kr = K * (yc * yc * yc);
             si = mc * kr;
-            sj = (MIXED ? R.mw[q] : R.mw[q] * (2.0 / 3.0)) * kr;
+            sj = R.mw[q] * kr;
         }
     }
     if (a.emit) {
@@ -160,7 +206,6 @@ __device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<MIXED> &R, int
                     int32_t *e3 = a.stage + ((size_t)wave_g * WSEG + pos) * 3;
                     e3[0] = (int32_t)(R.ii[q] + a.o);
                     e3[1] = (int32_t)(jg + a.o);
-                    e3[2] = 0;
                 }
                 R.kc[q] += 1;
             }
@@ -182,7 +227,7 @@ template <bool GEN>
 __device__ __forceinline__ void sym_chunk(const SymDev &a, SymRows<false> &R,
                                           const SymCols<false> &C, int colbase, const int *mode,
                                           double &cx, double &cy, double &cz, double c53,
-                                          double g2, int64_t wave_g, int *wcnt, int lane)
+                                          double g2, int64_t wave_g, int &nst, int lane)
 {
     for (int k0 = 0; k0 < 64; k0 += 2) {
 #pragma unroll
@@ -204,14 +249,14 @@ __device__ __forceinline__ void sym_chunk(const SymDev &a, SymRows<false> &R,
                 const double t = (y2 * yv) * pp;
                 double si = t * zm.y;
                 double sj = t * R.mw[q];
-                if (cand) {
+                if (__ballot(cand)) {
                     // the column index only here: an empty volatile asm keeps the
                     // compiler from computing it on the fast path
                     int ee = lane;
                     asm volatile("" : "+v"(ee));
                     ee += k0 + u;
-                    sym_slow<false>(a, R, q, colbase + (ee & 63), r2, C.rc2[ee], C.m[ee], si, sj,
-                                    wave_g, wcnt);
+                    sym_near(a, R, q, colbase + (ee & 63), r2, yv, y2, C.rc2[ee], C.m[ee], si, sj,
+                             wave_g, nst);
                 }
                 R.ax[q] = __builtin_fma(dx, si, R.ax[q]);
                 R.ay[q] = __builtin_fma(dy, si, R.ay[q]);
@@ -281,7 +326,7 @@ __device__ __forceinline__ void sym_chunk_mixed(const SymDev &a, SymRows<true> &
                     const double r3 = __builtin_fma(t3 * e1, pp, t3);
                     double wi = mc * r3, wj = R.mw[q] * r3;
                     if (r2 <= vmax_f64(R.rc2i[q], rc2c))
-                        sym_slow<true>(a, R, q, colbase + (ee & 63), r2, rc2c, mc, wi, wj, wave_g,
+                        sym_slow(a, R, q, colbase + (ee & 63), r2, rc2c, mc, wi, wj, wave_g,
                                        wcnt);
                     R.ax[q] = __builtin_fma(dx, wi, R.ax[q]);
                     R.ay[q] = __builtin_fma(dy, wi, R.ay[q]);
@@ -438,9 +483,11 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
         for (int q = 0; q < SYM_IPT; ++q) r2m = vmax_f64(r2m, R.rc2i[q]);
         rg = wave_max_hi(r2m);
     }
+    // pairs staged by the wave: uniform in the binary64 kick; mixed: in LDS
+    int nst = 0;
     int *wcnt = &sm.wcnt[w];
-    if (lane == 0) __hip_atomic_store(wcnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     if constexpr (MIXED) {
+        if (lane == 0) __hip_atomic_store(wcnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         sm.nacc[w][0][lane] = 0.0;
         sm.nacc[w][1][lane] = 0.0;
         sm.nacc[w][2][lane] = 0.0;
@@ -520,10 +567,10 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
                 bound_of_hi(max(rg, __builtin_amdgcn_readfirstlane(sm.gmax[b])));
             double cx = 0.0, cy = 0.0, cz = 0.0;
             if (full)
-                sym_chunk<false>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, wave_g, wcnt,
+                sym_chunk<false>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, wave_g, nst,
                                  lane);
             else
-                sym_chunk<true>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, wave_g, wcnt,
+                sym_chunk<true>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, wave_g, nst,
                                 lane);
             sm.acc[b][0][w][lane] = cx;
             sm.acc[b][1][w][lane] = cy;
@@ -553,8 +600,11 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
         if constexpr (MIXED) p[3 * SYM_RG] = R.mag[q];
         if (a.emit) a.cnt[(size_t)sid * SYM_RG + off] = R.kc[q];
     }
-    if (a.emit && lane == 0)
-        a.wcount[wave_g] = __hip_atomic_load(wcnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    if (a.emit && lane == 0) {
+        if constexpr (MIXED)
+            nst = __hip_atomic_load(wcnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        a.wcount[wave_g] = nst;
+    }
 }
 
 template <bool MIXED>

@@ -69,4 +69,12 @@ __device__ __forceinline__ double rsq_nr(double v)
     return __builtin_fma(y * e, 0.5, y);
 }
 
+// 1/v from v_rcp_f64 and two Newton steps.
+__device__ __forceinline__ double rcp_nr2(double v)
+{
+    double t = __builtin_amdgcn_rcp(v);
+    t = __builtin_fma(t, __builtin_fma(-v, t, 1.0), t);
+    return __builtin_fma(t, __builtin_fma(-v, t, 1.0), t);
+}
+
 }  // namespace genga

@@ -319,3 +319,24 @@ def test_direct_groups_of_many_partners(dev, n, k):
     ep, ev = _rel(out, ref, ("x", "y", "z")), _rel(out, ref, ("vx", "vy", "vz"))
     _say(f"ring {n}, {2 * k} partners: position {ep:.2e} velocity {ev:.2e}")
     assert ep < 1e-11 and ev < 1e-11
+
+
+@pytest.mark.parametrize("L,s,spec", [(1, 1, W.DISK_8192), (3, 2, W.DISK_2048), (4, 2, W.DISK_2048)])
+def test_groups_do_not_depend_on_arrival(dev, L, s, spec):
+    # groups, their members' slots, list segments and bodies are handed out in
+    # order of arrival; no result may depend on it: four runs from one state,
+    # the same bits, over groups of both classes of one launch
+    d = W.make_disk(spec)
+    cfg = _cfg(L, s)
+    outs = []
+    for _ in range(4):
+        st = N.State.from_numpy(d)
+        ws = N.Workspace(st.n, cfg)
+        for _ in range(3):
+            assert N.step(st, cfg, ws) == N.OK
+        outs.append((st.numpy(), N.group_stats(st.n, cfg, ws), N.level_counts(st.n, cfg, ws)))
+    assert outs[0][1][0] > 0
+    for o in outs[1:]:
+        assert o[1] == outs[0][1] and np.array_equal(o[2], outs[0][2])
+        for k in ("x", "y", "z", "vx", "vy", "vz"):
+            assert np.array_equal(o[0][k], outs[0][0][k]), k
