@@ -6,6 +6,13 @@
 // (kick with the close-encounter pre-check), Appendix B (fixed pair-list order
 // for exact reproducibility).
 //
+// This file holds the one-sided form and the host side of every form.  The
+// default forms of the binary64 kick are the row groups (csrc/rows.hip, below
+// SYM_MIN_N bodies), the symmetric kick (csrc/kick_sym.hip, from there on and
+// in a batch) and, with few massive bodies, csrc/tp.hip; the one-sided form is
+// what flags, slices and rows per thread ask for, the energy and the
+// test-particle modes beyond TP_MAX massive bodies.
+//
 // Design for gfx950 (wave64, 256 CUs):
 //  * The work is cut into tiles: a block of rows of one system against a
 //    range of its columns.  A single system uses an implicit 2-D grid of tiles
