@@ -613,9 +613,9 @@ struct LevelWeight {
 // the GL partial sums are combined by a fixed butterfly, so the result does
 // not depend on scheduling.  Bound by its dependent loads (body, segment,
 // partner, its state) and the chain of one pair, hence the corrected hardware
+// estimates, the level as a template argument (all radii in flight at once)
 // and one reciprocal for all levels (65,536 bodies, level 2 of 3 x 4: 8 -> 6-7
-// us per launch; level 1, 41,500 pairs of 235,000 in reach, 25 us of gathers).
-constexpr int GL = 8;
+// us per launch; level 1, 235,000 pairs: 24-27 us, mostly gathers).
 constexpr int GL = 8;
 constexpr int KB_DETECT = DB;   // blocks in front that count the next list
 
