@@ -30,6 +30,7 @@ struct RowsTeam {
     double part[4][3 * ROWS_G];
     double slow[ROWS_G][3];
     int32_t cnt[ROWS_G];
+    double row[ROWS_G][4];   // x, y, z, rc of the rows
 };
 
 // a and b summed over the two halves of the wave: lanes 0-31 hold a's sums
@@ -157,6 +158,12 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
         zi[q] = wave_uniform(real ? c.z[i] : 1e18);
         rc2i[q] = wave_uniform(real ? r * r : 0.0);
         rg = rc2i[q] > rg ? rc2i[q] : rg;
+        if (tid == 0) {
+            sm.row[q][0] = xi[q];
+            sm.row[q][1] = yi[q];
+            sm.row[q][2] = zi[q];
+            sm.row[q][3] = r;
+        }
     }
     rg = wave_uniform(rg);
     double acc[3 * ROWS_G] = {};
@@ -204,7 +211,7 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
             const uint64_t after = first <= 0 ? b : (first > 63 ? 0 : b & (~0ull << first));
             sm.bits[q][k] = after;
             cnt += __popcll(after);
-            const double ri = c.rc[i], Xi = c.x[i], Yi = c.y[i], Zi = c.z[i];
+            const double Xi = sm.row[q][0], Yi = sm.row[q][1], Zi = sm.row[q][2], ri = sm.row[q][3];
             while (b) {
                 const int j = k * 64 + __ffsll((unsigned long long)b) - 1;
                 b &= b - 1;

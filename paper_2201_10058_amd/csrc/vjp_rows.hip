@@ -34,6 +34,7 @@ struct VjpRowsSmem {
     double part[4][4 * VR_G];
     double slow[VR_G][5];
     double rc2[VR_G];
+    double row[VR_G][8];   // x, y, z, m, rc, scaled abar of the rows
 };
 
 struct VjpColumn {
@@ -54,6 +55,17 @@ __global__ __launch_bounds__(256) void k_vjp_rows(VjpRowsDev a)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = a.n, nw = (n + 63) >> 6, r0 = (int)blockIdx.x * VR_G;
     VjpColumn A = vjp_load(a, tid), B;
+    // the adjoints that the block adds to, loaded ahead of the columns
+    const bool last = tid < VR_G && r0 + tid < n;
+    double old[5] = {};
+    if (last) {
+        const int i = r0 + tid;
+        old[0] = a.adj.x[i];
+        old[1] = a.adj.y[i];
+        old[2] = a.adj.z[i];
+        old[3] = a.adj.m[i];
+        old[4] = a.adj.rc[i];
+    }
     for (int q = 0; q < VR_G; ++q)
         for (int k = tid; k < nw; k += 256) sm.bits[q][k] = 0;
     const int vzero = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
@@ -73,7 +85,17 @@ __global__ __launch_bounds__(256) void k_vjp_rows(VjpRowsDev a)
         by[q] = wave_uniform(a.scale * a.aby[i]);
         bz[q] = wave_uniform(a.scale * a.abz[i]);
         const double r2 = real ? r * r : 0.0;
-        if (tid == 0) sm.rc2[q] = r2;
+        if (tid == 0) {
+            sm.rc2[q] = r2;
+            sm.row[q][0] = xi[q];
+            sm.row[q][1] = yi[q];
+            sm.row[q][2] = zi[q];
+            sm.row[q][3] = mi[q];
+            sm.row[q][4] = r;
+            sm.row[q][5] = bx[q];
+            sm.row[q][6] = by[q];
+            sm.row[q][7] = bz[q];
+        }
         rg = r2 > rg ? r2 : rg;
     }
     rg = wave_uniform(rg);
@@ -157,8 +179,9 @@ __global__ __launch_bounds__(256) void k_vjp_rows(VjpRowsDev a)
     {
         // marked pairs of row w, a lane the words l, l + 64 (in true units)
         const int i = r0 + w < n ? r0 + w : n - 1;
-        const double X = a.x[i], Y = a.y[i], Z = a.z[i], mk = a.m[i], rck = a.rc[i];
-        const double kx = a.scale * a.abx[i], ky = a.scale * a.aby[i], kz = a.scale * a.abz[i];
+        const double *row = sm.row[w];
+        const double X = row[0], Y = row[1], Z = row[2], mk = row[3], rck = row[4];
+        const double kx = row[5], ky = row[6], kz = row[7];
         double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
         bool seen = false;
         for (int k = lane; k < nw; k += 64) {
@@ -200,7 +223,7 @@ __global__ __launch_bounds__(256) void k_vjp_rows(VjpRowsDev a)
             for (int k = 0; k < 5; ++k) sm.slow[w][k] = s[k];
     }
     __syncthreads();
-    if (tid < VR_G && r0 + tid < n) {
+    if (last) {
         const int i = r0 + tid;
         double t[4];
 #pragma unroll
@@ -208,11 +231,11 @@ __global__ __launch_bounds__(256) void k_vjp_rows(VjpRowsDev a)
             t[k] = (((sm.part[0][4 * tid + k] + sm.part[1][4 * tid + k]) + sm.part[2][4 * tid + k]) +
                     sm.part[3][4 * tid + k]) +
                    sm.slow[tid][k];
-        a.adj.x[i] += a.G * t[0];
-        a.adj.y[i] += a.G * t[1];
-        a.adj.z[i] += a.G * t[2];
-        a.adj.m[i] -= a.G * t[3];
-        a.adj.rc[i] += a.G * sm.slow[tid][4];
+        a.adj.x[i] = old[0] + a.G * t[0];
+        a.adj.y[i] = old[1] + a.G * t[1];
+        a.adj.z[i] = old[2] + a.G * t[2];
+        a.adj.m[i] = old[3] - a.G * t[3];
+        a.adj.rc[i] = old[4] + a.G * sm.slow[tid][4];
     }
 }
 
