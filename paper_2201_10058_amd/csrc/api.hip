@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "genga_internal.h"
+#include "rows.h"
 
 namespace genga {
 
@@ -128,8 +129,14 @@ static int do_kick(const genga_bodies *b, const genga_params *p, double h, doubl
                    double *az, genga_pairs *pairs, bool forces, void *ws, void *stream,
                    int ev_slot = 0, bool fuse_hc = false)
 {
-    const KickCfg c = choose_kick_cfg(b->n, p);
+    KickCfg c = choose_kick_cfg(b->n, p);
     const Layout L = make_layout(b->n, c);
+    if (c.use_rows || c.use_tp) {
+        const double *const in[] = {b->x, b->y, b->z, b->m, b->rc};
+        const double *const out[] = {ax, ay, az, h != 0.0 ? b->vx : nullptr,
+                                     h != 0.0 ? b->vy : nullptr, h != 0.0 ? b->vz : nullptr};
+        if (arrays_overlap(out, in, b->n)) c.use_rows = c.use_tp = false;
+    }
     KickLaunch k = kick_launch(b, p, h, ax, ay, az, pairs, forces, ev_slot);
     if (fuse_hc) {
         k.px = b->x; k.py = b->y; k.pz = b->z;

@@ -19,6 +19,18 @@
 
 namespace genga {
 
+// Whether any of the arrays of n doubles `out` lies over one of `in`: the row
+// groups write a row's results while other blocks still read the columns, so
+// such a call takes the forms that write in a second kernel.
+template <int NO, int NI>
+inline bool arrays_overlap(const double *const (&out)[NO], const double *const (&in)[NI], int64_t n)
+{
+    for (const double *o : out)
+        for (const double *i : in)
+            if (o && i && o < i + n && i < o + n) return true;
+    return false;
+}
+
 // Columns of a system (global memory or LDS).
 struct RowsCols {
     const double *x, *y, *z, *m, *rc;

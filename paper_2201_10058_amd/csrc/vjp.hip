@@ -20,6 +20,7 @@
 #include "device_common.h"
 #include "genga_internal.h"
 #include "kepler.h"
+#include "rows.h"
 
 namespace genga {
 
@@ -310,7 +311,9 @@ hipError_t launch_kick_vjp(const genga_bodies *b, const genga_params *p, double 
         return launch_kick_vjp_sym(c.sym, b, p->G, scale, abx, aby, abz, adj,
                                    (double *)(ws + L.part), (int32_t *)(ws + L.status), s);
     }
-    if (c.use_rows)
+    const double *const in[] = {b->x, b->y, b->z, b->m, b->rc, abx, aby, abz};
+    const double *const out[] = {adj->x, adj->y, adj->z, adj->m, adj->rc};
+    if (c.use_rows && !arrays_overlap(out, in, b->n))
         return launch_kick_vjp_rows(b, p->G, scale, abx, aby, abz, adj, (int32_t *)ws, s);
     // one row per thread for the adjoint (its register footprint is larger)
     c.ipt = 1;

@@ -5,6 +5,8 @@ and range, against the oracle.
 Tolerances as in the parity tests: 1e-12 per acceleration of the compensated
 oracle, encounter lists equal, 1e-12 of the largest component per step.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -149,3 +151,34 @@ def test_kick_vjp_against_tiled_form(dev, n, dense):
         assert all(np.array_equal(out[0][k], base[k]) for k in base)
     else:
         assert np.array_equal(out[0]["rc"] != base["rc"], out[1]["rc"] != base["rc"])
+
+
+def test_results_over_their_inputs(dev):
+    # accelerations written over the positions and adjoints added to the arrays
+    # that hold abar: as with arrays of their own (tolerances as above)
+    n = 300
+    d = W.random_cloud(n, seed=77, rc_scale=0.3)
+    cfg = N.Config(G=G)
+    ws = N.Workspace(n, cfg)
+    st = N.State.from_numpy(d)
+    ref = N.kick(st, cfg, ws, 0.0, acc=True).cpu().numpy()
+    b, p = st.bodies(), cfg.params()
+    assert N.load().genga_kick(ctypes.byref(b), ctypes.byref(p), 0.0, b.x, b.y, b.z, None, ws.ptr,
+                               None) == N.OK
+    torch.cuda.synchronize()
+    out = np.stack([st.t[k].cpu().numpy() for k in "xyz"])
+    assert np.max(np.linalg.norm(out - ref, axis=0) / np.linalg.norm(ref, axis=0)) <= TOL
+
+    st = N.State.from_numpy(d)
+    rng = np.random.default_rng(5)
+    base = {k: rng.normal(size=n) for k in N.AdjointState.KEYS}
+    res = []
+    for shared in (False, True):
+        adj = N.AdjointState(n, tensors={k: torch.tensor(v, device="cuda") for k, v in base.items()})
+        ab = [adj.t[k] if shared else adj.t[k].clone() for k in "xyz"]
+        N.kick_vjp(st, cfg, ws, 0.7, ab, adj)
+        assert N.read_status(ws) == N.OK
+        res.append({k: adj.t[k].cpu().numpy() for k in adj.KEYS})
+    for k in ("x", "y", "z", "m", "rc"):
+        size = max(np.abs(res[0][k] - base[k]).max(), 1.0)
+        assert np.abs(res[1][k] - res[0][k]).max() <= 8e-11 * size, k
