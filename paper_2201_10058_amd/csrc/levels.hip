@@ -592,6 +592,15 @@ __device__ __forceinline__ double rcp_full(double x)
     return __builtin_fma(t, __builtin_fma(e, e, e), t);
 }
 
+// 1 / rho for LevelWeight.  A radius of zero (a body at rest, or without mass,
+// where n1 or n2 leaves nothing else) has K = 1 at every distance: its
+// reciprocal is a number that takes y to 1, where rcp_full would give a NaN,
+// which the clamp turns into y = 0.
+__device__ __forceinline__ double rcp_radius(double rho)
+{
+    return rho > 1e-300 ? rcp_full(rho) : 1e300;
+}
+
 // The changeover K(y) = y^2 / (2 y^2 - 2 y + 1) of y = (r / rho - 0.1) / 0.9 in
 // [0, 1], as num^2 / den: `up` takes y for a factor K and 1 - y for a factor
 // 1 - K, so that a product over levels needs one reciprocal.
@@ -666,7 +675,7 @@ __global__ __launch_bounds__(LT) void k_level_kick(LevelKickDev k, DetectDev d)
             LevelWeight w;
 #pragma unroll
             for (int l = 0; l <= LEVEL; ++l)
-                w.add(r, rho[l] > 0.0 ? rcp_full(rho[l]) : 1e300, l == LEVEL);
+                w.add(r, rcp_radius(rho[l]), l == LEVEL);
             const double s = (k.G * mj) * w.value() * (ir * ir * ir);
             ax = __builtin_fma(s, dx, ax);
             ay = __builtin_fma(s, dy, ay);
@@ -1516,7 +1525,7 @@ __device__ __forceinline__ void bs_lanes(const BsDev &a, double (*irc)[GROUP_BLO
             for (int c = 0; c < 6; ++c) y[c] = a.state[c][b];
             P.m = a.m[b];
             P.R = a.radius ? a.radius[b] : 0.0;
-            for (int l = 0; l < a.nlev; ++l) irc[l][threadIdx.x] = rcp_full(a.rc[l][b]);
+            for (int l = 0; l < a.nlev; ++l) irc[l][threadIdx.x] = rcp_radius(a.rc[l][b]);
         }
         const bool failed = bs_run(a, P, y);
         if (failed && u == 0) atomicOr(a.status, ST_NOCONV);
@@ -1572,7 +1581,7 @@ __device__ __forceinline__ void bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &s
             sm.m[t] = a.m[b];
             sm.R[t] = a.radius ? a.radius[b] : 0.0;
             for (int l = 0; l < a.nlev; ++l)
-                sm.irc[l][t] = rcp_full(a.rc[l][b]);
+                sm.irc[l][t] = rcp_radius(a.rc[l][b]);
         }
         {
             const double tr = wave_max_all(rcd);
@@ -2210,7 +2219,7 @@ __global__ __launch_bounds__(GT, 2) void k_bs_grid(BsDev a, GridDev G)
             P.R = a.radius ? a.radius[b] : 0.0;
             P.rcd = a.rc[a.nlev - 1][b];
             for (int l = 0; l < a.nlev; ++l) {
-                const double ir = rcp_full(a.rc[l][b]);
+                const double ir = rcp_radius(a.rc[l][b]);
                 S.oirc[l][threadIdx.x] = ir;
                 if (P.owner()) G.mirc[(size_t)l * G.cap + t] = ir;
             }

@@ -340,3 +340,35 @@ def test_groups_do_not_depend_on_arrival(dev, L, s, spec):
         assert o[1] == outs[0][1] and np.array_equal(o[2], outs[0][2])
         for k in ("x", "y", "z", "vx", "vy", "vz"):
             assert np.array_equal(o[0][k], outs[0][0][k]), k
+
+
+@pytest.mark.parametrize("n, L, s", [(3, 1, 1), (8, 1, 1), (8, 2, 2), (12, 1, 1), (12, 2, 2), (150, 1, 1),
+                                     (600, 1, 1)])
+def test_members_without_a_radius(dev, n, L, s):
+    # bodies at rest under n1 = 0 have no critical radius: they meet the moving
+    # body's, and between themselves the kick takes their whole force (K = 1 at
+    # every distance), the direct solver none of it.  Groups of both classes of
+    # one launch and of the grid solver; tolerance as for the rings.
+    rng = np.random.default_rng(n)
+    d = {k: np.zeros(n) for k in ("x", "y", "z", "vx", "vy", "vz")}
+    d["x"][:] = 1.0
+    d["vz"][0] = 0.016
+    box = rng.uniform(-0.02, 0.02, (3, n - 1))
+    d["x"][1:] += 0.04 + box[0]
+    d["y"][1:] += box[1]
+    d["z"][1:] += box[2]
+    d["m"] = np.full(n, 1e-9)
+    cfg = N.Config(G=G, m_star=1.0, dt=1.0, n1=0.0, n2=6.0, slevels=L, substeps=s,
+                   level_capacity=n * n, direct=1)
+    st = N.State.from_numpy(d)
+    ws = N.Workspace(n, cfg)
+    ref = oracle.state_copy(d)
+    assert N.step(st, cfg, ws) == N.OK
+    r = oracle.step_direct(ref, G, 1.0, 1.0, 0.0, 6.0, L, s, rk_steps=400)
+    assert r[6] == 0 and N.group_stats(n, cfg, ws) == r[5] and r[5][0] >= 1
+    if L == 1:
+        assert r[5] == (1, n) and np.all(r[3][1:] == 0.0)
+    out = st.numpy()
+    ep, ev = _rel(out, ref, ("x", "y", "z")), _rel(out, ref, ("vx", "vy", "vz"))
+    _say(f"{n} bodies, {L}x{s}: position {ep:.2e} velocity {ev:.2e}")
+    assert ep < 1e-11 and ev < 1e-11
