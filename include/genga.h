@@ -90,6 +90,10 @@ extern "C" {
 #define GENGA_FLAG_DIRECTED  2
 #define GENGA_FLAG_SYMMETRIC 4
 
+/* genga_step with GENGA_MIXED takes the binary64 kick below this many bodies,
+ * unless p->ipt, p->slices or a form flag is set. */
+#define GENGA_MIXED_STEP_MIN 8192
+
 /* Bodies of one system, democratic coordinates, device SoA of length n.
  * rc holds the critical radii r_crit,i (eq. rcrit); genga_rcrit writes it.    */
 typedef struct {
@@ -270,8 +274,8 @@ int genga_drift(genga_bodies *b, const genga_params *p, double dt, void *ws, voi
  *   Kick(dt/2) with the same rc.
  * pairs (nullable) receives the list of the first half kick.  Unless
  * GENGA_FLAG_NOSYNC, synchronises the stream and returns the status.  With
- * GENGA_MIXED, systems below 8,192 bodies take the binary64 kick, which is
- * faster there, unless p->ipt, p->slices or a form flag is set.
+ * GENGA_MIXED, systems below GENGA_MIXED_STEP_MIN bodies take the binary64
+ * kick, which is faster there.
  *
  * Symplectic levels (p->slevels = L > 1; Sect. 6.2 and Appendix A): the
  * bodies of the level-0 list E_0 are not drifted for dt; from their state

@@ -48,13 +48,16 @@ class _Runner:
             # the adjoint covers the base step's operators only
             raise N.GengaError(N.E_UNSUPPORTED, "adjoint of a step with GR, levels, the direct "
                                "solver or test particles")
-        flags = N.FLAG_NOSYNC
-        if cfg.precision == N.MIXED and n < 8192:
-            # genga_step would take the binary64 kick here: name the default
-            # form, so that the forward pass runs the kicks that the backward
-            # pass recomputes
-            flags |= N.FLAG_DIRECTED
-        self.cfg = _Fixed(**{**cfg.__dict__, "flags": flags, "events": (None,) * 4})
+        flags, precision = N.FLAG_NOSYNC, cfg.precision
+        if precision == N.MIXED and n < N.MIXED_STEP_MIN:
+            # genga_step takes the binary64 kick here unless the caller sets the
+            # kick's form or shape; every operator of the pass takes the same
+            if cfg.ipt or cfg.slices or cfg.flags & (N.FLAG_DIRECTED | N.FLAG_SYMMETRIC):
+                flags |= N.FLAG_DIRECTED
+            else:
+                precision = N.FP64
+        self.cfg = _Fixed(**{**cfg.__dict__, "flags": flags, "precision": precision,
+                             "events": (None,) * 4})
         self.ws = N.Workspace(n, self.cfg, device=device)
         self.h = 0.5 * cfg.dt
 

@@ -22,12 +22,6 @@ static int hip_fail(hipError_t e)
     return GENGA_E_HIP;
 }
 
-// Mixed-precision steps take the binary64 kick below this many bodies, where it
-// is the row-group kick: the tiled mixed kick, its reduction and the binary64
-// refinement of cancelling rows take 13 launches (step, us, mixed / binary64:
-// 2,048 bodies 103 / 35, 5,000 160 / 73).
-constexpr int64_t MIXED_STEP_MIN = SYM_MIN_N;
-
 static bool is_fin(double v) { return isfinite(v); }
 
 static int check_bodies(const genga_bodies *b, bool need_v, bool need_rc)
@@ -423,10 +417,13 @@ int genga_step(genga_bodies *b, const genga_params *p, genga_pairs *pairs, void 
     const bool gr = p->c_light > 0.0;
     if (levels && p->tp_mode != 0) return GENGA_E_UNSUPPORTED;
     if (gr && (levels || p->tp_mode != 0)) return GENGA_E_UNSUPPORTED;
-    // Below MIXED_STEP_MIN bodies the binary64 kick is the faster one (its
-    // workspace is the same), unless the caller sets the kick's form or shape.
+    // Below GENGA_MIXED_STEP_MIN bodies the binary64 kick is the row-group kick
+    // and the faster one, by its launches: the tiled mixed kick, its reduction
+    // and the binary64 refinement of cancelling rows take 13 (step, us, mixed /
+    // binary64: 2,048 bodies 103 / 35, 5,000 160 / 73).  Its workspace is the
+    // same.
     genga_params fast;
-    if (p->precision == GENGA_MIXED && b->n < MIXED_STEP_MIN && p->ipt == 0 && p->slices == 0 &&
+    if (p->precision == GENGA_MIXED && b->n < GENGA_MIXED_STEP_MIN && p->ipt == 0 && p->slices == 0 &&
         !(p->flags & (GENGA_FLAG_DIRECTED | GENGA_FLAG_SYMMETRIC))) {
         fast = *p;
         fast.precision = GENGA_FP64;

@@ -32,6 +32,7 @@ MIXED = 1
 FLAG_NOSYNC = 1
 FLAG_DIRECTED = 2     # binary64 kick: one-sided form at any n
 FLAG_SYMMETRIC = 4    # binary64 kick: symmetric form at any n
+MIXED_STEP_MIN = 8192   # genga_step: MIXED takes the binary64 kick below (GENGA_MIXED_STEP_MIN)
 
 _c_double_p = ctypes.c_void_p
 

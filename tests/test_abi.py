@@ -225,3 +225,17 @@ def test_kick_static_host_checks():
         assert lib.genga_workspace_bytes(n, ctypes.byref(p)) > (96 << 20)
         assert lib.genga_kick_static(ctypes.byref(b), ctypes.byref(p), 0.0, None, None, None, None,
                                      fake, None) == native.E_SCRATCH
+
+
+def test_mixed_step_limit_on_host():
+    # the binding's limit is the header's, and a workspace sized for the mixed
+    # kick holds the binary64 one that genga_step runs below it
+    from paper_2201_10058_amd import native
+    lib = native.load()
+    limit = int(re.search(r"#define GENGA_MIXED_STEP_MIN (\d+)", open(HEADER).read()).group(1))
+    assert native.MIXED_STEP_MIN == limit
+    for kw in ({}, dict(c_light=173.1), dict(direct=1, level_capacity=64),
+               dict(slevels=3, substeps=2, level_capacity=1 << 12, direct=1)):
+        for n in (1, 2, 128, 129, 255, 257, 1000, 4097, limit - 1):
+            a, b = (native.Config(G=2.959e-4, precision=q, **kw).params() for q in (native.FP64, native.MIXED))
+            assert lib.genga_workspace_bytes(n, ctypes.byref(a)) == lib.genga_workspace_bytes(n, ctypes.byref(b))

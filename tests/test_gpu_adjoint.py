@@ -263,3 +263,51 @@ def test_fd_directions_disk4096_200_steps(dev):
         worst = max(worst, rel)
         _say(f"dir {k}: adjoint {ad:.10e} fd {fd:.10e} rel {rel:.2e}")
     assert worst <= 1e-5
+
+
+@pytest.mark.parametrize("n,steps", [(48, 12), (700, 4)])
+def test_mixed_simulate_follows_the_step(dev, n, steps):
+    # below MIXED_STEP_MIN bodies genga_step takes the binary64 kick: the
+    # trajectory is that of repeated steps, bit for bit, and the gradient that
+    # of the same map, which for 48 bodies autograd gives (bound as above)
+    d = _small_disk(n, seed=13)
+    cfg = N.Config(G=G, precision=N.MIXED)
+    rng = np.random.default_rng(3)
+    wX, wV = (torch.tensor(rng.normal(size=(3, n)), device="cuda") for _ in range(2))
+    grads = []
+    for c in (cfg, N.Config(G=G)):
+        X, V, m = (t.requires_grad_(True) for t in _torch_dev(d))
+        XT, VT = A.simulate(X, V, m, steps, c, checkpoint_every=5)
+        grads.append(torch.autograd.grad((XT * wX).sum() + (VT * wV).sum(), (X, V, m)))
+        st = _gpu_state(d)
+        ws = N.Workspace(n, c)
+        for _ in range(steps):
+            assert N.step(st, c, ws) == N.OK
+        for k, row in zip(("x", "y", "z", "vx", "vy", "vz"), (*XT.detach(), *VT.detach())):
+            assert torch.equal(st.t[k], row), k
+    for a, b in zip(*grads):
+        assert torch.equal(a, b)
+    if n == 48:
+        x, v, mm = T.state_tensors(d, requires_grad=True)
+        xT, vT = T.simulate(x, v, mm, steps, G, 1.0, 6.0, 3.0, 0.4)
+        Lr = (xT * wX.cpu().T).sum() + (vT * wV.cpu().T).sum()
+        ref = torch.autograd.grad(Lr, (x, v, mm))
+        e = [_rel(g.cpu().numpy().T, r.numpy()) for g, r in zip(grads[0], ref)]
+        _say("mixed trajectory gradient rel errors (x, v, m)", e)
+        assert max(e) < 1e-9
+
+
+@pytest.mark.parametrize("kw", [dict(flags=N.FLAG_DIRECTED), dict(flags=N.FLAG_SYMMETRIC), dict(ipt=2),
+                                dict(slices=3)])
+def test_mixed_simulate_keeps_a_kick_that_is_named(dev, kw):
+    # with the kick's form or shape set genga_step keeps the mixed kick, and so
+    # does the trajectory: binary32 rounding shows against the binary64 one
+    n = 700
+    d = _small_disk(n, seed=13)
+    out = []
+    for prec in (N.MIXED, N.FP64):
+        with torch.no_grad():
+            X, _ = A.simulate(*_torch_dev(d), 3, N.Config(G=G, precision=prec, **kw))
+        out.append(X)
+    assert not torch.equal(out[0], out[1])
+    assert (out[0] - out[1]).abs().max() <= 1e-9 * out[1].abs().max()
