@@ -1527,6 +1527,7 @@ __device__ __forceinline__ void bs_lanes(const BsDev &a, double (*irc)[GROUP_BLO
             P.R = a.radius ? a.radius[b] : 0.0;
             for (int l = 0; l < a.nlev; ++l) irc[l][threadIdx.x] = rcp_radius(a.rc[l][b]);
         }
+        wave_sync_lds();   // the partners' lanes read these
         const bool failed = bs_run(a, P, y);
         if (failed && u == 0) atomicOr(a.status, ST_NOCONV);
         if (u < g) {
