@@ -188,9 +188,16 @@ __global__ __launch_bounds__(256) void k_kick_rows(RowsDev a)
     }
 }
 
-// The encounter list from the rows' counts, lists and bitmaps: block `blk` writes the
-// pairs of rows [256 blk, 256 blk + 256); every block adds the counts before
-// its rows itself.  The last block writes the true number of pairs.
+// The encounter list from the rows' counts, lists and bitmaps: the blocks
+// `blk` + nblk * part write the pairs of rows [256 blk, 256 blk + 256); every
+// block adds the counts before its rows itself.  Part 0 writes the rows with a
+// list and, in the last block, the true number of pairs; a row with a bitmap,
+// whose words its wave takes one after another, is one wave's of all parts (kick
+// of 4,096 bodies with about 20 / 160 partners each: 197 / 527 us with one
+// part, 50 / 75 with 16, 39 / 54 with 64; few pairs: no difference).
+constexpr int ROWS_PARTS = 64;
+static_assert(ROWS_PARTS * (RB / 64) == RB, "a wave per row");
+
 struct RowsPairs {
     const int32_t *cnt, *seg;
     const uint64_t *bits;
@@ -204,25 +211,29 @@ struct RowsPairs {
 struct RowsPairsSmem {
     int64_t scan[RB / 64];
     int64_t pos[RB];
+    int32_t cnt[RB];
 };
 
-__device__ __forceinline__ void pairs_rows_block(const RowsPairs &d, int blk, RowsPairsSmem &sm)
+__device__ __forceinline__ void pairs_rows_block(const RowsPairs &d, int slot, RowsPairsSmem &sm)
 {
     const int tid = threadIdx.x, lane = tid & 63;
+    const int blk = slot % d.nblk, part = slot / d.nblk;
     const int row0 = blk * RB, i = row0 + tid;
+    const int32_t c = i < d.n ? d.cnt[i] : 0;
+    if (part > 0 && !__syncthreads_or(c > ROWS_SEG)) return;
     int64_t before = 0, base, own;
     for (int k = tid; k < row0; k += RB) before += d.cnt[k];
     (void)block_excl_scan<RB>(before, &base, sm.scan);
-    const int32_t c = i < d.n ? d.cnt[i] : 0;
     const int64_t off = block_excl_scan<RB>(c, &own, sm.scan);
     sm.pos[tid] = base + off;
-    if (blk == d.nblk - 1 && tid == 0) {
+    sm.cnt[tid] = c;
+    if (part == 0 && blk == d.nblk - 1 && tid == 0) {
         *d.count = base + own;
         if (base + own > d.capacity) atomicOr(d.status, ST_OVERFLOW);
     }
     __syncthreads();
     // few pairs: the row's thread copies them (their loads in flight together)
-    if (c > 0 && c <= ROWS_SEG) {
+    if (part == 0 && c > 0 && c <= ROWS_SEG) {
 #pragma unroll
         for (int e = 0; e < ROWS_SEG; ++e) {
             if (e >= c) continue;
@@ -233,28 +244,25 @@ __device__ __forceinline__ void pairs_rows_block(const RowsPairs &d, int blk, Ro
             }
         }
     }
-    uint64_t rows = __ballot(c > ROWS_SEG);
-    while (rows) {
-        const int t = (tid & ~63) + __ffsll((unsigned long long)rows) - 1;
-        rows &= rows - 1;
-        const int r = row0 + t;
-        int64_t pos = sm.pos[t];
-        for (int k0 = 0; k0 < d.nw; k0 += 64) {
-            const uint64_t word = k0 + lane < d.nw ? d.bits[(size_t)r * d.nw + k0 + lane] : 0;
-            uint64_t some = __ballot(word != 0);
-            while (some) {
-                const int k = __ffsll((unsigned long long)some) - 1;
-                some &= some - 1;
-                const uint64_t b = __shfl(word, k);
-                if ((b >> lane) & 1) {
-                    const int64_t p = pos + __popcll(b & lanemask_lt());
-                    if (p < d.capacity) {
-                        d.pi[p] = r;
-                        d.pj[p] = (k0 + k) * 64 + lane;
-                    }
+    const int t = part * (RB / 64) + __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (sm.cnt[t] <= ROWS_SEG) return;
+    const int r = row0 + t;
+    int64_t pos = sm.pos[t];
+    for (int k0 = 0; k0 < d.nw; k0 += 64) {
+        const uint64_t word = k0 + lane < d.nw ? d.bits[(size_t)r * d.nw + k0 + lane] : 0;
+        uint64_t some = __ballot(word != 0);
+        while (some) {
+            const int k = __ffsll((unsigned long long)some) - 1;
+            some &= some - 1;
+            const uint64_t b = __shfl(word, k);
+            if ((b >> lane) & 1) {
+                const int64_t p = pos + __popcll(b & lanemask_lt());
+                if (p < d.capacity) {
+                    d.pi[p] = r;
+                    d.pj[p] = (k0 + k) * 64 + lane;
                 }
-                pos += __popcll(b);
             }
+            pos += __popcll(b);
         }
     }
 }
@@ -295,7 +303,7 @@ __global__ __launch_bounds__(RB) void k_hc_apply_rows(double *x, double *y, doub
 // Blocks [0, nb): HC(h) with the row groups' momentum hc_in, the Kepler drift,
 // the drifted positions to xs (the next kick reads them there and writes the
 // state's after its Sun kick) and the momentum of 256 bodies to hc_out.
-// Blocks [nb, 2 nb): the encounter list of the kick before, meanwhile.
+// The blocks behind them: the encounter list of the kick before, meanwhile.
 __global__ __launch_bounds__(RB) void k_hc_drift_rows(const double *x, const double *y,
                                                       const double *z, double *vx, double *vy,
                                                       double *vz, const double *m, int64_t n,
@@ -627,7 +635,8 @@ hipError_t launch_kick_rows(const KickLaunch &k, const Layout &L, char *ws, hipS
 {
     hipError_t e = launch_rows(k, L, ws, nullptr, s);
     if (e != hipSuccess || !k.pairs || k.n <= ONE_MAX) return e;
-    hipLaunchKernelGGL(k_pairs_rows, dim3((unsigned)L.nb), dim3(RB), 0, s, rows_pairs(k, L, ws));
+    hipLaunchKernelGGL(k_pairs_rows, dim3((unsigned)(L.nb * ROWS_PARTS)), dim3(RB), 0, s,
+                       rows_pairs(k, L, ws));
     return hipGetLastError();
 }
 
@@ -676,8 +685,8 @@ hipError_t launch_step_rows(KickLaunch &k, genga_bodies *b, const genga_params *
     k.ev0 = p->prof_events[0];
     k.ev1 = p->prof_events[1];
     if ((e = launch_rows(k, L, ws, mom, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_hc_drift_rows, dim3((unsigned)(k.pairs ? 2 * L.nb : L.nb)), dim3(RB), 0, s,
-                       b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->n, mom, h, p->m_star,
+    hipLaunchKernelGGL(k_hc_drift_rows, dim3((unsigned)(k.pairs ? L.nb * (1 + ROWS_PARTS) : L.nb)),
+                       dim3(RB), 0, s, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->n, mom, h, p->m_star,
                        p->G * p->m_star, p->dt, xs, xs + L.npad, xs + 2 * L.npad, mom2,
                        (int32_t *)(ws + L.status), (int)L.nb, rows_pairs(k, L, ws));
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -182,3 +182,32 @@ def test_results_over_their_inputs(dev):
     for k in ("x", "y", "z", "m", "rc"):
         size = max(np.abs(res[0][k] - base[k]).max(), 1.0)
         assert np.abs(res[1][k] - res[0][k]).max() <= 8e-11 * size, k
+
+
+@pytest.mark.parametrize("n, k", [(200, 15), (200, 16), (300, 17), (513, 100), (2050, 40)])
+def test_lists_of_rows_with_many_pairs(dev, n, k):
+    # rows of up to 16 pairs go through a list, longer ones through the bitmap,
+    # a wave each; on a ring of k neighbours most rows have k.  Also with a
+    # capacity that ends inside a row: the list's start and the true count
+    d = W.make_ring(n, neighbours=k)
+    cfg = N.Config(G=G)
+    ws = N.Workspace(n, cfg)
+    oi, oj, cnt = oracle.pairs(d["x"], d["y"], d["z"], d["rc"], cap=n * n)
+    assert cnt == n * k
+    for cap in (cnt, cnt - k // 2, 0):
+        st = N.State.from_numpy(d)
+        pl = N.PairList(cap)
+        N.kick(st, cfg, ws, 0.0, acc=True, pairs=pl)
+        assert N.read_status(ws) == (N.OK if cap == cnt else N.E_OVERFLOW)
+        pi, pj, c = pl.result()
+        assert c == cnt and np.array_equal(pi, oi[:cap]) and np.array_equal(pj, oj[:cap])
+    # in a step, where the drift's launch writes the list
+    ring = W.make_bs_ring(n, neighbours=k)
+    cfg = N.Config(G=ring["G"], m_star=1.0, dt=ring["dt"], n1=ring["n1"], n2=0.0)
+    st = N.State.from_numpy(ring)
+    pl = N.PairList(cnt)
+    assert N.step(st, cfg, N.Workspace(n, cfg), pl) == N.OK
+    rc = st.t["rc"].cpu().numpy()
+    oi, oj, cnt = oracle.pairs(ring["x"], ring["y"], ring["z"], rc, cap=n * n)
+    pi, pj, c = pl.result()
+    assert c == cnt and np.array_equal(pi, oi[:cnt]) and np.array_equal(pj, oj[:cnt])
