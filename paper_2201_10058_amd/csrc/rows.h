@@ -5,11 +5,13 @@
 // sit in scalar registers (8 rows needed more of them than there are).  A lane
 // loads 5 values per column (the next column's while it works on this one's)
 // and evaluates 4 independent pairs, so no column is staged.
-// Pairs inside the critical radius are only marked in an LDS bitmap
-// (row x column) and leave no term in the loop; afterwards the words of a row
-// are shared out over a wave's lanes, which evaluate the marked pairs side by
-// side.  The bitmap, masked to j > i, is also the encounter list of the rows
-// in canonical order.  The self pair (r^2 = 0) reaches the marking branch like a
+// Pairs inside the critical radius are marked in an LDS bitmap (row x column).
+// Where a word of 64 columns has fewer than ROWS_CROWD of them they leave no
+// term in the loop; afterwards the words of a row are shared out over a wave's
+// lanes, which evaluate their pairs side by side, one after another within a
+// word.  A crowded word (neighbours in index, or a dense system) is evaluated
+// in the loop by the whole wave.  The bitmap, masked to j > i, is also the
+// encounter list of the rows in canonical order.  The self pair (r^2 = 0) reaches the marking branch like a
 // close pair and is dropped there: once per row, in one wave.
 // Every sum runs in a fixed order that does not depend on the launch.
 #pragma once
@@ -35,6 +37,17 @@ inline bool arrays_overlap(const double *const (&out)[NO], const double *const (
 struct RowsCols {
     const double *x, *y, *z, *m, *rc;
 };
+
+// Marked columns of a word from which on the wave evaluates them in the loop.
+// Left for the lanes, each one more in a word is another chain of gathers and
+// estimates for its row's wave; in the loop a word costs the wave one evaluation
+// however many it has.  Kick, us, with 3 / 4 / 6 / 10: 8,191 bodies of about 650
+// scattered partners 207 / 188 / 164 / 154, a ring of 2,048 with 8 index
+// neighbours on each side 18.3 / 17.9 / 18.7 / 19.5, all 200 bodies in reach
+// 13.3 / 14.1 / 13.6 / 16.0.  With all words left for the lanes the ring took
+// 24.6 (32 neighbours: 54, now 18; 8,000 bodies: 143, now 73) and 8,191 bodies
+// all in reach 849, now 265.
+constexpr int ROWS_CROWD = 6;
 
 // LDS of one team.
 struct RowsTeam {
@@ -84,6 +97,14 @@ __device__ __forceinline__ double row16_sum(double v)
 
 static_assert(ROWS_G == 4, "12 sums: two halvings leave 3 per row of 16 lanes, one row group per wave");
 
+// m K / r^3 of a pair inside its critical radius.
+__device__ __forceinline__ double close_weight(double r2, double rho2, double m)
+{
+    const double yc = rsq_full(r2), irho = rsq_full(rho2);
+    const double K = changeover_of_y(__builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0));
+    return (m * K) * (yc * yc * yc);
+}
+
 // One column against the rows.
 __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROWS_G],
                                             const double (&yi)[ROWS_G], const double (&zi)[ROWS_G],
@@ -109,6 +130,7 @@ __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROW
     }
     // rare: some lane has a row inside the larger of the rows' and its own radius
     if (__any(near <= vmax_f64(rg, rc2j))) {
+        unsigned crowded = 0;
 #pragma unroll
         for (int q = 0; q < ROWS_G; ++q) {
             const double rho2 = vmax_f64(rc2i[q], rc2j);
@@ -119,7 +141,24 @@ __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROW
             if (same && j < n && j != r0 + q) bad |= ST_NONFINITE;
             if (inside || same) sc[q] = 0.0;
             const uint64_t mask = __ballot(inside);
-            if (mask && lane == 0) sm.bits[q][word] = mask;
+            if (mask) {
+                if (lane == 0) sm.bits[q][word] = mask;
+                if (__popcll(mask) >= ROWS_CROWD) crowded |= 1u << q;
+            }
+        }
+        // (one copy of the evaluation for the rows, whose data come from LDS)
+        while (crowded) {
+            const int row = __builtin_ctz(crowded);
+            crowded &= crowded - 1;
+            const double *ri = sm.row[row];
+            const double ex = xj - ri[0], ey = yj - ri[1], ez = zj - ri[2];
+            const double e2 = __builtin_fma(ez, ez, __builtin_fma(ey, ey, ex * ex));
+            const double rho2 = rho2_of(ri[3], rcj);
+            const double w = close_weight(e2, rho2, mj);
+            const bool inside = e2 < rho2 && e2 != 0.0 && j < n;
+#pragma unroll
+            for (int q = 0; q < ROWS_G; ++q)
+                if (q == row && inside) sc[q] = w;
         }
     }
 #pragma unroll
@@ -223,17 +262,14 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
             const uint64_t after = first <= 0 ? b : (first > 63 ? 0 : b & (~0ull << first));
             sm.bits[q][k] = after;
             cnt += __popcll(after);
+            if (__popcll(b) >= ROWS_CROWD) continue;   // in the sums already
             const double Xi = sm.row[q][0], Yi = sm.row[q][1], Zi = sm.row[q][2], ri = sm.row[q][3];
             while (b) {
                 const int j = k * 64 + __ffsll((unsigned long long)b) - 1;
                 b &= b - 1;
                 const double dx = c.x[j] - Xi, dy = c.y[j] - Yi, dz = c.z[j] - Zi;
                 const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-                const double yc = rsq_full(r2);
-                const double irho = rsq_full(rho2_of(ri, c.rc[j]));
-                const double K =
-                    changeover_of_y(__builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0));
-                const double wk = (c.m[j] * K) * (yc * yc * yc);
+                const double wk = close_weight(r2, rho2_of(ri, c.rc[j]), c.m[j]);
                 sx = __builtin_fma(dx, wk, sx);
                 sy = __builtin_fma(dy, wk, sy);
                 sz = __builtin_fma(dz, wk, sz);

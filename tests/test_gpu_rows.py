@@ -211,3 +211,46 @@ def test_lists_of_rows_with_many_pairs(dev, n, k):
     oi, oj, cnt = oracle.pairs(ring["x"], ring["y"], ring["z"], rc, cap=n * n)
     pi, pj, c = pl.result()
     assert c == cnt and np.array_equal(pi, oi[:cnt]) and np.array_equal(pj, oj[:cnt])
+
+
+def _crowded(n, partners, seed):
+    """A cloud whose bodies have about `partners` partners each, close in index
+    as in space (sorted along x), so that words of 64 columns hold from none to
+    all of a row's partners."""
+    d = W.random_cloud(n, seed=seed)
+    order = np.argsort(d["x"])
+    for k in ("x", "y", "z", "m"):
+        d[k] = np.ascontiguousarray(d[k][order])
+    for k in ("y", "z"):
+        d[k] *= 0.3 * partners / n
+    d["rc"] = np.random.default_rng(seed).uniform(0.7, 1.4, n) * partners / n
+    return d
+
+
+CROWDED = [(129, 5), (129, 200), (300, 6), (300, 40), (2050, 4), (2050, 7), (2050, 60), (8191, 30)]
+
+
+@pytest.mark.parametrize("n, partners", CROWDED)
+def test_crowded_words(dev, n, partners):
+    # words below and above the number of marked columns from which the wave
+    # evaluates them in the loop, in one system
+    d = _crowded(n, partners, seed=n + partners)
+    oi, oj, cnt = oracle.pairs(d["x"], d["y"], d["z"], d["rc"], cap=n * n // 2 + 1)
+    words = np.bincount((np.concatenate([oi, oj]).astype(np.int64) * 256 +
+                         np.concatenate([oj, oi]) // 64))
+    if partners < 100:
+        assert words[words > 0].min() < 6
+    assert words.max() >= 6
+    st = N.State.from_numpy(d)
+    cfg = N.Config(G=G)
+    ws = N.Workspace(n, cfg)
+    pl = N.PairList(cnt)
+    a = N.kick(st, cfg, ws, 0.0, acc=True, pairs=pl).cpu().numpy()
+    assert N.read_status(ws) == N.OK
+    pi, pj, c = pl.result()
+    assert c == cnt and np.array_equal(pi, oi[:cnt]) and np.array_equal(pj, oj[:cnt])
+    ax, ay, az, code = oracle.kick_acc(d["x"], d["y"], d["z"], d["m"], d["rc"], G, precise=True)
+    assert code == 0
+    ref = np.stack([ax, ay, az])
+    size = np.linalg.norm(ref, axis=0)
+    assert np.max(np.linalg.norm(a - ref, axis=0) / np.where(size > 0, size, 1.0)) <= TOL
