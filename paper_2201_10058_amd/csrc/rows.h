@@ -5,14 +5,14 @@
 // sit in scalar registers (8 rows needed more of them than there are).  A lane
 // loads 5 values per column (the next column's while it works on this one's)
 // and evaluates 4 independent pairs, so no column is staged.
-// Pairs inside the critical radius are marked in an LDS bitmap (row x column).
-// Where a word of 64 columns has fewer than ROWS_CROWD of them they leave no
-// term in the loop; afterwards the words of a row are shared out over a wave's
-// lanes, which evaluate their pairs side by side, one after another within a
-// word.  A crowded word (neighbours in index, or a dense system) is evaluated
-// in the loop by the whole wave.  The bitmap, masked to j > i, is also the
-// encounter list of the rows in canonical order.  The self pair (r^2 = 0) reaches the marking branch like a
-// close pair and is dropped there: once per row, in one wave.
+// Pairs inside the critical radius are marked in an LDS bitmap (row x column) and
+// leave no term in the loop.  Afterwards a row's wave evaluates them: its words of
+// 64 columns with at least ROWS_CROWD of them (neighbours in index, or a dense
+// system) one after another, a pair per lane, its other words side by side, one
+// or two per lane, whose pairs follow each other.  The bitmap, masked to j > i,
+// is also the encounter list of the rows in canonical order.  The self pair
+// (r^2 = 0) reaches the marking branch like a close pair and is dropped there:
+// once per row, in one wave.
 // Every sum runs in a fixed order that does not depend on the launch.
 #pragma once
 
@@ -38,16 +38,16 @@ struct RowsCols {
     const double *x, *y, *z, *m, *rc;
 };
 
-// Marked columns of a word from which on the wave evaluates them in the loop.
-// Left for the lanes, each one more in a word is another chain of gathers and
-// estimates for its row's wave; in the loop a word costs the wave one evaluation
-// however many it has.  Kick, us, with 3 / 4 / 6 / 10: 8,191 bodies of about 650
-// scattered partners 207 / 188 / 164 / 154, a ring of 2,048 with 8 index
-// neighbours on each side 18.3 / 17.9 / 18.7 / 19.5, all 200 bodies in reach
-// 13.3 / 14.1 / 13.6 / 16.0.  With all words left for the lanes the ring took
-// 24.6 (32 neighbours: 54, now 18; 8,000 bodies: 143, now 73) and 8,191 bodies
-// all in reach 849, now 265.
-constexpr int ROWS_CROWD = 6;
+// Marked columns of a word from which on its row's wave takes it by itself, a
+// pair per lane: such a word costs the wave one evaluation however many columns it
+// has, while left to a lane each column is another chain of gathers and
+// estimates.  Kick / VJP, us, with 4 / 6 / 10 / 16: 8,191 bodies of about 650
+// scattered partners 224, 191, 155, 155 / 312, 254, 195, 193; a ring of 2,048 with
+// 8 index neighbours on each side 18.0, 19.0, 19.8, 22.1 / 17.0, 17.2, 20.0, 22.6;
+// 2,048 bodies that all meet 34, 34, 35, 38 / 38, 39, 40, 44.  With every word
+// left to the lanes: ring of 32 neighbours 88 / 77 (now 19 / 20), 8,191 bodies that
+// all meet 849 / 1,290 (278 / 388).
+constexpr int ROWS_CROWD = 10;
 
 // LDS of one team.
 struct RowsTeam {
@@ -97,6 +97,36 @@ __device__ __forceinline__ double row16_sum(double v)
 
 static_assert(ROWS_G == 4, "12 sums: two halvings leave 3 per row of 16 lanes, one row group per wave");
 
+// The crowded words of a row of the bitmap (nw <= ROWS_MAX / 64 words; all lanes
+// of a wave pass): eval(j, column) by every lane whose column j = 64 k + lane is
+// marked in such a word k, the words in order; the next one's columns are loaded
+// meanwhile.
+template <class Load, class Eval>
+__device__ __forceinline__ void crowded_words(const uint64_t *bits, int nw, Load load, Eval eval)
+{
+    static_assert(ROWS_MAX / 64 <= 128, "two words a lane");
+    const int lane = threadIdx.x & 63;
+    auto pick = [&](int k) { return __ballot(k < nw && __popcll(bits[k < nw ? k : 0]) >= ROWS_CROWD); };
+    uint64_t todo[2] = {pick(lane), nw > 64 ? pick(64 + lane) : 0};
+    auto next = [&]() {
+        const int h = todo[0] == 0;
+        if (!todo[h]) return -1;
+        const int k = __builtin_ctzll(todo[h]);
+        todo[h] &= todo[h] - 1;
+        return 64 * h + k;
+    };
+    int k = next();
+    if (k < 0) return;
+    auto cur = load(64 * k + lane);
+    while (k >= 0) {
+        const int kn = next();
+        const auto nx = load(64 * (kn < 0 ? k : kn) + lane);
+        if ((bits[k] >> lane) & 1) eval(64 * k + lane, cur);
+        cur = nx;
+        k = kn;
+    }
+}
+
 // m K / r^3 of a pair inside its critical radius.
 __device__ __forceinline__ double close_weight(double r2, double rho2, double m)
 {
@@ -130,7 +160,6 @@ __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROW
     }
     // rare: some lane has a row inside the larger of the rows' and its own radius
     if (__any(near <= vmax_f64(rg, rc2j))) {
-        unsigned crowded = 0;
 #pragma unroll
         for (int q = 0; q < ROWS_G; ++q) {
             const double rho2 = vmax_f64(rc2i[q], rc2j);
@@ -141,24 +170,7 @@ __device__ __forceinline__ void rows_column(RowsTeam &sm, const double (&xi)[ROW
             if (same && j < n && j != r0 + q) bad |= ST_NONFINITE;
             if (inside || same) sc[q] = 0.0;
             const uint64_t mask = __ballot(inside);
-            if (mask) {
-                if (lane == 0) sm.bits[q][word] = mask;
-                if (__popcll(mask) >= ROWS_CROWD) crowded |= 1u << q;
-            }
-        }
-        // (one copy of the evaluation for the rows, whose data come from LDS)
-        while (crowded) {
-            const int row = __builtin_ctz(crowded);
-            crowded &= crowded - 1;
-            const double *ri = sm.row[row];
-            const double ex = xj - ri[0], ey = yj - ri[1], ez = zj - ri[2];
-            const double e2 = __builtin_fma(ez, ez, __builtin_fma(ey, ey, ex * ex));
-            const double rho2 = rho2_of(ri[3], rcj);
-            const double w = close_weight(e2, rho2, mj);
-            const bool inside = e2 < rho2 && e2 != 0.0 && j < n;
-#pragma unroll
-            for (int q = 0; q < ROWS_G; ++q)
-                if (q == row && inside) sc[q] = w;
+            if (mask && lane == 0) sm.bits[q][word] = mask;
         }
     }
 #pragma unroll
@@ -248,12 +260,25 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
         if ((lane & 15) == 0) sm.part[w][(lane >> 4) * 3 + k] = s;
     }
     __syncthreads();
-    // marked pairs: wave w takes row w, a lane the words l, l + 64
+    // marked pairs: wave w takes row w, first its crowded words, then a lane the
+    // words l, l + 64 of the others
     {
         const int q = w, i = r0 + w < n ? r0 + w : n - 1;
+        const double Xi = sm.row[q][0], Yi = sm.row[q][1], Zi = sm.row[q][2], ri = sm.row[q][3];
         double sx = 0.0, sy = 0.0, sz = 0.0;
         int cnt = 0;
         bool seen = false;
+        auto pair = [&](const RowsColumn &v) {
+            const double dx = v.x - Xi, dy = v.y - Yi, dz = v.z - Zi;
+            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+            const double wk = close_weight(r2, rho2_of(ri, v.rc), v.m);
+            sx = __builtin_fma(dx, wk, sx);
+            sy = __builtin_fma(dy, wk, sy);
+            sz = __builtin_fma(dz, wk, sz);
+        };
+        crowded_words(
+            sm.bits[q], nw, [&](int j) { return rows_load(c, n, j); },
+            [&](int, const RowsColumn &v) { pair(v); });
         for (int k = lane; k < nw; k += 64) {
             uint64_t b = sm.bits[q][k];
             if (!b) continue;
@@ -262,17 +287,10 @@ __device__ __forceinline__ void rows_team(const RowsCols &c, int n, int r0, int 
             const uint64_t after = first <= 0 ? b : (first > 63 ? 0 : b & (~0ull << first));
             sm.bits[q][k] = after;
             cnt += __popcll(after);
-            if (__popcll(b) >= ROWS_CROWD) continue;   // in the sums already
-            const double Xi = sm.row[q][0], Yi = sm.row[q][1], Zi = sm.row[q][2], ri = sm.row[q][3];
+            if (__popcll(b) >= ROWS_CROWD) continue;
             while (b) {
-                const int j = k * 64 + __ffsll((unsigned long long)b) - 1;
+                pair(rows_load(c, n, k * 64 + __ffsll((unsigned long long)b) - 1));
                 b &= b - 1;
-                const double dx = c.x[j] - Xi, dy = c.y[j] - Yi, dz = c.z[j] - Zi;
-                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-                const double wk = close_weight(r2, rho2_of(ri, c.rc[j]), c.m[j]);
-                sx = __builtin_fma(dx, wk, sx);
-                sy = __builtin_fma(dy, wk, sy);
-                sz = __builtin_fma(dz, wk, sz);
             }
         }
         if (__any(seen)) {

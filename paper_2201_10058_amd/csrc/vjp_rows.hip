@@ -4,7 +4,7 @@
 // rows' adjoints and no sums pass through memory; the tiled form is a kernel of
 // column slices, whose diagonal waves enter the rare path once per column for
 // the self pair, and a reduction.  Pairs inside the critical radius are marked
-// in an LDS bitmap and evaluated afterwards, side by side over the lanes.
+// in an LDS bitmap and evaluated afterwards, as in the kick.
 //
 // Bound by the binary64 vector units: 36 instructions and one v_rsq_f64 per
 // ordered pair, 15 us at 4,096 bodies, whose kernel takes 38 us.  Sums kept as
@@ -14,6 +14,7 @@
 #include "device_common.h"
 #include "genga_internal.h"
 #include "rows.h"
+#include "sym_common.h"
 
 namespace genga {
 
@@ -177,40 +178,48 @@ __global__ __launch_bounds__(256) void k_vjp_rows(VjpRowsDev a)
     }
     __syncthreads();
     {
-        // marked pairs of row w, a lane the words l, l + 64 (in true units)
+        // marked pairs of row w (in true units)
         const int i = r0 + w < n ? r0 + w : n - 1;
         const double *row = sm.row[w];
         const double X = row[0], Y = row[1], Z = row[2], mk = row[3], rck = row[4];
         const double kx = row[5], ky = row[6], kz = row[7];
         double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
         bool seen = false;
+        auto pair = [&](int j, const VjpColumn &v) {
+            const double dx = v.x - X, dy = v.y - Y, dz = v.z - Z;
+            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+            const double jx = a.scale * v.ax, jy = a.scale * v.ay, jz = a.scale * v.az;
+            const double yc = rsq_full(r2), irho = rsq_full(rho2_of(rck, v.rc));
+            const double yc2 = yc * yc, yc3 = yc2 * yc;
+            // K and K' (both by one reciprocal; the clamp gives their values outside
+            // the band)
+            double y = __builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0);
+            y = vmin_f64(vmax_f64(y, 0.0), 1.0);
+            const double yy = y * y, h = rcp_nr2(__builtin_fma(2.0, yy - y, 1.0));
+            const double K = yy * h, Kp = (2.0 * (y - yy)) * (h * h);
+            const double wk = K * yc3;
+            // w_r / r = K' / (0.9 rho r^4) - 3 K / r^5
+            const double wr_r = (Kp * (irho * (1.0 / 0.9))) * (yc2 * yc2) - (3.0 * K) * (yc3 * yc2);
+            const double da = __builtin_fma(dz, jz, __builtin_fma(dy, jy, dx * jx));
+            const double db = __builtin_fma(dz, kz, __builtin_fma(dy, ky, dx * kx));
+            const double du = __builtin_fma(mk, da, -(v.m * db));
+            const double c = wr_r * du;
+            s[0] += __builtin_fma(c, dx, wk * __builtin_fma(mk, jx, -(v.m * kx)));
+            s[1] += __builtin_fma(c, dy, wk * __builtin_fma(mk, jy, -(v.m * ky)));
+            s[2] += __builtin_fma(c, dz, wk * __builtin_fma(mk, jz, -(v.m * kz)));
+            s[3] = __builtin_fma(wk, da, s[3]);
+            const bool owner = rck > v.rc || (rck == v.rc && i < j);
+            if (owner && Kp != 0.0) s[4] += ((Kp * (irho * irho)) * (1.0 / 0.9)) * yc2 * du;
+            seen = true;
+        };
+        crowded_words(sm.bits[w], nw, [&](int j) { return vjp_load(a, j); }, pair);
         for (int k = lane; k < nw; k += 64) {
             uint64_t b = sm.bits[w][k];
-            seen = seen || b != 0;
+            if (__popcll(b) >= ROWS_CROWD) continue;
             while (b) {
                 const int j = k * 64 + __ffsll((unsigned long long)b) - 1;
                 b &= b - 1;
-                const double dx = a.x[j] - X, dy = a.y[j] - Y, dz = a.z[j] - Z;
-                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-                const double mj = a.m[j], rcj = a.rc[j];
-                const double jx = a.scale * a.abx[j], jy = a.scale * a.aby[j], jz = a.scale * a.abz[j];
-                const double yc = rsq_full(r2), irho = rsq_full(rho2_of(rck, rcj));
-                const double yc2 = yc * yc, yc3 = yc2 * yc;
-                double K, Kp;
-                changeover_kdk_of_y(__builtin_fma((r2 * yc) * irho, 1.0 / 0.9, -1.0 / 9.0), K, Kp);
-                const double wk = K * yc3;
-                // w_r / r = K' / (0.9 rho r^4) - 3 K / r^5
-                const double wr_r = (Kp * (irho * (1.0 / 0.9))) * (yc2 * yc2) - (3.0 * K) * (yc3 * yc2);
-                const double da = __builtin_fma(dz, jz, __builtin_fma(dy, jy, dx * jx));
-                const double db = __builtin_fma(dz, kz, __builtin_fma(dy, ky, dx * kx));
-                const double du = __builtin_fma(mk, da, -(mj * db));
-                const double c = wr_r * du;
-                s[0] += __builtin_fma(c, dx, wk * __builtin_fma(mk, jx, -(mj * kx)));
-                s[1] += __builtin_fma(c, dy, wk * __builtin_fma(mk, jy, -(mj * ky)));
-                s[2] += __builtin_fma(c, dz, wk * __builtin_fma(mk, jz, -(mj * kz)));
-                s[3] = __builtin_fma(wk, da, s[3]);
-                const bool owner = rck > rcj || (rck == rcj && i < j);
-                if (owner && Kp != 0.0) s[4] += ((Kp * (irho * irho)) * (1.0 / 0.9)) * yc2 * du;
+                pair(j, vjp_load(a, j));
             }
         }
         if (__any(seen)) {
