@@ -43,6 +43,12 @@ struct TileDesc {
 // slices first, then the narrow ones, those over the groups' own rows last.
 // Wide slices write fewer row sums, narrow ones at the end even out what the
 // compute units have to do (A = d, M = 1: slices of one width).
+// A wave of a narrow tile has room to stage WSEG pairs, of a wide one P WSEG (P
+// at most M): a wave that finds more is computed a second time.  P is the
+// largest with which the whole room is that of 8,192 narrow tiles (50 MB), so
+// that a column of a wide slice has about as much room as slices of one width, of
+// 4,096 tiles, would give it (20,011 bodies of about 100 partners each: kick with
+// list 805 us with P = 1, 379 with 4, 420 with slices of 64 columns).
 constexpr int SYM_NW = 4;
 constexpr int SYM_IPT = 2;
 constexpr int SYM_NT = SYM_NW * 64;
@@ -54,6 +60,7 @@ struct SymShape {
     int64_t S0 = 0;      // narrow slices that group 0 would have (ceil(n / W))
     int W = 0, d = 0;    // columns per narrow slice, slices over a group's own rows
     int A = 0, M = 1;    // narrow slices of a group, width of the wide ones in W
+    int P = 1;           // staging room of a wide tile's waves, in WSEG pairs
     int64_t gl = 0;      // groups with wide slices
     int64_t nb0 = 0;     // wide slices of group 0 (group g < gl: nb0 - g d / M)
     int64_t T = 0;       // tiles
@@ -72,10 +79,10 @@ struct SymShape {
     // columns [c0, c1) of slice s of group g
     __host__ __device__ void cols(int64_t g, int64_t s, int64_t &c0, int64_t &c1) const
     {
-        const bool wide = g < gl && s >= A;
-        const int64_t u = wide ? A + (s - A) * M : s;
+        const bool w = wide(g, s);
+        const int64_t u = w ? A + (s - A) * M : s;
         c0 = g * SYM_RG + u * W;
-        c1 = c0 + (wide ? M * W : W);
+        c1 = c0 + (w ? M * W : W);
         c1 = c1 < n ? c1 : n;
     }
     // column sums of group g: 3 rows of collen(g) doubles from 3 coloff(g)
@@ -86,9 +93,20 @@ struct SymShape {
     }
     // wide tiles before group g
     __host__ __device__ int64_t bf(int64_t g) const { return g * nb0 - (d / M) * ((g * (g - 1)) / 2); }
+    // staging room before tile (g, s) and of one of its waves, in narrow tiles
+    // and in WSEG pairs
+    __host__ __device__ bool wide(int64_t g, int64_t s) const { return g < gl && s >= A; }
+    __host__ __device__ int64_t room(int64_t g, int64_t s) const
+    {
+        const int64_t k = g < gl ? g : gl;
+        return k * A + P * bf(k) + (tb(g) - tb(k)) + (wide(g, s) ? A + (s - A) * P : s);
+    }
+    __host__ __device__ int segs(int64_t g, int64_t s) const { return wide(g, s) ? P : 1; }
     // blocks of a launch (sym_tile): the wide tiles, then A slots per group
     __host__ __device__ int64_t blocks() const { return tfull + G * A; }
 };
+constexpr int SYM_PMAX = 4;
+constexpr int64_t SYM_ROOM = 8192;
 // A = 0: slices of W columns only.
 inline SymShape sym_shape(int64_t n, int W, int A = 0, int M = 1)
 {
@@ -106,6 +124,7 @@ inline SymShape sym_shape(int64_t n, int W, int A = 0, int M = 1)
     }
     h.T = h.tb(h.G);
     h.tfull = h.bf(h.gl);
+    while (h.P * 2 <= M && h.P * 2 <= SYM_PMAX && h.T + (2 * h.P - 1) * h.tfull <= SYM_ROOM) h.P *= 2;
     return h;
 }
 
@@ -149,7 +168,7 @@ hipError_t launch_kick_sym_b(const SymBatch &b, const double *x, const double *y
                              int32_t *status, bool emit, hipStream_t s);
 hipError_t launch_scatter_sym(const SymShape &h, const SymBatch *b, const double *x,
                               const double *y, const double *z, const double *rc,
-                              const int32_t *cnt, const int32_t *stage, const int32_t *wcount,
+                              const int32_t *cnt, int32_t *stage, const int32_t *wcount,
                               const int32_t *rowloc, const int64_t *boff, genga_pairs *pairs,
                               hipStream_t s);
 

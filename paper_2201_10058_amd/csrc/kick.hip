@@ -1447,7 +1447,8 @@ Layout make_layout(int64_t n, const KickCfg &c, int64_t S)
                              5 * symx)
                   : 0;
     size_t sym_cnt = c.use_sym ? (size_t)c.sym.T * SYM_RG : 0;
-    size_t nw = std::max<size_t>((size_t)c.nwaves, c.use_sym ? (size_t)c.sym.T * SYM_NW : 0);
+    size_t nw = std::max<size_t>((size_t)c.nwaves,
+                                 c.use_sym ? (size_t)c.sym.room(c.sym.G, 0) * SYM_NW : 0);
     size_t symb_part = 0;
     if (c.use_symb) {
         symb_part = 3 * ((size_t)c.symb_T * SYM_RG + (size_t)c.symb_cols);

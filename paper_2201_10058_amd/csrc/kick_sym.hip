@@ -52,7 +52,7 @@ struct SymDev {
     double *rowpart;   // [T][ps][SYM_RG]
     double *colpart;   // group g: [ps][collen(g)] from ps coloff(g)
     int32_t *cnt;      // [T][SYM_RG]
-    int32_t *stage;    // [T SYM_NW][WSEG][3]  (i, j, unused)
+    int32_t *stage;    // [room SYM_NW][WSEG][3]  (i, j, unused)
     int32_t *wcount;   // [T SYM_NW]
     int32_t *status;
     int32_t *refine_cnt;   // mixed: rows listed for binary64 evaluation (reset here)
@@ -65,6 +65,23 @@ struct SymDev {
     double widen;      // mixed: squared widening of the binary32 near test
     double far_row, far_col;   // coordinates of padding rows and columns
 };
+
+// Where a wave stages its pairs (in WSEG), and how many at most.
+struct SymStage {
+    int seg, cap;
+    __device__ int32_t *at(int32_t *stage, int pos) const
+    {
+        return stage + ((size_t)seg * WSEG + pos) * 3;
+    }
+};
+
+// The segment of wave w of tile (g, s); `room` narrow tiles of staging before it.
+__device__ __forceinline__ SymStage sym_stage(const SymShape &h, int64_t g, int64_t s, int64_t room,
+                                              int w)
+{
+    const int p = h.segs(g, s);
+    return {(int)room * SYM_NW + w * p, p * WSEG};
+}
 
 // Padding rows and columns sit far away, on opposite sides (no two padding
 // bodies coincide), with mass 0 and critical radius 0: r^2 stays finite (below
@@ -132,7 +149,7 @@ struct SymRows {
 // ensemble's kick, this takes 321.
 __device__ __forceinline__ void sym_near(const SymDev &a, SymRows<false> &R, int q, int jg, double r2,
                                          double yv, double y2, double rc2c, double mc, double &si,
-                                         double &sj, int64_t wave_g, int &nst)
+                                         double &sj, const SymStage &st, int &nst)
 {
     const double rho2 = vmax_f64(R.rc2i[q], rc2c);
     const bool zero = r2 == 0.0;
@@ -157,8 +174,8 @@ __device__ __forceinline__ void sym_near(const SymDev &a, SymRows<false> &R, int
             const uint64_t mask = __ballot(emit);
             if (emit) {
                 const int pos = nst + __popcll(mask & lanemask_lt());
-                if (pos < WSEG) {
-                    int32_t *e3 = a.stage + ((size_t)wave_g * WSEG + pos) * 3;
+                if (pos < st.cap) {
+                    int32_t *e3 = st.at(a.stage, pos);
                     e3[0] = (int32_t)(R.ii[q] + a.o);
                     e3[1] = (int32_t)(jg + a.o);
                 }
@@ -173,7 +190,7 @@ __device__ __forceinline__ void sym_near(const SymDev &a, SymRows<false> &R, int
 // lanes concerned; the same rules.
 __device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<true> &R, int q, int jg,
                                          double r2, double rc2c, double mc, double &si,
-                                         double &sj, int64_t wave_g, int *wcnt)
+                                         double &sj, const SymStage &st, int *wcnt)
 {
     bool emit = false;
     if (jg == R.ii[q]) {
@@ -202,8 +219,8 @@ __device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<true> &R, int 
             const int base = __hip_atomic_load(wcnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             if (emit) {
                 const int pos = base + __popcll(mask & lanemask_lt());
-                if (pos < WSEG) {
-                    int32_t *e3 = a.stage + ((size_t)wave_g * WSEG + pos) * 3;
+                if (pos < st.cap) {
+                    int32_t *e3 = st.at(a.stage, pos);
                     e3[0] = (int32_t)(R.ii[q] + a.o);
                     e3[1] = (int32_t)(jg + a.o);
                 }
@@ -227,7 +244,7 @@ template <bool GEN>
 __device__ __forceinline__ void sym_chunk(const SymDev &a, SymRows<false> &R,
                                           const SymCols<false> &C, int colbase, const int *mode,
                                           double &cx, double &cy, double &cz, double c53,
-                                          double g2, int64_t wave_g, int &nst, int lane)
+                                          double g2, const SymStage &st, int &nst, int lane)
 {
     for (int k0 = 0; k0 < 64; k0 += 2) {
 #pragma unroll
@@ -256,7 +273,7 @@ __device__ __forceinline__ void sym_chunk(const SymDev &a, SymRows<false> &R,
                     asm volatile("" : "+v"(ee));
                     ee += k0 + u;
                     sym_near(a, R, q, colbase + (ee & 63), r2, yv, y2, C.rc2[ee], C.m[ee], si, sj,
-                             wave_g, nst);
+                             st, nst);
                 }
                 R.ax[q] = __builtin_fma(dx, si, R.ax[q]);
                 R.ay[q] = __builtin_fma(dy, si, R.ay[q]);
@@ -288,7 +305,7 @@ __device__ __forceinline__ void sym_chunk_mixed(const SymDev &a, SymRows<true> &
                                                 const SymCols<true> &C, double (*nacc)[64],
                                                 int colbase, const int *mode, float &cx,
                                                 float &cy, float &cz, float &cm, double c15,
-                                                double c1875, int64_t wave_g, int *wcnt, int lane)
+                                                double c1875, const SymStage &st, int *wcnt, int lane)
 {
     for (int k0 = 0; k0 < 64; k0 += 2) {
 #pragma unroll
@@ -326,8 +343,7 @@ __device__ __forceinline__ void sym_chunk_mixed(const SymDev &a, SymRows<true> &
                     const double r3 = __builtin_fma(t3 * e1, pp, t3);
                     double wi = mc * r3, wj = R.mw[q] * r3;
                     if (r2 <= vmax_f64(R.rc2i[q], rc2c))
-                        sym_slow(a, R, q, colbase + (ee & 63), r2, rc2c, mc, wi, wj, wave_g,
-                                       wcnt);
+                        sym_slow(a, R, q, colbase + (ee & 63), r2, rc2c, mc, wi, wj, st, wcnt);
                     R.ax[q] = __builtin_fma(dx, wi, R.ax[q]);
                     R.ay[q] = __builtin_fma(dy, wi, R.ay[q]);
                     R.az[q] = __builtin_fma(dz, wi, R.az[q]);
@@ -418,10 +434,10 @@ __device__ __forceinline__ void sym_colsum(const SymDev &a, const SymSmem<MIXED>
 // moves to scratch are reloaded once per chunk, not per step (unrolling 4
 // steps, or 5 waves per SIMD, spill inside the step loop: 15 % slower).
 // Tile (g, s) of the system described by a (its shape, and for a batch its
-// arrays from its first body on), stored as tile sid.
+// arrays from its first body on), stored as tile sid; room: SymShape::room.
 template <bool MIXED>
 __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t s, int64_t sid,
-                                             SymSmem<MIXED> &sm)
+                                             int64_t room, SymSmem<MIXED> &sm)
 {
     const SymShape &h = a.sh;
     const int tid = threadIdx.x;
@@ -434,6 +450,7 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
     h.cols(g, s, col0, col1);
     const int nch = (int)((col1 - col0 + 63) / 64);
     const int64_t wave_g = sid * SYM_NW + w;
+    const SymStage st = sym_stage(h, g, s, room, w);
     const bool diag = s < h.d;
     const int vzero = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);
     const double c53 = a.c53 + (double)vzero;
@@ -542,10 +559,10 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
             float cx = 0.0f, cy = 0.0f, cz = 0.0f, cm = 0.0f;
             if (full)
                 sym_chunk_mixed<false>(a, R, sm.col[b], sm.nacc[w], colbase, mode, cx, cy, cz, cm,
-                                       c15, c1875, wave_g, wcnt, lane);
+                                       c15, c1875, st, wcnt, lane);
             else
                 sym_chunk_mixed<true>(a, R, sm.col[b], sm.nacc[w], colbase, mode, cx, cy, cz, cm,
-                                      c15, c1875, wave_g, wcnt, lane);
+                                      c15, c1875, st, wcnt, lane);
             // binary32 row sums of the chunk into binary64
 #pragma unroll
             for (int q = 0; q < SYM_IPT; ++q) {
@@ -567,10 +584,10 @@ __device__ __forceinline__ void sym_tile_run(const SymDev &a, int64_t g, int64_t
                 bound_of_hi(max(rg, __builtin_amdgcn_readfirstlane(sm.gmax[b])));
             double cx = 0.0, cy = 0.0, cz = 0.0;
             if (full)
-                sym_chunk<false>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, wave_g, nst,
+                sym_chunk<false>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, st, nst,
                                  lane);
             else
-                sym_chunk<true>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, wave_g, nst,
+                sym_chunk<true>(a, R, sm.col[b], colbase, mode, cx, cy, cz, c53, g2, st, nst,
                                 lane);
             sm.acc[b][0][w][lane] = cx;
             sm.acc[b][1][w][lane] = cy;
@@ -616,7 +633,7 @@ __global__ __launch_bounds__(SYM_NT) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     int64_t g, s;
     sym_tile(a.sh, blockIdx.x, g, s);
     if (s < 0) return;   // (uniform over the block)
-    sym_tile_run<MIXED>(a, g, s, a.sh.tb(g) + s, sm);
+    sym_tile_run<MIXED>(a, g, s, a.sh.tb(g) + s, a.sh.room(g, s), sm);
 }
 
 // Batch: one block per tile, tiles launched in decreasing order of work
@@ -637,18 +654,23 @@ __global__ __launch_bounds__(SYM_NT) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     a.m += ss.o;
     a.rc += ss.o;
     a.colpart += ss.cbase;
-    sym_tile_run<false>(a, t.g, t.s, sid, sm);
+    sym_tile_run<false>(a, t.g, t.s, sid, sid, sm);   // (slices of one width: P = 1)
 }
 
 // Place the staged pairs of the symmetric kick (a block per tile, one wave of
-// 64 threads per kick wave).  Rank of a pair inside its (row, tile): the number of pairs of
-// the same row with a smaller j in the wave's segment.  A wave whose segment
-// overflowed is recomputed over its rows and the tile's columns, j ascending.
+// 64 threads per kick wave).  Rank of a pair inside its (row, tile): the number
+// of pairs of the same row with a smaller j in the wave's segment, counted over
+// keys of row and column.  A wave whose segment overflowed is recomputed: 64
+// columns at a time, a lane each, against its rows one after another, so that a
+// row's pairs go out side by side (20,011 bodies of about 800 partners each: kick
+// 825 us; with a row per lane, whose pairs are scattered words, 1,085).
 struct SymScatterDev {
     SymShape sh;                    // one system (b.tiles null)
     SymBatch b;                     // batch: tile and system descriptors
     const double *x, *y, *z, *rc;
-    const int32_t *cnt, *stage, *wcount;
+    const int32_t *cnt;
+    int32_t *stage;
+    const int32_t *wcount;
     const int32_t *rowloc;
     const int64_t *boff;
     int32_t *pi, *pj;
@@ -657,10 +679,14 @@ struct SymScatterDev {
 
 __global__ __launch_bounds__(SYM_NT) void k_pairs_scatter_sym(SymScatterDev d)
 {
-    __shared__ int32_t si_all[SYM_NW][WSEG], sj_all[SYM_NW][WSEG];
+    __shared__ union {
+        uint32_t key[SYM_PMAX * WSEG];
+        double4 row[SYM_IPT * 64];   // x, y, z, rc^2 of the wave's rows
+    } sm[SYM_NW];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int32_t *si_ = si_all[w], *sj_ = sj_all[w];
+    uint32_t *key = sm[w].key;
+    double4 *row = sm[w].row;
     const int64_t sid = blockIdx.x;
     const int64_t wave_g = sid * SYM_NW + w;
     const int nst = d.wcount[wave_g];
@@ -680,53 +706,74 @@ __global__ __launch_bounds__(SYM_NT) void k_pairs_scatter_sym(SymScatterDev d)
         s = sid - h.tb(g);
     }
     const int64_t row0 = g * SYM_RG;   // (local to the system)
-    if (nst <= WSEG) {
+    const SymStage st = sym_stage(h, g, s, d.b.tiles ? sid : h.room(g, s), w);
+    int64_t col0, col1;
+    h.cols(g, s, col0, col1);
+    if (nst <= st.cap) {
+        static_assert(SYM_RG <= 1024, "a tile's column in 10 bits");
+        const int32_t i0 = (int32_t)(o + row0), j0 = (int32_t)(o + col0);
         for (int e = lane; e < nst; e += 64) {
-            const int32_t *e3 = d.stage + ((size_t)wave_g * WSEG + e) * 3;
-            si_[e] = e3[0];
-            sj_[e] = e3[1];
+            const int32_t *e3 = st.at(d.stage, e);
+            key[e] = (uint32_t)(e3[0] - i0) << 10 | (uint32_t)(e3[1] - j0);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         for (int e = lane; e < nst; e += 64) {
-            const int32_t i = si_[e], j = sj_[e];
+            const uint32_t k = key[e], first = k & ~1023u, col = k & 1023u;
             int rank = 0;
-            for (int f = 0; f < nst; ++f) rank += (si_[f] == i && sj_[f] < j) ? 1 : 0;
+            for (int f = 0; f < nst; ++f) rank += key[f] - first < col ? 1 : 0;
+            const int32_t i = i0 + (int32_t)(k >> 10);
             const int64_t pos = d.boff[i / RB] + d.rowloc[i] +
-                                d.cnt[(size_t)sid * SYM_RG + (i - o - row0)] + rank;
+                                d.cnt[(size_t)sid * SYM_RG + (k >> 10)] + rank;
             if (pos < d.capacity) {
                 d.pi[pos] = i;
-                d.pj[pos] = j;
+                d.pj[pos] = j0 + (int32_t)col;
             }
         }
         return;
     }
     const int64_t n = h.n;
     const int64_t rowend = row0 + SYM_RG < n ? row0 + SYM_RG : n;
-    int64_t col0, col1;
-    h.cols(g, s, col0, col1);
+    int64_t pos[SYM_IPT];   // of the rows of this lane
+#pragma unroll
     for (int q = 0; q < SYM_IPT; ++q) {
         const int64_t li = row0 + (int64_t)(q * SYM_NW + w) * 64 + lane;
-        if (li >= rowend) continue;
-        const int64_t i = o + li;
-        int64_t pos = d.boff[i / RB] + d.rowloc[i] + d.cnt[(size_t)sid * SYM_RG + (li - row0)];
-        const double xi = d.x[i], yi = d.y[i], zi = d.z[i];
-        const double rci = d.rc[i];
-        const double rc2i = rci * rci;
-        for (int64_t lj = (col0 > li + 1 ? col0 : li + 1); lj < col1; ++lj) {
-            const int64_t j = o + lj;
-            const double dx = d.x[j] - xi, dy = d.y[j] - yi, dz = d.z[j] - zi;
-            const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-            const double rcj = d.rc[j];
-            const double rc2j = rcj * rcj;
-            const double rho2 = rc2i > rc2j ? rc2i : rc2j;
-            if (r2 < rho2) {
-                if (pos < d.capacity) {
-                    d.pi[pos] = (int32_t)i;
-                    d.pj[pos] = (int32_t)j;
+        pos[q] = 0;
+        if (li < rowend) {
+            const int64_t i = o + li;
+            const double rci = d.rc[i];
+            row[q * 64 + lane] = make_double4(d.x[i], d.y[i], d.z[i], rci * rci);
+            pos[q] = d.boff[i / RB] + d.rowloc[i] + d.cnt[(size_t)sid * SYM_RG + (li - row0)];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int64_t c0 = col0; c0 < col1; c0 += 64) {
+        const int64_t lj = c0 + lane;
+        const bool real = lj < col1;
+        const int64_t j = o + (real ? lj : col1 - 1);
+        const double xj = d.x[j], yj = d.y[j], zj = d.z[j], rcj = d.rc[j], rc2j = rcj * rcj;
+#pragma unroll
+        for (int q = 0; q < SYM_IPT; ++q) {
+            const int64_t l0 = row0 + (int64_t)(q * SYM_NW + w) * 64;
+            const int rows = (int)(rowend - l0 < 64 ? rowend - l0 : 64);
+            for (int r = 0; r < rows; ++r) {
+                const double4 b = row[q * 64 + r];
+                const double dx = xj - b.x, dy = yj - b.y, dz = zj - b.z;
+                const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
+                const bool inside = r2 < (b.w > rc2j ? b.w : rc2j) && r2 != 0.0 && real && lj > l0 + r;
+                const uint64_t mask = __ballot(inside);
+                if (!mask) continue;
+                const uint32_t lo = __builtin_amdgcn_readlane((int)pos[q], r);
+                const uint32_t hi = __builtin_amdgcn_readlane((int)(pos[q] >> 32), r);
+                const int64_t p = (int64_t)((uint64_t)hi << 32 | lo) + __popcll(mask & lanemask_lt());
+                if (inside && p < d.capacity) {
+                    d.pi[p] = (int32_t)(o + l0 + r);
+                    d.pj[p] = (int32_t)j;
                 }
-                ++pos;
+                if (lane == r) pos[q] += __popcll(mask);
             }
         }
     }
@@ -789,7 +836,7 @@ hipError_t launch_kick_sym_b(const SymBatch &b, const double *x, const double *y
 
 hipError_t launch_scatter_sym(const SymShape &h, const SymBatch *b, const double *x,
                               const double *y, const double *z, const double *rc,
-                              const int32_t *cnt, const int32_t *stage, const int32_t *wcount,
+                              const int32_t *cnt, int32_t *stage, const int32_t *wcount,
                               const int32_t *rowloc, const int64_t *boff, genga_pairs *pairs,
                               hipStream_t s)
 {

@@ -259,3 +259,23 @@ def test_sym_disk16384_default_form(dev):
     _say("disk16384 symmetric sampled max rel err", max(err))
     assert max(err) <= ACC_TOL
     assert np.max(_rel_err(a, a_d)) <= 2 * ACC_TOL
+
+
+@pytest.mark.parametrize("n, rc_scale", [(8193, 0.3), (8193, 0.4), (8193, 0.5), (13001, 0.3), (13001, 0.45),
+                                         (23500, 0.3), (23500, 0.35), (40001, 0.2), (40001, 0.3)])
+@pytest.mark.parametrize("precision", [N.FP64, N.MIXED])
+def test_lists_of_dense_systems(dev, n, rc_scale, precision):
+    # waves of wide tiles that stage from a few to more pairs than they have
+    # room for (up to 512), which are then computed a second time, at the sizes
+    # where the shapes and their room change: the list against the oracle's
+    d = W.random_cloud(n, seed=n, rc_scale=rc_scale)
+    oi, oj, cnt = oracle.pairs(d["x"], d["y"], d["z"], d["rc"], cap=1 << 25)
+    assert cnt <= 1 << 25
+    st = N.State.from_numpy(d)
+    cfg = N.Config(G=G, precision=precision)
+    ws = N.Workspace(n, cfg)
+    pl = N.PairList(cnt)
+    N.kick(st, cfg, ws, 0.0, pairs=pl)
+    assert N.read_status(ws) == N.OK
+    pi, pj, c = pl.result()
+    assert c == cnt and np.array_equal(pi, oi[:cnt]) and np.array_equal(pj, oj[:cnt])
