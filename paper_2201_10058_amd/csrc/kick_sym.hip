@@ -85,8 +85,9 @@ __device__ __forceinline__ SymStage sym_stage(const SymShape &h, int64_t g, int6
 
 // Padding rows and columns sit far away, on opposite sides (no two padding
 // bodies coincide), with mass 0 and critical radius 0: r^2 stays finite (below
-// 1.3e37, also in binary32), every weight they give or take is 0 and they
-// never reach the rare path.  (Passed as kernel arguments, so that they sit in
+// 1.3e37, also in binary32) and every weight they give or take is 0.  Only a
+// radius of more than 1.7e18 takes them to the rare path, which keeps them out of
+// the list (sym_lists).  (Passed as kernel arguments, so that they sit in
 // scalar registers.)
 constexpr double SYM_FAR_ROW = 1e18, SYM_FAR_COL = -1e18;
 
@@ -132,6 +133,14 @@ struct SymRows {
     float axf[SYM_IPT], ayf[SYM_IPT], azf[SYM_IPT], magf[SYM_IPT];
 };
 
+// Whether the pair (i, j) is the list's: real bodies (a critical radius beyond the
+// padding's distance, or an infinite one, reaches padding rows, i = -1, and
+// columns), each pair once.
+__device__ __forceinline__ bool sym_lists(const SymDev &a, int i, int j)
+{
+    return i >= 0 && j > i && j < a.sh.n;
+}
+
 // Rare path of the binary64 kick, entered by the whole wave when any lane's r^2
 // is at most the gate's bound g2 (which is at least max(rc_i^2, rc_j^2)): the
 // self pair, coincident bodies, the changeover band and encounter recording.
@@ -170,7 +179,7 @@ __device__ __forceinline__ void sym_near(const SymDev &a, SymRows<false> &R, int
         si = inside ? mc * kr : si;
         sj = inside ? (R.mw[q] * (2.0 / 3.0)) * kr : sj;
         if (a.emit) {
-            const bool emit = inside && jg > R.ii[q];
+            const bool emit = inside && sym_lists(a, R.ii[q], jg);
             const uint64_t mask = __ballot(emit);
             if (emit) {
                 const int pos = nst + __popcll(mask & lanemask_lt());
@@ -203,7 +212,7 @@ __device__ __forceinline__ void sym_slow(const SymDev &a, SymRows<true> &R, int 
     } else {
         const double rho2 = R.rc2i[q] > rc2c ? R.rc2i[q] : rc2c;
         const bool inside = r2 < rho2;
-        emit = inside && jg > R.ii[q];
+        emit = inside && sym_lists(a, R.ii[q], jg);
         if (inside) {
             const double yc = rsq_nr(r2);
             const double irho = rsq_nr(rho2);

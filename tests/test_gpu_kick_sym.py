@@ -279,3 +279,29 @@ def test_lists_of_dense_systems(dev, n, rc_scale, precision):
     assert N.read_status(ws) == N.OK
     pi, pj, c = pl.result()
     assert c == cnt and np.array_equal(pi, oi[:cnt]) and np.array_equal(pj, oj[:cnt])
+
+
+@pytest.mark.parametrize("precision", [N.FP64, N.MIXED])
+@pytest.mark.parametrize("n", [1, 65, 520, 1100])
+def test_radii_beyond_the_padding(dev, n, precision):
+    # rows and columns past the end stand at 1e18 from the bodies: a radius
+    # that reaches them lists no pair of theirs and leaves the sums alone.  With
+    # every pair far below its band K and the accelerations are exact zeros
+    d = W.random_cloud(n, seed=n)
+    d["rc"] = np.full(n, 1e19)
+    cfg = N.Config(G=G, flags=SYM, precision=precision)
+    ws = N.Workspace(n, cfg)
+    st = N.State.from_numpy(d)
+    pl = N.PairList(n * n // 2 + 1)
+    a = N.kick(st, cfg, ws, 0.0, acc=True, pairs=pl).cpu().numpy()
+    assert N.read_status(ws) == N.OK and np.all(a == 0.0)
+    i, j = np.triu_indices(n, 1)
+    pi, pj, c = pl.result()
+    assert c == i.size and np.array_equal(pi, i) and np.array_equal(pj, j)
+    # an infinite one is reported, and the list holds real bodies only
+    st.t["rc"].fill_(0.1)
+    st.t["rc"][n // 2] = np.inf
+    N.kick(st, cfg, ws, 0.0, acc=True, pairs=pl)
+    assert N.read_status(ws) in (N.E_RCRIT, N.E_NONFINITE)
+    pi, pj, c = pl.result()
+    assert c <= i.size and np.all(pi >= 0) and np.all(pi < pj) and np.all(pj < n)
