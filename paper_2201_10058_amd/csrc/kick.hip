@@ -1317,8 +1317,11 @@ __global__ __launch_bounds__(64) void k_pairs_scatter(ScatterDev d)
 //   10,000: 175 -> 163 (64, 16, 2)    16,384: 326 -> 310 (64, 24, 4)
 //   20,011: 457 -> 428 (64, 24, 4)    32,768: 994 -> 974 (64, 24, 4)
 //   45,000: 1802 -> 1734 (128, 16, 4) 65,536: 3614 -> 3535 (128, 16, 4)
-// at 20,011 with 2, 4 and 8 as multiple: 432, 428, 456.  From 131,072 bodies on
-// 512 columns alone are some hundred tiles to a compute unit.
+// at 20,011 with 2, 4 and 8 as multiple: 432, 428, 456.  Between (64, 16, 2) and
+// (64, 24, 4), binary64 / mixed: 13,001 bodies 235 / 266 and 254 / 291 (one
+// width 252 / 283), 14,000 243 / 285 and 250 / 294, 15,000 269 / 307 and 260 /
+// 299, 16,384 304 / 334 and 299 / 342.  From 131,072 bodies on 512 columns alone
+// are some hundred tiles to a compute unit.
 static SymShape sym_default_shape(int64_t n)
 {
     if (n < SYM_MIN_N) {
@@ -1327,7 +1330,7 @@ static SymShape sym_default_shape(int64_t n)
         while (W > 64 && sym_shape(n, W).T < 4096) W /= 2;
         return sym_shape(n, W);
     }
-    if (n < 13000) return sym_shape(n, 64, 16, 2);
+    if (n < 14500) return sym_shape(n, 64, 16, 2);
     if (n < 40000) return sym_shape(n, 64, 24, 4);
     if (n < 131072) return sym_shape(n, 128, 16, 4);
     return sym_shape(n, SYM_RG);

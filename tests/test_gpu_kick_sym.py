@@ -261,7 +261,7 @@ def test_sym_disk16384_default_form(dev):
     assert np.max(_rel_err(a, a_d)) <= 2 * ACC_TOL
 
 
-@pytest.mark.parametrize("n, rc_scale", [(8193, 0.3), (8193, 0.4), (8193, 0.5), (13001, 0.3), (13001, 0.45),
+@pytest.mark.parametrize("n, rc_scale", [(8193, 0.3), (8193, 0.4), (8193, 0.5), (13001, 0.3), (14501, 0.3), (14501, 0.45),
                                          (23500, 0.3), (23500, 0.35), (40001, 0.2), (40001, 0.3)])
 @pytest.mark.parametrize("precision", [N.FP64, N.MIXED])
 def test_lists_of_dense_systems(dev, n, rc_scale, precision):

@@ -32,7 +32,7 @@ static int check(int64_t n, int W, int A, int M)
 }
 int main()
 {
-    for (int64_t n : {1, 511, 512, 513, 4097, 8192, 8193, 12999, 13000, 20011, 23000, 39999, 40000, 46000,
+    for (int64_t n : {1, 511, 512, 513, 4097, 8192, 8193, 12999, 13000, 14499, 14500, 20011, 23000, 39999, 40000, 46000,
                       65536, 131071})
         for (int W : {64, 128, 256, 512})
             for (int A : {0, 8, 16, 24})
