@@ -489,8 +489,8 @@ int genga_step_batched(genga_bodies *b, const genga_batch *bt, const genga_param
  * non-null the choice is first looked up in, and after tuning appended to, a
  * plain-text file: one line "key block ipt tile_cols grid slices ms" per
  * problem, key = kind, device architecture, precision and problem signature
- * (N rounded up to a power of two; or S, total N and a histogram of the system
- * sizes); the last line of a key wins.  ms_out (nullable) receives the time
+ * (test-particle mode and the power of two above N; or S, total N and a
+ * histogram of the system sizes); the last line of a key wins.  ms_out (nullable) receives the time
  * of one kick with the chosen shape (genga_autotune_batched: of a step's two
  * kicks, one without and one with the encounter list).  Synchronises the
  * stream.

@@ -58,13 +58,18 @@ std::string batch_key(const genga_batch *bt, int precision)
     return buf;
 }
 
-std::string single_key(int64_t n, int precision)
+// Sizes from one power of two up to the next, which the default kick's form does
+// not change within (SYM_MIN_N is one).  "rows" tells the lines apart from those
+// timed before the row-group and test-particle kicks were what a shape of (1, 0)
+// names.
+std::string single_key(int64_t n, const genga_params *p)
 {
+    static_assert((SYM_MIN_N & (SYM_MIN_N - 1)) == 0, "");
     int64_t bucket = 1;
-    while (bucket < n) bucket <<= 1;
+    while (bucket <= n) bucket <<= 1;
     char buf[128];
-    snprintf(buf, sizeof buf, "single:%s:p%d:N%lld", arch_name().c_str(), precision,
-             (long long)bucket);
+    snprintf(buf, sizeof buf, "single:rows:%s:p%d:t%d:N%lld", arch_name().c_str(), p->precision,
+             p->tp_mode, (long long)bucket);
     return buf;
 }
 
@@ -319,7 +324,7 @@ int genga_autotune(const genga_bodies *b, genga_params *p, void *ws, size_t ws_b
 {
     if (!b || !p || !ws || b->n < 1) return GENGA_E_INVAL;
     hipStream_t s = (hipStream_t)stream;
-    const std::string key = single_key(b->n, p->precision);
+    const std::string key = single_key(b->n, p);
     Shape best;
     double best_ms = -1.0;
     if (!cache_lookup(cache_path, key, best, best_ms)) {

@@ -339,3 +339,19 @@ def test_autotune_single_choice_is_valid(dev, tmp_path, monkeypatch, n):
     a0 = N.kick(st, cfg, N.Workspace(st.n, cfg), 0.0, acc=True).cpu().numpy()
     a1 = N.kick(st, tuned, N.Workspace(st.n, tuned), 0.0, acc=True).cpu().numpy()
     assert np.max(np.linalg.norm(a0 - a1, axis=0) / np.linalg.norm(a0, axis=0)) <= 1e-13
+
+
+def test_autotune_single_keys(dev, tmp_path, monkeypatch):
+    # lines of kicks that were timed before the row groups, and of other modes and
+    # size ranges, do not answer: each of these tunes by itself
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv(autotune.CACHE_ENV, str(cache))
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    cache.write_text(f"single:{arch}:p0:N8192 0 2 0 0 64 0.5 {N.FLAG_DIRECTED}\n")
+    lines = 1
+    for n, kw in ((5000, {}), (8191, {}), (8192, {}), (5000, dict(tp_mode=2, n_massive=8))):
+        d = W.make_tp_disk(n, 8, seed=3) if kw else \
+            W.make_disk(W.DiskSpec(f"disk_n{n}", n, 0.5, 2.0, 2.0, seed=n))
+        autotune.tune_single(N.State.from_numpy(d), N.Config(G=G, **kw))
+        lines += n != 8191      # (as 5,000 bodies)
+        assert len(cache.read_text().splitlines()) == lines, (n, kw)
