@@ -524,8 +524,11 @@ size_t genga_autotune_workspace_bytes(int64_t n, const genga_params *p);
  * test-particle mode) the symmetric form with slices {library choice, 1, 2, 4,
  * 8} (see genga_params.slices).  Writes p->ipt, p->slices and the form
  * (GENGA_FLAG_DIRECTED or GENGA_FLAG_SYMMETRIC in p->flags, the other form
- * flag cleared).  Cache lines written before the symmetric form existed
- * (seven fields) read as the library's form. */
+ * flag cleared).  With GENGA_MIXED below GENGA_MIXED_STEP_MIN bodies also the
+ * binary64 kick that genga_step takes there; where it is the fastest, p->ipt and
+ * p->slices are 0 and both form flags cleared, so that genga_step keeps it
+ * (genga_kick then runs the mixed kick in the library's shape).  Lines of seven
+ * fields, without the form, read as the library's form. */
 int genga_autotune(const genga_bodies *b, genga_params *p, void *ws, size_t ws_bytes,
                    const char *cache_path, double *ms_out, void *stream);
 

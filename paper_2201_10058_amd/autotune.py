@@ -56,7 +56,8 @@ def tune_batched(state: N.State, batch: N.Batch, cfg: N.Config, use_cache: bool 
 def tune_single(state: N.State, cfg: N.Config, use_cache: bool = True) -> dict:
     """Pick the kick form (one-sided or symmetric) and its (ipt, slices) for
     the single-system kick of this size; `flags` is cfg.flags with the chosen
-    form flag."""
+    form flag, or with neither (form "library") where mixed precision is best left
+    to genga_step, which then takes the binary64 kick."""
     lib = N.load()
     p = cfg.params()
     nbytes = lib.genga_autotune_workspace_bytes(state.n, ctypes.byref(p))
@@ -70,7 +71,8 @@ def tune_single(state: N.State, cfg: N.Config, use_cache: bool = True) -> dict:
                                 ctypes.c_size_t(int(nbytes)), path, ctypes.byref(ms),
                                 ctypes.c_void_p(N._stream_ptr())),
              "genga_autotune")
-    form = "symmetric" if p.flags & N.FLAG_SYMMETRIC else "one-sided"
+    form = "symmetric" if p.flags & N.FLAG_SYMMETRIC else \
+        "one-sided" if p.flags & N.FLAG_DIRECTED else "library"
     return dict(form=form, ipt=p.ipt, slices=p.slices, flags=p.flags, ms=ms.value)
 
 

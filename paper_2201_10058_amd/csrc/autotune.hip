@@ -172,10 +172,18 @@ std::vector<Shape> batch_candidates(const genga_params *p)
 
 // One-sided form: rows per thread x column slices; symmetric form (binary64
 // or mixed, every body massive): slice widths (slices d = 1, 2, 4, 8 of a
-// 512-row group, or the library's width).
-std::vector<Shape> single_candidates(const genga_params *p)
+// 512-row group, or the library's width).  Where genga_step takes the binary64
+// kick for mixed precision as long as nothing is set, nothing set is the first
+// candidate.
+bool step_is_binary64(int64_t n, const genga_params *p)
+{
+    return p->precision == GENGA_MIXED && p->tp_mode == 0 && n < GENGA_MIXED_STEP_MIN;
+}
+
+std::vector<Shape> single_candidates(int64_t n, const genga_params *p)
 {
     std::vector<Shape> v;
+    if (step_is_binary64(n, p)) v.push_back(Shape());
     for (int ipt : {1, 2})
         for (int sl : {0, 8, 16, 32, 64}) {
             Shape s;
@@ -310,7 +318,7 @@ size_t genga_autotune_workspace_bytes(int64_t n, const genga_params *p)
 {
     if (!p || n < 1) return 0;
     size_t most = 0;
-    for (const Shape &s : single_candidates(p)) {
+    for (const Shape &s : single_candidates(n, p)) {
         genga_params q = *p;
         apply(s, &q);
         q.flags = (p->flags & ~FORM_FLAGS) | s.flags;
@@ -329,10 +337,11 @@ int genga_autotune(const genga_bodies *b, genga_params *p, void *ws, size_t ws_b
     double best_ms = -1.0;
     if (!cache_lookup(cache_path, key, best, best_ms)) {
         best_ms = -1.0;
-        for (const Shape &c : single_candidates(p)) {
+        for (const Shape &c : single_candidates(b->n, p)) {
             genga_params q = timing_params(p);
             apply(c, &q);
             q.flags = (p->flags & ~FORM_FLAGS) | c.flags;
+            if (step_is_binary64(b->n, p) && c.ipt == 0 && c.flags == 0) q.precision = GENGA_FP64;
             q.block = p->block;
             q.tile_cols = p->tile_cols;
             q.grid = p->grid;

@@ -341,6 +341,23 @@ def test_autotune_single_choice_is_valid(dev, tmp_path, monkeypatch, n):
     assert np.max(np.linalg.norm(a0 - a1, axis=0) / np.linalg.norm(a0, axis=0)) <= 1e-13
 
 
+@pytest.mark.parametrize("n", [300, 2048, 5000])
+def test_autotune_leaves_small_mixed_steps_to_the_library(dev, tmp_path, monkeypatch, n):
+    # below MIXED_STEP_MIN bodies genga_step takes the binary64 kick as long as no
+    # form or shape is set, and that kick is several times faster than any mixed
+    # shape: the tuner sets none, so a tuned step is the untuned one
+    monkeypatch.setenv(autotune.CACHE_ENV, str(tmp_path / "tune.txt"))
+    d = W.make_disk(W.DiskSpec(f"disk_n{n}", n, 0.5, 1.5, 1.0, seed=n))
+    cfg = N.Config(G=G, precision=N.MIXED)
+    st = N.State.from_numpy(d)
+    N.rcrit(st, cfg, N.Workspace(n, cfg))
+    choice = autotune.tune_single(st, cfg)
+    _say("autotuned mixed shape", n, choice)
+    assert (choice["form"], choice["ipt"], choice["slices"], choice["flags"]) == ("library", 0, 0, 0)
+    assert {k: v for k, v in autotune.tune_single(st, cfg).items() if k != "ms"} == \
+        {k: v for k, v in choice.items() if k != "ms"}
+
+
 def test_autotune_single_keys(dev, tmp_path, monkeypatch):
     # lines of kicks that were timed before the row groups, and of other modes and
     # size ranges, do not answer: each of these tunes by itself
