@@ -33,6 +33,18 @@ inline bool arrays_overlap(const double *const (&out)[NO], const double *const (
     return false;
 }
 
+// Whether any two of the arrays of n doubles `out` overlap: sums added to them one
+// after another, as the two-kernel forms do, are not sums added to values read
+// ahead.
+template <int NO>
+inline bool arrays_overlap(const double *const (&out)[NO], int64_t n)
+{
+    for (int a = 0; a < NO; ++a)
+        for (int b = 0; b < a; ++b)
+            if (out[a] < out[b] + n && out[b] < out[a] + n) return true;
+    return false;
+}
+
 // Columns of a system (global memory or LDS).
 struct RowsCols {
     const double *x, *y, *z, *m, *rc;

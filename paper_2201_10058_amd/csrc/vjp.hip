@@ -313,7 +313,7 @@ hipError_t launch_kick_vjp(const genga_bodies *b, const genga_params *p, double 
     }
     const double *const in[] = {b->x, b->y, b->z, b->m, b->rc, abx, aby, abz};
     const double *const out[] = {adj->x, adj->y, adj->z, adj->m, adj->rc};
-    if (c.use_rows && !arrays_overlap(out, in, b->n))
+    if (c.use_rows && !arrays_overlap(out, in, b->n) && !arrays_overlap(out, b->n))
         return launch_kick_vjp_rows(b, p->G, scale, abx, aby, abz, adj, (int32_t *)ws, s);
     // one row per thread for the adjoint (its register footprint is larger)
     c.ipt = 1;

@@ -313,3 +313,25 @@ def test_kick_vjp_components_against_tiled_form(dev, n, kind):
     for k in N.AdjointState.KEYS:
         want = base[k] + rows[k]
         assert np.abs(again[k] - want).max() <= 2.0**-52 * (np.abs(base[k]) + np.abs(rows[k])).max(), k
+
+
+def test_vjp_into_one_array_twice(dev):
+    # one array for two gradients takes both sums, as in the tiled form
+    n = 300
+    d = W.random_cloud(n, seed=78, rc_scale=0.3)
+    rng = np.random.default_rng(6)
+    ab = [torch.tensor(rng.normal(size=n), device="cuda") for _ in range(3)]
+    st = N.State.from_numpy(d)
+    got = []
+    for slices in (0, 3):
+        cfg = N.Config(G=1.0, slices=slices)
+        ws = N.Workspace(n, cfg)
+        one = N.AdjointState(n)
+        one.t["y"] = one.t["x"]
+        N.kick_vjp(st, cfg, ws, 0.7, ab, one)
+        assert N.read_status(ws) == N.OK
+        got.append(one.t["x"].cpu().numpy())
+    apart = _vjp(d, N.Config(G=1.0, slices=3), ab)
+    want = apart["x"] + apart["y"]
+    for g in got:
+        assert np.abs(g - want).max() <= 1e-11 * np.abs(want).max()
