@@ -311,3 +311,26 @@ def test_mixed_simulate_keeps_a_kick_that_is_named(dev, kw):
         out.append(X)
     assert not torch.equal(out[0], out[1])
     assert (out[0] - out[1]).abs().max() <= 1e-9 * out[1].abs().max()
+
+
+@pytest.mark.parametrize("kw", [dict(slices=3), dict(slices=64), dict(precision=N.MIXED)])
+@pytest.mark.parametrize("n,scale", [(200, 0.4), (700, 0.15), (1100, 0.1)])
+def test_tiled_kick_vjp_matches_autograd(dev, n, scale, kw):
+    # the tiled gather form, which column slices and mixed precision name: the
+    # row groups and the symmetric form are compared with it at larger sizes
+    d = W.random_cloud(n, seed=21, rc_scale=scale)
+    abar = np.random.default_rng(1).normal(size=(3, n))
+    x, v, m = T.state_tensors(d, requires_grad=True)
+    rc = torch.tensor(d["rc"], dtype=T.TD, requires_grad=True)
+    L = (T.kick_acc(x, m, rc, G) * torch.tensor(abar.T) * 0.7).sum()
+    ref = torch.autograd.grad(L, (x, m, rc))
+    cfg = N.Config(G=G, **kw)
+    ws = N.Workspace(n, cfg)
+    adj = N.AdjointState(n)
+    N.kick_vjp(_gpu_state(d, rc=d["rc"]), cfg, ws, 0.7, [torch.tensor(a, device="cuda") for a in abar], adj)
+    assert N.read_status(ws) == N.OK
+    got = (np.stack([adj.t[k].cpu().numpy() for k in "xyz"]).T, adj.t["m"].cpu().numpy(),
+           adj.t["rc"].cpu().numpy())
+    e = [_rel(g, r.numpy()) for g, r in zip(got, ref)]
+    _say("tiled kick vjp rel errors (x, m, rc)", e)
+    assert max(e) < 1e-10

@@ -1,5 +1,5 @@
 """The row-group kick of small systems (fewer than 8,192 bodies) and the base
-step on it, at the edges of its row groups (8), waves (64), column chunks (256)
+step on it, at the edges of its row groups (4), waves (64), column chunks (256)
 and range, against the oracle.
 
 Tolerances as in the parity tests: 1e-12 per acceleration of the compensated
@@ -335,3 +335,62 @@ def test_vjp_into_one_array_twice(dev):
     want = apart["x"] + apart["y"]
     for g in got:
         assert np.abs(g - want).max() <= 1e-11 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("where", ["inside", "last"])
+@pytest.mark.parametrize("n", [70, 129, 257, 300, 1031])
+def test_invalid_radius_at_ragged_sizes(dev, n, where):
+    # an infinite radius reaches the lanes past the last column, which repeat
+    # the last body: reported, by the kick and by its VJP, and the list holds
+    # real bodies only, once each
+    d = W.random_cloud(n, seed=5, rc_scale=0.1)
+    rc = d["rc"].copy()
+    rc[3 if where == "inside" else n - 1] = np.inf
+    st = N.State.from_numpy(d, rc=rc)
+    cfg = N.Config(G=G)
+    ws = N.Workspace(n, cfg)
+    pl = N.PairList(n * n)
+    N.kick(st, cfg, ws, 0.0, acc=True, pairs=pl)
+    assert N.read_status(ws) == N.E_RCRIT
+    pi, pj, c = pl.result()
+    oi, oj, cnt = oracle.pairs(d["x"], d["y"], d["z"], rc)
+    assert c == cnt and np.array_equal(pi, oi) and np.array_equal(pj, oj)
+    ab = [torch.ones(n, dtype=torch.float64, device="cuda") for _ in range(3)]
+    N.kick_vjp(st, cfg, ws, 1.0, ab, N.AdjointState(n))
+    assert N.read_status(ws) == N.E_RCRIT
+
+
+def test_largest_size_of_the_row_groups(dev):
+    # 8,192 bodies take them under FLAG_DIRECTED: every word of the bitmap and
+    # every sum of 256 bodies is full
+    n = 8192
+    cfg = N.Config(G=G, flags=N.FLAG_DIRECTED)
+    d = W.random_cloud(n, seed=8, rc_scale=0.1)
+    st = N.State.from_numpy(d)
+    ws = N.Workspace(n, cfg)
+    oi, oj, cnt = oracle.pairs(d["x"], d["y"], d["z"], d["rc"])
+    pl = N.PairList(cnt)
+    a = N.kick(st, cfg, ws, 0.0, acc=True, pairs=pl).cpu().numpy()
+    assert N.read_status(ws) == N.OK
+    pi, pj, c = pl.result()
+    assert c == cnt and np.array_equal(pi, oi) and np.array_equal(pj, oj)
+    ax, ay, az, code = oracle.kick_acc(d["x"], d["y"], d["z"], d["m"], d["rc"], G, precise=True)
+    ref = np.stack([ax, ay, az])
+    assert np.max(np.linalg.norm(a - ref, axis=0) / np.linalg.norm(ref, axis=0)) <= TOL
+    rng = np.random.default_rng(n)
+    ab = [torch.tensor(rng.normal(size=n), device="cuda") for _ in range(3)]
+    rows = _vjp(d, N.Config(G=1.0, flags=N.FLAG_DIRECTED), ab)
+    tiled = _vjp(d, N.Config(G=1.0, flags=N.FLAG_DIRECTED, slices=3), ab)
+    size = _vjp_size(d, ab)
+    tol = 2 * (64 * 2.0**-52 + 7e-14) + np.sqrt(n) * 2.0**-52    # (as above)
+    for k in ("x", "y", "z", "m", "rc"):
+        assert np.all(np.abs(rows[k] - tiled[k]) <= tol * size[k]), k
+    disk = W.make_disk(W.DiskSpec("disk_n8192", n, 0.5, 2.0, 3.0, seed=91))
+    st, ref = N.State.from_numpy(disk), oracle.state_copy(disk)
+    pl = N.PairList(64 * n)
+    for _ in range(2):
+        assert N.step(st, cfg, ws, pl) == N.OK
+        oracle.step(ref, G, 1.0, 6.0, 3.0, 0.4)
+    out = st.numpy()
+    for k in ("x", "y", "z", "vx", "vy", "vz"):
+        assert np.max(np.abs(out[k] - ref[k])) <= 2 * TOL * np.max(np.abs(ref[k])), k

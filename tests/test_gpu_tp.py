@@ -1,6 +1,8 @@
 """Test-particle modes 1 and 2 (Sect. 8) of the binary64 kick, pair list and
 step against the oracle's test-particle functions (pinned in test_oracle_tp.py).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -205,3 +207,22 @@ def test_tp_graph_replay(dev):
         a, b = pl.result(), pl_e.result()
         assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     assert N.read_status(ws) == N.OK and N.read_status(ws_e) == N.OK
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+def test_tp_results_over_their_inputs(dev, mode):
+    # accelerations written over the positions: as with arrays of their own
+    # (both within the oracle's bound of the accelerations)
+    n, nm = 700, 9
+    d = _cloud(n, nm, seed=41)
+    cfg = N.Config(G=G, tp_mode=mode, n_massive=nm)
+    ws = N.Workspace(n, cfg)
+    st = N.State.from_numpy(d)
+    ref = N.kick(st, cfg, ws, 0.0, acc=True).cpu().numpy()
+    b, p = st.bodies(), cfg.params()
+    assert N.load().genga_kick(ctypes.byref(b), ctypes.byref(p), 0.0, b.x, b.y, b.z, None, ws.ptr,
+                               None) == N.OK
+    assert N.read_status(ws) == N.OK
+    out = np.stack([st.t[k].cpu().numpy() for k in "xyz"])
+    size = np.linalg.norm(ref, axis=0)
+    assert np.max(np.linalg.norm(out - ref, axis=0) / np.where(size > 0, size, 1.0)) <= 2 * ACC_TOL
