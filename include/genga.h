@@ -79,9 +79,9 @@ extern "C" {
  * it to both bodies; the one-sided form evaluates every ordered pair for its
  * first body.  Both give the same encounter list (bit for bit) and
  * accelerations that differ by summation order only.  By default the
- * symmetric form runs from n >= 8192 bodies (up to about 370,000: its
+ * symmetric form runs from n >= 8192 bodies (up to about 331,000: its
  * workspace holds row and column sums that grow as n^2 / 512, 8 GiB there,
- * 0.34 GiB at 65,536 bodies) in the all-massive kick, binary64
+ * 0.43 GiB at 65,536 bodies) in the all-massive kick, binary64
  * and mixed (genga_kick, genga_step and the levels' base kick), and in the
  * binary64 batch (genga_kick_batched, genga_step_batched; every system, in
  * 512-row groups and 512-column slices); the flags force one form at any n
@@ -490,10 +490,10 @@ int genga_step_batched(genga_bodies *b, const genga_batch *bt, const genga_param
  * plain-text file: one line "key block ipt tile_cols grid slices ms" per
  * problem, key = kind, device architecture, precision and problem signature
  * (test-particle mode and the power of two above N; or S, total N and a
- * histogram of the system sizes); the last line of a key wins.  ms_out (nullable) receives the time
- * of one kick with the chosen shape (genga_autotune_batched: of a step's two
- * kicks, one without and one with the encounter list).  Synchronises the
- * stream.
+ * histogram of the system sizes); the last line of a key wins.  ms_out
+ * (nullable) receives the time of one kick with the chosen shape
+ * (genga_autotune_batched: of a step's two kicks, one without and one with the
+ * encounter list).  Synchronises the stream.
  * ------------------------------------------------------------------------ */
 
 /* Workspace for genga_autotune_batched: the largest any candidate needs,

@@ -417,11 +417,13 @@ int genga_step(genga_bodies *b, const genga_params *p, genga_pairs *pairs, void 
     const bool gr = p->c_light > 0.0;
     if (levels && p->tp_mode != 0) return GENGA_E_UNSUPPORTED;
     if (gr && (levels || p->tp_mode != 0)) return GENGA_E_UNSUPPORTED;
-    // Below GENGA_MIXED_STEP_MIN bodies the binary64 kick is the row-group kick
-    // and the faster one, by its launches: the tiled mixed kick, its reduction
-    // and the binary64 refinement of cancelling rows take 13 (step, us, mixed /
-    // binary64: 2,048 bodies 103 / 35, 5,000 160 / 73).  Its workspace is the
-    // same.
+    // Below GENGA_MIXED_STEP_MIN bodies the binary64 kick is the row-group kick,
+    // three times as fast by its launches: the tiled mixed kick, its reduction and
+    // the binary64 refinement of cancelling rows take 13 (step, us, mixed /
+    // binary64: 2,048 bodies 103 / 32, 5,000 160 / 66).  From there on both are
+    // symmetric and nearer (8,192: 175 / 136, 16,384: 341 / 300, 32,768: 921 / 937,
+    // 65,536: 3,245 / 3,400; they cross at about 30,000), and a caller who asks
+    // for binary32 pairs gets them.  The workspace is the same.
     genga_params fast;
     if (p->precision == GENGA_MIXED && b->n < GENGA_MIXED_STEP_MIN && p->ipt == 0 && p->slices == 0 &&
         !(p->flags & (GENGA_FLAG_DIRECTED | GENGA_FLAG_SYMMETRIC))) {

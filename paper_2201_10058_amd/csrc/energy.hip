@@ -200,8 +200,10 @@ hipError_t launch_energy_k_pairs(const genga_bodies *b, const genga_params *p, g
     return hipGetLastError();
 }
 
-// Bound by the binary64 vector units: one v_rsq_f64 and 10 other instructions
-// per unordered pair (65,536 bodies: 2.1e9 pairs).  Summing phi_i over j > i
+// Bound by the binary64 vector units and, for a fifth of the time, by the LDS
+// read of each column that only one row per lane shares: one v_rsq_f64 and 12 other
+// vector instructions per unordered pair (65,536 bodies: 2.1e9 pairs), the units
+// at work 79 % of the kernel.  Summing phi_i over j > i
 // instead of all j, and testing for the encounter list in the same pass instead
 // of a second one over every ordered pair, took genga_energy_k there from 3.25
 // to 1.18 ms.

@@ -146,11 +146,16 @@ struct SymBatch {
     const int32_t *order;
     int64_t S, T;
 };
-constexpr int64_t SYM_MIN_N = 8192;    // default: symmetric kick from this many bodies
+// Default: the symmetric kick from this many bodies, below them the row groups.
+// The two cross there: step on the 0.5-4 AU disk, us, row groups / symmetric:
+// 4,096 bodies 52 / 81, 6,000 84 / 108, 7,500 121 / 127, 8,191 130 / 136, 8,192
+// (16 full groups of 512) 130 / 126.  The VJP follows its kick's form (alone it
+// would cross at about 6,700: 7,000 bodies 85 / 82, 8,191 111 / 98).
+constexpr int64_t SYM_MIN_N = 8192;
 // below this many bodies the symmetric kick's row totals are summed in
 // SYM_FOLD parts over the whole chip before the reduction (k_sym_fold)
 constexpr int64_t SYM_FOLD_BELOW = 32768;
-// default limit of the symmetric kick's row and column sums (about 370,000
+// default limit of the symmetric kick's row and column sums (about 331,000
 // bodies); larger systems take the one-sided form unless forced
 constexpr int64_t SYM_WS_MAX = (int64_t)8 << 30;
 constexpr int SYM_FOLD = 8;

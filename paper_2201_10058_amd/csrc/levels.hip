@@ -1885,7 +1885,8 @@ struct GridPol {
                     for (int c = 0; c < 6; ++c) bj[c] = B[c];
                     rj = trho[Jl];
                     const double rr = rhoI > rj ? rhoI : rj;
-                    // (a NaN box keeps the tile: the flow then fails as a whole)
+                    // (members at NaN are not in their tile's box: they fail the
+                    // flow by their own error)
                     near = !(box_gap2(lo, hi, bj) > rr * rr * (1.0 + 0x1p-18));
                 }
                 unsigned long long mask = __ballot(near);

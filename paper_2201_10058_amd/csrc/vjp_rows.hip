@@ -6,8 +6,10 @@
 // the self pair, and a reduction.  Pairs inside the critical radius are marked
 // in an LDS bitmap and evaluated afterwards, as in the kick.
 //
-// Bound by the binary64 vector units: 36 instructions and one v_rsq_f64 per
-// ordered pair, 15 us at 4,096 bodies, whose kernel takes 38 us.  Sums kept as
+// Bound by the binary64 vector units and their latency: 36 instructions and one
+// v_rsq_f64 per ordered pair are 15 us at 4,096 bodies, whose kernel takes 37 us,
+// in 59 % of which the units work (54 instructions per pair with everything, 3
+// waves to a SIMD).  Sums kept as
 // factors (sum w abar_j, sum w m_j, sum c d) save three instructions per pair
 // and need 32 more registers: 43 us.  Error against extended precision equal
 // to the tiled form's.
