@@ -4,7 +4,8 @@ the direct solver), by the hand-written VJPs of libgenga.so.
 
 The forward pass keeps a checkpoint of (x, v) every `checkpoint_every` steps.
 The backward pass recomputes each segment from its checkpoint with the same
-kernels (bitwise identical to the forward: every kernel is deterministic),
+kernels (every kernel is deterministic; xa and xc are the positions the
+operators' own calls give, which differ from the fused step's by rounding),
 keeps the per-step intermediate states and applies the adjoints of the
 operators in reverse order:
 
