@@ -713,7 +713,8 @@ constexpr int KM = 8;
 constexpr int BS_TRIES = 4096;
 
 struct BsDev {
-    const int32_t *groot, *gstart, *gsize, *gmem, *gcount;
+    int32_t *groot;                     // (each block of k_bs reorders its own medium ones)
+    const int32_t *gstart, *gsize, *gmem, *gcount;
     const double *state[6];             // x, y, z, vx, vy, vz before the drift
     int64_t n;
     double *x, *y, *z, *vx, *vy, *vz;
@@ -1006,11 +1007,47 @@ __device__ __forceinline__ void bs_accel(const BsDev &a, BsSmem<BT> &sm, const B
     if (E.total) flush();
 }
 
+// The same sums, term by term and in the same order, with each partner
+// evaluated where it is met, for groups whose members want most of it: a search finds
+// nearly every partner then, and an entry's way through LDS costs about as much as
+// its remainder.  Rings whose members all meet, us a step, entries / in place:
+// 40 bodies 260 / 212, 100 615 / 434, 150 1,357 / 870, 512 8,640 / 4,530.
+template <int BT, int NL>
+__device__ __forceinline__ void bs_accel_whole(const BsDev &a, const BsSmem<BT> &sm, int t, int g,
+                                               int S, int sub, double rcd, double acc[3])
+{
+    const int t0 = t - (int)(threadIdx.x & 63), i = t < g ? t : 0;
+    const double *BI = sm.box[t0 >> 6];
+    const double lo[3] = {BI[0], BI[1], BI[2]}, hi[3] = {BI[3], BI[4], BI[5]};
+    const double rhoI = sm.trho[t0 >> 6];
+    const double x = sm.px[i], y = sm.py[i], z = sm.pz[i];
+    const int per = 64 / S;
+    for (int J = 0; J * 64 < g; ++J) {
+        const double rJ = sm.trho[J], rr = rhoI > rJ ? rhoI : rJ;
+        if (box_gap2(lo, hi, sm.box[J]) > rr * rr * (1.0 + 0x1p-18)) continue;
+        const double re = rcd > rJ ? rcd : rJ;
+        const double far2 = t < g ? re * re * (1.0 + 0x1p-18) : -1.0;
+        const int q0 = J * 64 + sub * per, q1 = g < q0 + per ? g : q0 + per;
+#pragma unroll 1
+        for (int q = q0; q < q1; ++q) {
+            const double dx = sm.px[q] - x, dy = sm.py[q] - y, dz = sm.pz[q] - z;
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            if (q == t || r2 > far2) continue;
+            const double ir = rsq_full(r2);
+            const double R = bs_remainder<NL>(r2 * ir, &sm.irc[0][i], BT, &sm.irc[0][q], BT, a.nlev);
+            const double s = a.G * sm.m[q] * R * (ir * ir * ir);
+            acc[0] += s * dx;
+            acc[1] += s * dy;
+            acc[2] += s * dz;
+        }
+    }
+}
+
 // Publish positions (and each wave's box), then every member's derivative
 // at them: the star's pull plus the S shares' partner sums, added in share
 // order (the waves of a share hold copies of the same members; only share 0
 // writes).  The shares' sums pass through pv, which no evaluation uses.
-template <int BT, int NL>
+template <int BT, int NL, bool WHOLE>
 __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, const BsFrame &fr, int t,
                                          int g, int S, int sub, double rcd, const double z[6],
                                          double f[6])
@@ -1021,7 +1058,7 @@ __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, const B
         sm.px[t] = z[0];
         sm.py[t] = z[1];
         sm.pz[t] = z[2];
-        sm.cell[t] = bs_cell(fr, z[0], z[1]);
+        if (!WHOLE) sm.cell[t] = bs_cell(fr, z[0], z[1]);
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -1037,7 +1074,12 @@ __device__ __forceinline__ void bs_deriv(const BsDev &a, BsSmem<BT> &sm, const B
     f[1] = z[4];
     f[2] = z[5];
     double p[3] = {0.0, 0.0, 0.0};
-    if (t - (int)(threadIdx.x & 63) < g) bs_accel<BT, NL>(a, sm, fr, t, g, S, sub, rcd, p);
+    if (t - (int)(threadIdx.x & 63) < g) {
+        if constexpr (WHOLE)
+            bs_accel_whole<BT, NL>(a, sm, t, g, S, sub, rcd, p);
+        else
+            bs_accel<BT, NL>(a, sm, fr, t, g, S, sub, rcd, p);
+    }
     double k[3] = {0.0, 0.0, 0.0};
     if (mem) {
         const double r2s = z[0] * z[0] + z[1] * z[1] + z[2] * z[2];
@@ -1087,7 +1129,7 @@ __device__ __forceinline__ double bs_block_max(BsSmem<BT> &sm, double v)
 // whole state of member q after publish(), its mass, radius and body index,
 // a group-wide minimum of an integer key, and updates of the own member's
 // mass and radius.
-template <int BT, int NL>
+template <int BT, int NL, bool WHOLE>
 struct BlockPol {
     BsSmem<BT> &sm;
     int t, g;
@@ -1096,7 +1138,7 @@ struct BlockPol {
     BsFrame fr;   // the group's plane (bs_cell)
     __device__ void deriv(const BsDev &a, const double z[6], double f[6])
     {
-        bs_deriv<BT, NL>(a, sm, fr, t, g, S, sub, rcd, z, f);
+        bs_deriv<BT, NL, WHOLE>(a, sm, fr, t, g, S, sub, rcd, z, f);
     }
     __device__ double gmax(double v) { return bs_block_max<BT>(sm, v); }
     __device__ bool member() const { return t < g; }
@@ -1341,8 +1383,8 @@ __device__ long long bs_overlap(const BsDev &a, Pol &P, const double z[6])
 }
 
 // (positions and radii only, the share's own partners)
-template <int BT, int NL>
-__device__ long long BlockPol<BT, NL>::overlap(const BsDev &a, const double z[6])
+template <int BT, int NL, bool WHOLE>
+__device__ long long BlockPol<BT, NL, WHOLE>::overlap(const BsDev &a, const double z[6])
 {
     publish(z);
     long long key = NO_PAIR;
@@ -1540,26 +1582,54 @@ __device__ __forceinline__ void bs_lanes(const BsDev &a, double (*irc)[GROUP_BLO
     }
 }
 
+// Whether the members want more than half of the group, from one partner per
+// thread, spread over the group; uniform over the block.  (The forms cross where they
+// want about half: rings of 300 bodies and 120 partners each 2,240 us by entries and
+// 2,260 in place, of 150 and 80 1,005 and 780.)
+template <int BT>
+__device__ __forceinline__ bool bs_crowded(BsSmem<BT> &sm, int t, int g, int S, bool owner,
+                                           double rcd, const double y[6])
+{
+    if (owner) {
+        sm.px[t] = y[0];
+        sm.py[t] = y[1];
+        sm.pz[t] = y[2];
+    }
+    __syncthreads();
+    const int q = (int)((((uint32_t)threadIdx.x * 40503u & 0xffffu) * (uint32_t)g) >> 16);
+    const double dx = sm.px[q] - y[0], dy = sm.py[q] - y[1], dz = sm.pz[q] - y[2];
+    const double re = rcd > sm.trho[q >> 6] ? rcd : sm.trho[q >> 6];
+    return 2 * __syncthreads_count(t < g && dx * dx + dy * dy + dz * dz <= re * re) > g * S;
+}
+
 // Groups of more than BS_GS and at most GROUP_BLOCK bodies, one workgroup each
 // (larger ones are the grid solver's).  A group of fewer members than threads
 // spreads each member over S waves (S = GROUP_BLOCK / 64 over the member waves, a
 // power of two): the waves of member wave I are I * S ... I * S + S - 1, each
 // taking one share of the partners, and the first of them (the owner) alone
 // writes.
-template <int NL>
-__device__ __forceinline__ void bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &sm, int blk, int blocks)
+//
+// The crowded ones (bs_crowded) wait for a second pass, WHOLE: the two forms in one
+// loop share their registers out worse (2-4 % of the 8,192-body disk).  What
+// a group is is decided once, before it moves: the first pass puts the roots of
+// the crowded ones into the block's first slots and returns their count, the
+// second takes those `count` slots.
+template <int NL, bool WHOLE>
+__device__ __forceinline__ int bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &sm, int blk, int blocks,
+                                         int count)
 {
     // (the wave index is uniform: the partner loops then run on scalar registers)
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int ng = a.gcount[2];
-    for (int gi = blk; gi < ng; gi += blocks) {
-        const int32_t root = a.groot[a.n - 1 - gi];
+    int32_t *slot = a.groot + (a.n - 1 - blk);   // the block's k-th group: slot[-k * blocks]
+    int left = 0;
+    for (int k = 0; k < count; ++k) {
+        const int32_t root = slot[-(int64_t)k * blocks];
         const int g = a.gsize[root];
         const int nw = (g + 63) >> 6;
         int S = 1;
         while (nw * S * 2 <= GROUP_BLOCK / 64) S *= 2;
         const int t = (w / S) * 64 + lane, sub = w % S;
-        BlockPol<GROUP_BLOCK, NL> P{sm, t, g, S, sub, 0.0, {}};
+        BlockPol<GROUP_BLOCK, NL, WHOLE> P{sm, t, g, S, sub, 0.0, {}};
         // the member of rank t
         const int32_t start = a.gstart[root];
         if (P.owner()) sm.idx[t] = a.gmem[start + t];
@@ -1588,7 +1658,7 @@ __device__ __forceinline__ void bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &s
             const double tr = wave_max_all(rcd);
             if (lane == 0 && P.owner()) sm.trho[t >> 6] = tr;
         }
-        {
+        if (!WHOLE) {
             // the group's frame: its x-y extent and what its members travel
             const bool in = t < g;
             const double far = bs_block_max(sm, in ? __builtin_fmax(fabs(y[3]), fabs(y[4])) : 0.0) *
@@ -1602,6 +1672,15 @@ __device__ __forceinline__ void bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &s
             P.fr.y0 = y0;
             P.fr.scale = side > 0.0 && side < 1e300 ? 16000.0 / side : 0.0;
         }
+        if (!WHOLE && bs_crowded(sm, t, g, S, P.owner(), rcd, y)) {
+            // (every thread has read its root, and LDS is free behind the count)
+            if (threadIdx.x == 0) {
+                slot[-(int64_t)k * blocks] = slot[-(int64_t)left * blocks];
+                slot[-(int64_t)left * blocks] = root;
+            }
+            ++left;
+            continue;
+        }
         bool failed;
         [[clang::always_inline]] failed = bs_run(a, P, y);
         if (failed && threadIdx.x == 0) atomicOr(a.status, ST_NOCONV);
@@ -1614,6 +1693,8 @@ __device__ __forceinline__ void bs_medium(const BsDev &a, BsSmem<GROUP_BLOCK> &s
         }
         __syncthreads();   // LDS reuse by the next group
     }
+    __syncthreads();   // the roots put forward
+    return left;
 }
 
 // Both classes in one launch, so that the small groups run beside the medium
@@ -1631,9 +1712,12 @@ template <int NL>
 __global__ __launch_bounds__(GROUP_BLOCK) void k_bs(BsDev a)
 {
     __shared__ BsLds sm;
-    if (blockIdx.x < BS_MEDIUM)
-        bs_medium<NL>(a, sm.medium, (int)blockIdx.x, BS_MEDIUM);
-    else
+    if (blockIdx.x < BS_MEDIUM) {
+        const int blk = (int)blockIdx.x, ng = a.gcount[2];
+        const int count = ng > blk ? (ng - blk + BS_MEDIUM - 1) / BS_MEDIUM : 0;
+        const int left = bs_medium<NL, false>(a, sm.medium, blk, BS_MEDIUM, count);
+        if (left) bs_medium<NL, true>(a, sm.medium, blk, BS_MEDIUM, left);
+    } else
         bs_lanes<BS_GS, NL>(a, sm.irc, (int)blockIdx.x - BS_MEDIUM, BS_SMALL);
 }
 

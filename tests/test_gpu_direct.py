@@ -372,3 +372,77 @@ def test_members_without_a_radius(dev, n, L, s):
     ep, ev = _rel(out, ref, ("x", "y", "z")), _rel(out, ref, ("vx", "vy", "vz"))
     _say(f"{n} bodies, {L}x{s}: position {ep:.2e} velocity {ev:.2e}")
     assert ep < 1e-11 and ev < 1e-11
+
+
+@pytest.mark.parametrize("n, L, s", [(9, 1, 1), (33, 2, 2), (64, 1, 1), (65, 1, 1), (100, 2, 2), (129, 1, 1),
+                                     (257, 1, 1), (512, 1, 1)])
+def test_crowded_groups(dev, n, L, s):
+    # groups whose members all meet are evaluated partner by partner: sizes
+    # around the 64 members of a wave and the numbers of waves that share a
+    # member; tolerance as for the other groups
+    d = W.random_cloud(n, seed=n, spread=0.01)
+    ring = {k: d[k].copy() for k in ("x", "y", "z", "vx", "vy", "vz", "m")}
+    for k in ("vx", "vy", "vz"):
+        ring[k] *= 0.01
+    ring["x"] += 1.0
+    ring["vy"] += G ** 0.5
+    ring["m"][:] = 1e-9
+    n1 = 0.08 / (1e-9 / 3.0) ** (1.0 / 3.0)
+    cfg = N.Config(G=G, m_star=1.0, dt=1.0, n1=n1, n2=0.0, slevels=L, substeps=s, direct=1,
+                   level_capacity=n * n)
+    st = N.State.from_numpy(ring)
+    ws = N.Workspace(n, cfg)
+    ref = oracle.state_copy(ring)
+    for _ in range(2):
+        assert N.step(st, cfg, ws) == N.OK
+        r = oracle.step_direct(ref, G, 1.0, 1.0, n1, 0.0, L, s, rk_steps=200)
+        assert r[6] == 0 and N.group_stats(n, cfg, ws) == r[5] and r[5][1] == n
+    out = st.numpy()
+    ep, ev = _rel(out, ref, ("x", "y", "z")), _rel(out, ref, ("vx", "vy", "vz"))
+    _say(f"crowded group of {n}, {L}x{s}: position {ep:.2e} velocity {ev:.2e}")
+    assert ep < 1e-11 and ev < 1e-11
+
+
+def test_crowded_groups_beside_others(dev):
+    # 600 groups of 9 bodies, several to a workgroup: clouds whose members all
+    # meet and spread during the step, and chains whose members meet their
+    # neighbours and end the step as close together as the clouds began.  Each
+    # group is integrated once, whatever it has become: without masses no group
+    # feels another, so that each third of them alone, with a workgroup per
+    # group, ends in the same bits.
+    rng = np.random.default_rng(4)
+    g, dt = 9, 4.0
+    thirds = []
+    for a in (1.0, 1.2, 1.4):
+        rows = {k: [] for k in ("x", "y", "z", "vx", "vy", "vz")}
+        for q in range(200):
+            c, s, v = np.cos(np.pi * q / 100), np.sin(np.pi * q / 100), (G / a) ** 0.5
+            if q % 2:
+                off, end = rng.uniform(-5e-4, 5e-4, (3, g)), 8.0
+            else:
+                off, end = rng.uniform(-1e-4, 1e-4, (3, g)), 0.1
+                off[1] += 1.3e-3 * (np.arange(g) - 4)
+            vel = off * (end - 1.0) / dt
+            rows["x"].append(a * c + off[0] * c - off[1] * s)
+            rows["y"].append(a * s + off[0] * s + off[1] * c)
+            rows["z"].append(off[2])
+            rows["vx"].append(-v * s + vel[0] * c - vel[1] * s)
+            rows["vy"].append(v * c + vel[0] * s + vel[1] * c)
+            rows["vz"].append(vel[2])
+        thirds.append({k: np.concatenate(v) for k, v in rows.items()})
+    cfg = N.Config(G=G, m_star=1.0, dt=dt, n1=0.0, n2=2.1e-3 / (dt * G ** 0.5), slevels=1, substeps=1,
+                   direct=1, level_capacity=1 << 17)
+
+    def stepped(d, groups):
+        d = dict(d, m=np.zeros(d["x"].size))
+        st = N.State.from_numpy(d)
+        ws = N.Workspace(st.n, cfg)
+        assert N.step(st, cfg, ws) == N.OK
+        assert N.group_stats(st.n, cfg, ws) == (groups, g)
+        return st.numpy()
+
+    out = stepped({k: np.concatenate([t[k] for t in thirds]) for k in thirds[0]}, 600)
+    for q, t in enumerate(thirds):
+        alone = stepped(t, 200)
+        for k in ("x", "y", "z", "vx", "vy", "vz"):
+            assert np.array_equal(out[k][q * 200 * g:(q + 1) * 200 * g], alone[k]), (q, k)
